@@ -371,7 +371,7 @@ static bool mfma_ok(const Gemm& a) {
 static bool combo_used(const Gemm& a) {
   if (a.ta && a.tb) return false;
   if (a.ta) return a.c_f32 && a.epi == EPI_STORE;                                             // weight gradient
-  if (a.tb) return a.c_f32 ? (a.epi == EPI_RES) : (a.epi == EPI_STORE || a.epi == EPI_MUL_DGELU);  // input gradient
+  if (a.tb) return a.c_f32 ? (a.epi == EPI_RES || a.epi == EPI_STORE) : (a.epi == EPI_STORE || a.epi == EPI_MUL_DGELU);  // input gradient
   return a.c_f32 ? (a.epi == EPI_BIAS || a.epi == EPI_BIAS_RES)                                 // forward
                  : (a.epi == EPI_BIAS || a.epi == EPI_BIAS_RES || a.epi == EPI_BIAS_GELU);
 }
@@ -384,7 +384,7 @@ bool gemm_epilogue_vec_ok(const Gemm& a) {
   return ok;
 }
 
-bool gemm_uses_mfma(int dt, const Gemm& a) { return dt != 0 && mfma_ok(a) && combo_used(a); }
+bool gemm_uses_mfma(int dt, const Gemm& a) { return dt != 0 && (mfma_ok(a) || gemm_dma_ok(a)) && combo_used(a); }
 
 typedef Cfg<128, 128, 32, 2, 2> Cfg0;
 
@@ -457,37 +457,15 @@ void gemm(int dt, const Gemm& a, hipStream_t st) {
   if (a.c_f32 && (a.epi == EPI_BIAS_GELU || a.epi == EPI_MUL_DGELU)) return;  // not used by the step
   if (gemm_uses_mfma(dt, a) && (!a.ta || a.ldc == a.N)) {
     if (g_cfg_override != 0 && gemm_dma_ok(a)) {
-      // Weight gradients: 256x128 tiles (128x128 for small outputs), split over K.
-      // Forward and input-gradient products with at least 4096 rows and K a multiple of 64: the two-group
-      // kernel with 256x256 or 192x256 tiles, one workgroup per CU, whichever fills whole rounds of 256
-      // CUs better (M = 12608, N = 768: 198 tiles of 192x256 against 150 of 256x256); wide outputs with
-      // a short K do better with 256x128 tiles, two workgroups per CU, whose prologues and epilogues
-      // overlap.  Everything else, and products whose large tiles would leave many CUs idle: 128x128 tiles,
-      // three per CU.
-      if (g_cfg_override < 0 && gemm_dma_skinny(a, st)) return;
-      int v = g_cfg_override >= 10 ? g_cfg_override - 10 : 1;
-      if (g_cfg_override < 0) {
-        v = (a.ta || a.N >= 3072) ? 2 : 1;
-        if (a.ta && (int64_t)a.M * a.N <= 1024 * 1024) v = 1;
-        if (!a.ta && a.M >= 4096 && a.K % 64 == 0) {
-          const int tn = cdiv(a.N, 256);
-          const int t192 = cdiv(a.M, 192) * tn, t256 = cdiv(a.M, 256) * tn;
-          if (a.N >= 3072 && (a.K < 1024 || a.tb)) {
-            // wide and short: 192-row tiles only when their last round of 256 is (nearly) full, as for the
-            // 12288 tokens of BERT-base (768 tiles at N = 3072; 9-10 % faster than 256x128 there)
-            const int last = t192 % 256;
-            if (last == 0 || last >= 224) v = 6;
-          } else {
-            v = cdiv(t192, 256) * 192 < cdiv(t256, 256) * 256 ? 6 : 5;
-            // fewer tiles than 60 % of the CUs of their rounds (8192 tokens at N = 768: 129 tiles): 128x128 tiles,
-            // three workgroups per CU, fill the chip better (6-13 % faster on those five products)
-            const int tiles = v == 6 ? t192 : t256;
-            if (tiles * 10 < cdiv(tiles, 256) * 256 * 6) v = 1;
-          }
-        }
+      if (g_cfg_override >= 10) { gemm_dma(a, g_cfg_override - 10, st); return; }
+      if (!a.ta) {
+        if (!gemm_dma_skinny(a, st)) gemm_dma(a, gemm_dma_variant(a), st);
+        return;
       }
-      gemm_dma(a, v, st);
-      return;
+      // a weight gradient alone: 256x128 tiles (128x128 for small outputs) split over a long K, otherwise one
+      // group of its own
+      if (a.K % 32 == 0 && a.K >= 2048) { gemm_dma(a, (int64_t)a.M * a.N <= 1024 * 1024 ? 1 : 2, st); return; }
+      if (gemm_wgrad_group(&a, 1, st, nullptr, nullptr, nullptr)) return;
     }
     dispatch_mfma<Cfg0>(a, st);
     return;

@@ -16,9 +16,11 @@
 // Both use an XOR swizzle of the 16-byte slot index (applied to the global
 // address each lane fetches), which makes the fragment reads bank-conflict free.
 //
-// Requirements checked by the host: K a multiple of BK (no zero fill exists on
-// this path), 16-byte aligned rows.  Rows / columns past the edge are clamped to
-// the last valid one: they only feed outputs that are never stored.
+// Requirements checked by the host: 16-byte aligned rows, K a multiple of BK or a
+// kernel with TAIL.  Rows / columns past the edge are clamped to the last valid
+// one: they only feed outputs that are never stored.  With TAIL the lanes whose k
+// lies past the end fetch a line of zeros instead.
+#include <algorithm>
 #include "common.h"
 #include "kernels.h"
 #include "gemm_epilogue.h"
@@ -32,7 +34,9 @@ namespace {
 #define PT_GLB(p) ((const __attribute__((address_space(1))) void*)(p))
 typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf16x4;
 
-constexpr int kBK = 32;
+
+// what lanes past the end of the contraction fetch
+__device__ __attribute__((aligned(64))) const unsigned int g_zeros[16] = {};
 
 __device__ __forceinline__ void compiler_fence() { asm volatile("" ::: "memory"); }
 
@@ -75,13 +79,22 @@ struct TileK {
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) foff[ks] = row * ROWB + (((2 * ks + (lane >> 5)) ^ swzk(row)) << 4);
   }
-  __device__ __forceinline__ void issue_one(unsigned char* tile, int wave, int i) {
-    __builtin_amdgcn_global_load_lds(PT_GLB(gp[i]), PT_LDS(tile + (wave * LOADS + i) * 1024), 16, 0, 0);
+  // klim (TAIL only): k values of this tile that exist, a multiple of 8
+  template <bool TAIL = false>
+  __device__ __forceinline__ void issue_one(unsigned char* tile, int wave, int i, int klim = BK) {
+    const bf16* src = gp[i];
+    if (TAIL) {
+      const int lane = threadIdx.x & 63;
+      const int c = (lane % CPR) ^ swzk(RPL * (wave * LOADS + i) + lane / CPR);
+      if (8 * c >= klim) src = reinterpret_cast<const bf16*>(g_zeros);
+    }
+    __builtin_amdgcn_global_load_lds(PT_GLB(src), PT_LDS(tile + (wave * LOADS + i) * 1024), 16, 0, 0);
     gp[i] += BK;
   }
-  __device__ __forceinline__ void issue(unsigned char* tile, int wave) {
+  template <bool TAIL = false>
+  __device__ __forceinline__ void issue(unsigned char* tile, int wave, int klim = BK) {
 #pragma unroll
-    for (int i = 0; i < LOADS; ++i) issue_one(tile, wave, i);
+    for (int i = 0; i < LOADS; ++i) issue_one<TAIL>(tile, wave, i, klim);
   }
   // fragments of all row blocks for one k-step, issued as inline assembly (see TileS::read)
   static constexpr int READS = NFRAG;   // LDS instructions per k-step
@@ -100,7 +113,12 @@ struct TileK {
 // the k+8 group to the other 32 bytes of each, which makes any two groups served together conflict-free
 // (checked against a bank model; the earlier (k & 3) << 1 left two-way conflicts, 21 % of the cycles of the
 // weight-gradient kernel by SQ_LDS_BANK_CONFLICT).
-__device__ __forceinline__ constexpr int swz(int k) { return ((k & 3) << 2) ^ (((k >> 3) & 1) << 1); }
+// Rows of 128 bytes (64-row tiles): two k rows share the 256 bytes of the banks, so bit 1 of k moves a group's
+// rows to the other 64 bytes of their half and the k + 8 group to the other 32.
+template <int ROWS>
+__device__ __forceinline__ constexpr int swz(int k) {
+  return ROWS == 64 ? (((k >> 1) & 1) << 2) ^ (((k >> 3) & 1) << 1) : ((k & 3) << 2) ^ (((k >> 3) & 1) << 1);
+}
 // Fragments come from ds_read_b64_tr_b16 (each lane gets four consecutive k of one row).  All fragment
 // reads are issued as inline assembly: the compiler would otherwise wait for every outstanding
 // global->LDS load before a transpose read, which serialises the pipeline, and explicit lgkmcnt waits
@@ -113,7 +131,7 @@ struct TileS {
   static constexpr int CPR = ROWS / 8;                           // 16-byte chunks per k row
   static constexpr int KS = BK / 16;
   static_assert(BK % (KPL * NW) == 0 && KPL >= 1, "tile must divide over the waves");
-  static_assert(CPR >= 16, "swz permutes chunks within groups of 16");
+  static_assert(CPR >= 16 || CPR == 8, "swz permutes chunks within groups of 16, or of 8");
   const bf16* gp[LOADS];
   int64_t gstep;
   unsigned foff[NFRAG];    // fragment byte offsets (k-step 0, first half) per 32-row block
@@ -123,7 +141,7 @@ struct TileS {
 #pragma unroll
     for (int i = 0; i < LOADS; ++i) {
       const int k = KPL * (wave * LOADS + i) + lane / CPR;
-      const int c = (lane % CPR) ^ swz(k);
+      const int c = (lane % CPR) ^ swz<ROWS>(k);
       int gr = r0 + 8 * c;
       gr = gr + 8 <= R ? gr : (R - 8);   // R >= 8 and R % 8 == 0 are checked by the host
       gp[i] = p + (int64_t)(k0 + k) * ld + gr;
@@ -134,16 +152,23 @@ struct TileS {
 #pragma unroll
     for (int j = 0; j < NFRAG; ++j) {
       const int col = rbase + j * 32 + (grp & 1) * 16 + 4 * (l16 & 3);
-      foff[j] = k * ROWB + (((col >> 3) ^ swz(k)) << 4) + (col & 7) * 2;
+      foff[j] = k * ROWB + (((col >> 3) ^ swz<ROWS>(k)) << 4) + (col & 7) * 2;
     }
   }
-  __device__ __forceinline__ void issue_one(unsigned char* tile, int wave, int i) {
-    __builtin_amdgcn_global_load_lds(PT_GLB(gp[i]), PT_LDS(tile + (wave * LOADS + i) * 1024), 16, 0, 0);
+  template <bool TAIL = false>
+  __device__ __forceinline__ void issue_one(unsigned char* tile, int wave, int i, int klim = BK) {
+    const bf16* src = gp[i];
+    if (TAIL) {
+      const int lane = threadIdx.x & 63;
+      if (KPL * (wave * LOADS + i) + lane / CPR >= klim) src = reinterpret_cast<const bf16*>(g_zeros);
+    }
+    __builtin_amdgcn_global_load_lds(PT_GLB(src), PT_LDS(tile + (wave * LOADS + i) * 1024), 16, 0, 0);
     gp[i] += gstep;
   }
-  __device__ __forceinline__ void issue(unsigned char* tile, int wave) {
+  template <bool TAIL = false>
+  __device__ __forceinline__ void issue(unsigned char* tile, int wave, int klim = BK) {
 #pragma unroll
-    for (int i = 0; i < LOADS; ++i) issue_one(tile, wave, i);
+    for (int i = 0; i < LOADS; ++i) issue_one<TAIL>(tile, wave, i, klim);
   }
   static constexpr int READS = 2 * NFRAG;
   // ks is a compile-time constant at every call site (unrolled), so the offsets fold to immediates
@@ -164,7 +189,7 @@ struct TileS {
     float s = 0.f;
 #pragma unroll
     for (int k = 0; k < BK; ++k) {
-      const int c = (n >> 3) ^ swz(k);
+      const int c = (n >> 3) ^ swz<ROWS>(k);
       s += to_f32(*reinterpret_cast<const bf16*>(lds + k * ROWB + c * 16 + (n & 7) * 2));
     }
     return s;
@@ -197,10 +222,11 @@ __device__ __forceinline__ void wait_vm() {
 constexpr int dma_waves_per_simd(int lds_bytes, int waves) {
   return (lds_bytes <= 48 * 1024 ? 3 : (lds_bytes <= 80 * 1024 ? 2 : 1)) * waves / 4;
 }
-template <int BM, int BN, int WGM, int WGN, int kNS, int BK, bool TA, bool TB, int EPI, typename TC>
-__global__ __launch_bounds__(64 * WGM * WGN, dma_waves_per_simd((BM + BN) * BK * 2 * kNS, WGM * WGN))
-void gemm_dma_kernel(GemmDev<bf16> g, SplitArgs sp, int tiles_m, int tiles_n,
-                                                                  int group_n, int vec_ok) {
+// dma_run computes one output tile (rows m0.., columns n0..) over the k tiles kt0 .. kt0 + n - 1 and stores it
+// to slab `split`; all threads of the workgroup take part.  TAIL: g.K need not be a multiple of BK.
+template <int BM, int BN, int WGM, int WGN, int kNS, int BK, bool TA, bool TB, int EPI, typename TC, bool TAIL>
+__device__ __forceinline__ void dma_run(const GemmDev<bf16>& g, const SplitArgs& sp, int split, int kt0, int n, int m0, int n0,
+                                        int vec_ok) {
   constexpr int NW = WGM * WGN;
   constexpr int WTM = BM / WGM, WTN = BN / WGN, TM = WTM / 32, TN = WTN / 32;
   typedef typename TileSel<TA, BM, NW, TM, BK>::type LA;    // A strided when stored [K,M]
@@ -212,27 +238,12 @@ void gemm_dma_kernel(GemmDev<bf16> g, SplitArgs sp, int tiles_m, int tiles_n,
   constexpr int LDS_BYTES = kNS * STAGE > EPI_BYTES ? kNS * STAGE : EPI_BYTES;
   constexpr int LPT = LA::LOADS + LB::LOADS;  // DMA loads per thread per tile
   constexpr int RPS = LA::READS + LB::READS;  // LDS read instructions per k-step
-  static_assert(LPT * (kNS >= 4 ? 2 : 1) < 64, "vmcnt is a 6-bit counter");
+  static_assert(LPT * (kNS - 2) < 64, "vmcnt is a 6-bit counter");
   static_assert(RPS <= 15, "lgkmcnt is a 4-bit counter");
-  static_assert(kNS >= 2 && LDS_BYTES <= 160 * 1024, "stages must fit the LDS");
+  static_assert(kNS >= 2 && kNS <= 6 && LDS_BYTES <= 160 * 1024, "stages must fit the LDS");
   __shared__ __attribute__((aligned(1024))) unsigned char lds[LDS_BYTES];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave / WGN, wn = wave % WGN;
-  // Workgroups are dealt to the 8 XCDs round-robin by their index, and each XCD has an L2 of its own.  The
-  // index is remapped so that one XCD works through a contiguous range of the sequence
-  //   for split: for column group (group_n tile columns): for tile row: for tile column in the group
-  // which keeps a K slice (split-K) or a band of B panels small enough to stay in that L2 while the A panels
-  // stream past it once.
-  const int total_tiles = tiles_m * tiles_n, total_work = total_tiles * sp.splits;
-  const int per = (total_work + 7) >> 3;
-  const int work = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
-  if (work >= total_work) return;
-  const int split = work / total_tiles;
-  const int t = work - split * total_tiles;
-  const int grp = t / (group_n * tiles_m);
-  const int rem = t - grp * group_n * tiles_m;
-  const int gw = tiles_n - grp * group_n < group_n ? tiles_n - grp * group_n : group_n;
-  const int m0 = (rem / gw) * BM, n0 = (grp * group_n + rem % gw) * BN;
 
   f32x16 acc[TM][TN];
 #pragma unroll
@@ -242,10 +253,6 @@ void gemm_dma_kernel(GemmDev<bf16> g, SplitArgs sp, int tiles_m, int tiles_n,
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
 
-  const int nk_all = g.K / BK;
-  const int kt0 = split * sp.tiles_per_split;
-  const int kt1 = (kt0 + sp.tiles_per_split < nk_all) ? kt0 + sp.tiles_per_split : nk_all;
-  const int n = kt1 > kt0 ? kt1 - kt0 : 0;
   const bool do_colsum = !TB && sp.colsum != nullptr && m0 == 0;
   float cs = 0.f;
 
@@ -253,29 +260,30 @@ void gemm_dma_kernel(GemmDev<bf16> g, SplitArgs sp, int tiles_m, int tiles_n,
   LB tb;
   ta.setup(g.A, g.lda, g.M, m0, kt0 * BK, wm * WTM, wave, lane);
   tb.setup(g.B, g.ldb, g.N, n0, kt0 * BK, wn * WTN, wave, lane);
+  auto issue = [&](int t, int stage) {
+    const int klim = TAIL ? g.K - (kt0 + t) * BK : BK;
+    ta.template issue<TAIL>(lds + stage * STAGE, wave, klim);
+    tb.template issue<TAIL>(lds + stage * STAGE + LA::BYTES, wave, klim);
+  };
 
   int fill = 0;  // stage the next issued tile goes to
 #pragma unroll
   for (int s = 0; s < kNS - 1; ++s)
-    if (s < n) {
-      ta.issue(lds + s * STAGE, wave);
-      tb.issue(lds + s * STAGE + LA::BYTES, wave);
-    }
+    if (s < n) issue(s, s);
   fill = kNS - 1;
   int cur = 0;   // stage of the tile being consumed
 
   for (int it = 0; it < n; ++it) {
     // this wave's loads of tile `it` have landed when at most the loads of the later tiles are pending
-    if (kNS >= 4 && it + 2 < n) wait_vm<2 * LPT>();
+    if (kNS >= 6 && it + 4 < n) wait_vm<(kNS >= 6 ? 4 : 0) * LPT>();
+    else if (kNS >= 5 && it + 3 < n) wait_vm<(kNS >= 5 ? 3 : 0) * LPT>();
+    else if (kNS >= 4 && it + 2 < n) wait_vm<(kNS >= 4 ? 2 : 0) * LPT>();
     else if (kNS >= 3 && it + 1 < n) wait_vm<LPT>();
     else wait_vm<0>();
     compiler_fence();
     __builtin_amdgcn_s_barrier();   // everybody's loads of tile `it` have landed, and tile it-1 is fully consumed
     compiler_fence();
-    if (it + kNS - 1 < n) {
-      ta.issue(lds + fill * STAGE, wave);
-      tb.issue(lds + fill * STAGE + LA::BYTES, wave);
-    }
+    if (it + kNS - 1 < n) issue(it + kNS - 1, fill);
     fill = fill + 1 == kNS ? 0 : fill + 1;
     const unsigned char* sa = lds + cur * STAGE;
     const unsigned char* sb = sa + LA::BYTES;
@@ -324,6 +332,29 @@ void gemm_dma_kernel(GemmDev<bf16> g, SplitArgs sp, int tiles_m, int tiles_n,
                                                    m0 + wm * WTM, n0 + wn * WTN, lane, vec_ok);
 }
 
+// Workgroups are dealt to the 8 XCDs round-robin by their index, and each XCD has an L2 of its own.  The
+// index is remapped so that one XCD works through a contiguous range of the sequence
+//   for split: for column group (group_n tile columns): for tile row: for tile column in the group
+// which keeps a K slice (split-K) or a band of B panels small enough to stay in that L2 while the A panels
+// stream past it once.
+template <int BM, int BN, int WGM, int WGN, int kNS, int BK, bool TA, bool TB, int EPI, typename TC, bool TAIL>
+__global__ __launch_bounds__(64 * WGM * WGN, dma_waves_per_simd((BM + BN) * BK * 2 * kNS, WGM * WGN))
+void gemm_dma_kernel(GemmDev<bf16> g, SplitArgs sp, int tiles_m, int tiles_n, int group_n, int vec_ok) {
+  const int total_tiles = tiles_m * tiles_n, total_work = total_tiles * sp.splits;
+  const int per = (total_work + 7) >> 3;
+  const int work = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
+  if (work >= total_work) return;
+  const int split = work / total_tiles;
+  const int t = work - split * total_tiles;
+  const int grp = t / (group_n * tiles_m);
+  const int rem = t - grp * group_n * tiles_m;
+  const int gw = tiles_n - grp * group_n < group_n ? tiles_n - grp * group_n : group_n;
+  const int m0 = (rem / gw) * BM, n0 = (grp * group_n + rem % gw) * BN;
+  const int nk_all = TAIL ? (g.K + BK - 1) / BK : g.K / BK;
+  const int kt0 = split * sp.tiles_per_split;
+  const int kt1 = (kt0 + sp.tiles_per_split < nk_all) ? kt0 + sp.tiles_per_split : nk_all;
+  dma_run<BM, BN, WGM, WGN, kNS, BK, TA, TB, EPI, TC, TAIL>(g, sp, split, kt0, kt1 > kt0 ? kt1 - kt0 : 0, m0, n0, vec_ok);
+}
 
 // ---- 256x256x64 (or 192x256x64) tiles, two wave groups in alternating roles ----
 // The eight waves form two groups of four, one wave of each group per SIMD.  Time is cut into phases that
@@ -351,8 +382,8 @@ __device__ __forceinline__ unsigned char* pp_lds() {
   __shared__ __attribute__((aligned(1024))) unsigned char lds[BYTES];
   return lds;
 }
-constexpr int kPpLdsBytes256 = 160 * 1024;   // 256-row tiles: three A stages and two B stages of 32 KB
-template <int BM, bool WHOLE, bool TA, bool TB, int EPI, typename TC>
+constexpr int pp_lds_bytes(int bm) { return 3 * bm * 128 + 2 * 256 * 128; }   // three A stages and two B stages
+template <int BM, bool WHOLE, bool TA, bool TB, int EPI, typename TC, bool TAIL>
 __device__ __forceinline__ void pp_run(const GemmDev<bf16>& g, const SplitArgs& sp, int split, int kt0, int n, int m0, int n0,
                                        int vec_ok) {
   constexpr int BN = 256, WGN = 4, BK = 64, NW = 8, NSA = 3, NSB = 2;
@@ -367,7 +398,7 @@ __device__ __forceinline__ void pp_run(const GemmDev<bf16>& g, const SplitArgs& 
   constexpr int KSF = 4 / NH;              // k-steps (MFMA depth 16) per half
   constexpr int NPART = 2 * NH - 1;        // A(t+2) goes out in this many parts, one per phase after the first
   static_assert(LA::LOADS >= NPART, "A loads are spread over the phases");
-  static_assert(BM != 256 || LDS_BYTES == kPpLdsBytes256, "kPpLdsBytes256 names the 256-row kernels' array");
+  static_assert(LDS_BYTES == pp_lds_bytes(BM), "pp_lds_bytes names this kernel's array");
   unsigned char* const lds = pp_lds<LDS_BYTES>();
   unsigned char* const ldsB = lds + NSA * LA::BYTES;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -389,6 +420,8 @@ __device__ __forceinline__ void pp_run(const GemmDev<bf16>& g, const SplitArgs& 
   LB tb;
   ta.setup(g.A, g.lda, g.M, m0, kt0 * BK, wm * WTM, wave, lane);
   tb.setup(g.B, g.ldb, g.N, n0, kt0 * BK, wn * WTN, wave, lane);
+
+  auto klim = [&](int t) { return TAIL ? g.K - (kt0 + t) * BK : BK; };   // k values of tile t that exist
 
   bf16x8 fa[KSF][TM], fb[KSF][TN];
   // fragment reads of one half (k-steps KSF*half ..), complete once fetched() returns
@@ -441,11 +474,11 @@ __device__ __forceinline__ void pp_run(const GemmDev<bf16>& g, const SplitArgs& 
   };
 
   if (n > 0) {
-    ta.issue(lds, wave);
-    tb.issue(ldsB, wave);
+    ta.template issue<TAIL>(lds, wave, klim(0));
+    tb.template issue<TAIL>(ldsB, wave, klim(0));
   }
   if (n > 1) {
-    ta.issue(lds + LA::BYTES, wave);
+    ta.template issue<TAIL>(lds + LA::BYTES, wave, klim(1));
     wait_vm<LA::LOADS>();
   } else {
     wait_vm<0>();
@@ -469,15 +502,15 @@ __device__ __forceinline__ void pp_run(const GemmDev<bf16>& g, const SplitArgs& 
         // fetch phase: B(t+1) with the first half, a part of A(t+2) with the others
         fetch(sa, sb, h);
         if (h == 0) {
-          if (moreB) tb.issue(dstB, wave);
+          if (moreB) tb.template issue<TAIL>(dstB, wave, klim(t + 1));
         } else if (moreA) {
 #pragma unroll
-          for (int q = part_lo(2 * h - 1); q < part_lo(2 * h); ++q) ta.issue_one(dstA, wave, q);
+          for (int q = part_lo(2 * h - 1); q < part_lo(2 * h); ++q) ta.template issue_one<TAIL>(dstA, wave, q, klim(t + 2));
         }
         fetched();
         phase_end();
         // compute phase
-        compute(moreA, part_lo(2 * h + 1) - part_lo(2 * h), [&](int q) { ta.issue_one(dstA, wave, part_lo(2 * h) + q); });
+        compute(moreA, part_lo(2 * h + 1) - part_lo(2 * h), [&](int q) { ta.template issue_one<TAIL>(dstA, wave, part_lo(2 * h) + q, klim(t + 2)); });
         if constexpr (!TB) {
           if (h == 0 && do_colsum) cs += LB::colsum(sb, tid);   // threads 0..255 are this group
         }
@@ -490,7 +523,7 @@ __device__ __forceinline__ void pp_run(const GemmDev<bf16>& g, const SplitArgs& 
   } else {
     int ia = 0, ib = 0;
     // first phase of tile 0: nothing to compute yet
-    if (n > 1) tb.issue(ldsB + LB::BYTES, wave);
+    if (n > 1) tb.template issue<TAIL>(ldsB + LB::BYTES, wave, klim(1));
     if (n > 0) phase_end();
     for (int t = 0; t < n; ++t) {
       const bool moreA = t + 2 < n;
@@ -503,7 +536,7 @@ __device__ __forceinline__ void pp_run(const GemmDev<bf16>& g, const SplitArgs& 
         fetch(sa, sb, h);
         if (moreA) {
 #pragma unroll
-          for (int q = part_lo(2 * h); q < part_lo(2 * h + 1); ++q) ta.issue_one(dstA, wave, q);
+          for (int q = part_lo(2 * h); q < part_lo(2 * h + 1); ++q) ta.template issue_one<TAIL>(dstA, wave, q, klim(t + 2));
         }
         fetched();
         if (h == NH - 1) tile_done(moreA);
@@ -511,11 +544,11 @@ __device__ __forceinline__ void pp_run(const GemmDev<bf16>& g, const SplitArgs& 
         // compute phase: the next part of A(t+2), or, in the first phase of tile t + 1, B(t+2) into the stage
         // tile t's B has just left
         if (h < NH - 1) {
-          compute(moreA, part_lo(2 * h + 2) - part_lo(2 * h + 1), [&](int q) { ta.issue_one(dstA, wave, part_lo(2 * h + 1) + q); });
+          compute(moreA, part_lo(2 * h + 2) - part_lo(2 * h + 1), [&](int q) { ta.template issue_one<TAIL>(dstA, wave, part_lo(2 * h + 1) + q, klim(t + 2)); });
           phase_end();
         } else if (t + 1 < n) {
           unsigned char* const dstB = ldsB + ib * LB::BYTES;
-          compute(moreA, LB::LOADS, [&](int q) { tb.issue_one(dstB, wave, q); });
+          compute(moreA, LB::LOADS, [&](int q) { tb.template issue_one<TAIL>(dstB, wave, q, klim(t + 2)); });
           phase_end();
         }
       }
@@ -558,6 +591,8 @@ struct GroupArgs {
   LnBwdArgs<bf16, bf16, bf16> ln;   // dy and x are fp32 when ln_on == 2 (the pointers are cast back)
   int ln_on;
 };
+// TAIL: the contraction (the tokens) need not be a multiple of 64.
+template <bool TAIL>
 __global__ __launch_bounds__(512) void gemm_wgrad_group_kernel(GroupArgs ga) {
   const int total_tiles = ga.tile0[ga.nprob], total_work = total_tiles * ga.splits;
   const int per = (total_work + 7) >> 3;
@@ -568,7 +603,7 @@ __global__ __launch_bounds__(512) void gemm_wgrad_group_kernel(GroupArgs ga) {
     // The same workgroups first run a LayerNorm backward pass that does not depend on these products (the
     // block's last one, whose result only the next block reads): 135 MB more, still well inside what 40 CUs
     // stream while the others work through their 98 k tiles.
-    float* red = reinterpret_cast<float*>(pp_lds<kPpLdsBytes256>());
+    float* red = reinterpret_cast<float*>(pp_lds<pp_lds_bytes(256)>());
     const int rid = (int)blockIdx.x - 8 * per, nred = (int)gridDim.x - 8 * per;
     if (ga.ln_on == 1) {
       if (ga.ln.D <= 768) ln_bwd_rows<bf16, bf16, bf16, 3, 8>(ga.ln, red, rid, nred);
@@ -599,11 +634,33 @@ __global__ __launch_bounds__(512) void gemm_wgrad_group_kernel(GroupArgs ga) {
   while (p + 1 < ga.nprob && tt >= ga.tile0[p + 1]) ++p;
   const int local = tt - ga.tile0[p];
   const SplitArgs sp{ga.splits, ga.tiles_per_split, ga.slab[p], ga.colsum[p]};
-  const int nk_all = ga.g[p].K / 64;
+  const int nk_all = TAIL ? (ga.g[p].K + 63) / 64 : ga.g[p].K / 64;
   const int kt0 = split * ga.tiles_per_split;
   const int kt1 = (kt0 + ga.tiles_per_split < nk_all) ? kt0 + ga.tiles_per_split : nk_all;
-  pp_run<256, false, true, false, EPI_STORE, float>(ga.g[p], sp, split, kt0, kt1 > kt0 ? kt1 - kt0 : 0, (local / ga.tiles_n[p]) * 256,
-                                             (local % ga.tiles_n[p]) * 256, ga.vec_ok[p]);
+  pp_run<256, false, true, false, EPI_STORE, float, TAIL>(ga.g[p], sp, split, kt0, kt1 > kt0 ? kt1 - kt0 : 0,
+                                                          (local / ga.tiles_n[p]) * 256, (local % ga.tiles_n[p]) * 256, ga.vec_ok[p]);
+}
+
+// The same with BT x BT tiles of the single-role pipeline, for few tokens or narrow matrices, where the large tiles
+// leave most CUs without work or write split-K slabs that cost more than the products (wgrad_tiling has the line).  Two
+// workgroups per CU hide each other's loads, which bound them (8 KB per 128x64 operand tile at 45-50 GB/s per CU).
+template <int BT, int NS, int BK>
+__global__ __launch_bounds__(256, 2) void gemm_wgrad_group_small_kernel(GroupArgs ga) {
+  const int total_tiles = ga.tile0[ga.nprob], total_work = total_tiles * ga.splits;
+  const int per = (total_work + 7) >> 3;
+  const int work = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
+  if (work >= total_work) return;
+  const int split = work / total_tiles;
+  const int tt = work - split * total_tiles;
+  int p = 0;
+  while (p + 1 < ga.nprob && tt >= ga.tile0[p + 1]) ++p;
+  const int local = tt - ga.tile0[p];
+  const SplitArgs sp{ga.splits, ga.tiles_per_split, ga.slab[p], ga.colsum[p]};
+  const int nk_all = (ga.g[p].K + BK - 1) / BK;
+  const int kt0 = split * ga.tiles_per_split;
+  const int kt1 = (kt0 + ga.tiles_per_split < nk_all) ? kt0 + ga.tiles_per_split : nk_all;
+  dma_run<BT, BT, 2, 2, NS, BK, true, false, EPI_STORE, float, true>(ga.g[p], sp, split, kt0, kt1 > kt0 ? kt1 - kt0 : 0,
+                                                                         (local / ga.tiles_n[p]) * BT, (local % ga.tiles_n[p]) * BT, ga.vec_ok[p]);
 }
 
 // Workgroups are dealt to the 8 XCDs round-robin by their index; the index is remapped so that one XCD works
@@ -625,7 +682,7 @@ __global__ __launch_bounds__(512) void gemm_pp_kernel(GemmDev<bf16> g, SplitArgs
   const int kt0 = split * sp.tiles_per_split;
   const int kt1 = (kt0 + sp.tiles_per_split < nk_all) ? kt0 + sp.tiles_per_split : nk_all;
   const int n = kt1 > kt0 ? kt1 - kt0 : 0;
-  pp_run<BM, WHOLE, TA, TB, EPI, TC>(g, sp, split, kt0, n, m0, n0, vec_ok);
+  pp_run<BM, WHOLE, TA, TB, EPI, TC, false>(g, sp, split, kt0, n, m0, n0, vec_ok);
 }
 
 #ifdef PT_TUNING_HOOKS   // stand-alone experiments only; the library is built without it
@@ -636,12 +693,12 @@ constexpr int g_group_n = 0;
 constexpr int64_t g_group_bytes = 1536 << 10;  // L2 bytes a column group's B panels may take
 #endif
 
-template <int BM, int BN, int WGM, int WGN, int NS, int BK, bool TA, bool TB, int EPI, typename TC>
+template <int BM, int BN, int WGM, int WGN, int NS, int BK, bool TA, bool TB, int EPI, typename TC, bool TAIL = false>
 void launch_dma(const Gemm& a, int splits, float* cbase, int64_t slab, float* colsum_part, hipStream_t st) {
   GemmDev<bf16> g{(const bf16*)a.A, (const bf16*)a.B, cbase ? (void*)cbase : a.C, a.M, a.N, a.K, a.lda, a.ldb, a.ldc,
                   (const bf16*)a.bias, (const bf16*)a.aux, (bf16*)a.aux_out, a.ld_aux};
   const int tiles_m = cdiv(a.M, BM), tiles_n = cdiv(a.N, BN), total = tiles_m * tiles_n;
-  const int nk = a.K / BK;
+  const int nk = TAIL ? cdiv(a.K, BK) : a.K / BK;
   SplitArgs sp{splits, cdiv(nk, splits), slab, colsum_part};
   dim3 grid(8 * cdiv(total * splits, 8), 1, 1);
   // column-group width: the B panels of a group (whole K) should fit beside the streaming A panels in a 4 MB L2
@@ -652,7 +709,7 @@ void launch_dma(const Gemm& a, int splits, float* cbase, int64_t slab, float* co
     if (group_n < 1) group_n = 1;
   }
   if (group_n > tiles_n) group_n = tiles_n;
-  hipLaunchKernelGGL((gemm_dma_kernel<BM, BN, WGM, WGN, NS, BK, TA, TB, EPI, TC>), grid, dim3(64 * WGM * WGN), 0, st, g, sp,
+  hipLaunchKernelGGL((gemm_dma_kernel<BM, BN, WGM, WGN, NS, BK, TA, TB, EPI, TC, TAIL>), grid, dim3(64 * WGM * WGN), 0, st, g, sp,
                      tiles_m, tiles_n, group_n, gemm_epilogue_vec_ok(a) ? 1 : 0);
 }
 
@@ -708,11 +765,10 @@ void launch_split_epilogue(const Gemm& a, const float* part, int splits, hipStre
 }  // namespace
 
 bool gemm_dma_ok(const Gemm& a) {
-  if (a.K % kBK != 0 || a.K < kBK) return false;
-  if (!aligned16(a.A) || !aligned16(a.B) || a.lda % 8 || a.ldb % 8) return false;
-  if (a.ta && (a.M % 8 || a.M < 8)) return false;
+  if (!aligned16(a.A) || !aligned16(a.B) || a.lda % 8 || a.ldb % 8 || a.K < 1) return false;
+  if (a.ta && (a.M % 8 || a.M < 8)) return false;      // strided operands: 16-byte pieces along the rows
   if (!a.tb && (a.N % 8 || a.N < 8)) return false;
-  return a.M >= 32 && a.N >= 32;
+  return (a.ta && !a.tb) || a.K % 8 == 0;              // a k-major operand: 16-byte pieces along k
 }
 
 // workgroups a split-K weight gradient aims for: two 256x128 workgroups per CU
@@ -751,21 +807,64 @@ static void dispatch_wgrad(const Gemm& a, hipStream_t st) {
   }
 }
 
+// How the weight gradients of a launch are tiled and split.
+struct WgradTiling {
+  int bm, bn, bk, splits;   // bn == 256: the two-group kernel, otherwise the single-role pipeline
+};
+#ifdef PT_TUNING_HOOKS
+WgradTiling g_wgrad_force{};
+void gemm_set_wgrad(int bm, int bn, int bk, int splits) { g_wgrad_force = WgradTiling{bm, bn, bk, splits}; }
+#endif
+static WgradTiling wgrad_tiling(const Gemm* a, int n) {
+#ifdef PT_TUNING_HOOKS
+  if (g_wgrad_force.bm) return g_wgrad_force;
+#endif
+  // Microseconds of a launch, fitted to launches over a block's four matrices of widths 256 and 768 with 7 to 12608
+  // tokens (within 15 %; k = tokens / 1000, s splits, w workgroups on the fullest CU):
+  //   64x64 tiles    the larger of 3.6 + 13.7 k / s (one workgroup's own chain) and w (1.2 + 4.8 k / s)
+  //   128x128 tiles  the larger of 4.7 + 21.5 k / s and w (4 + 12.2 k / s)
+  //   256x256 tiles  w (6 + 33.8 k / s)
+  // and for s > 1 the slabs' summation at 4 TB/s, of which the two-group launch hides about half (WgradCarry).
+  // Width 768: 1379 tokens 39 us on 128x128 tiles against 50 on 256x256 ones with two splits, 4096 tokens 102
+  // against 94, 12608 tokens 302 against 235; width 256: 231 tokens 6.8 us on 64x64 tiles against 15.3.
+  const double k = 1e-3 * a[0].K;
+  double floats = 0;
+  for (int i = 0; i < n; ++i) floats += (double)a[i].M * a[i].N;
+  WgradTiling best{64, 64, 64, 1};
+  double best_us = 1e30;
+  auto consider = [&](int b, int s, double chain0, double chain, double each0, double each, double red) {
+    int64_t t = 0;
+    for (int i = 0; i < n; ++i) t += (int64_t)cdiv(a[i].M, b) * cdiv(a[i].N, b);
+    const double w = (double)((t * s + 255) / 256);
+    double us = std::max(chain0 + chain * k / s, w * (each0 + each * k / s));
+    if (s > 1) us += red * (4.0 + (s + 1) * floats * 1e-6);
+    if (us < best_us) { best_us = us; best = WgradTiling{b, b, 64, s}; }
+  };
+  for (int s = 1; s <= 4 && (s == 1 || a[0].K >= 512 * s); s *= 2) {
+    consider(64, s, 3.6, 13.7, 1.2, 4.8, 1.0);
+    consider(128, s, 4.7, 21.5, 4.0, 12.2, 1.0);
+  }
+  int64_t t256 = 0;
+  for (int i = 0; i < n; ++i) t256 += (int64_t)cdiv(a[i].M, 256) * cdiv(a[i].N, 256);
+  int s = (int)(256 / t256);
+  if (s > a[0].K / 256) s = a[0].K / 256;
+  if (s > 16) s = 16;
+  consider(256, s < 1 ? 1 : s, 6.0, 33.8, 6.0, 33.8, 0.5);
+  return best;
+}
+
 bool gemm_wgrad_group(const Gemm* a, int n, hipStream_t st, hipEvent_t mid, WgradCarry* carry, LnBwdRide* ln) {
   if (n < 1 || n > kMaxGroup) return false;
-  int64_t total = 0, per_split = 0;
+  int64_t per_split = 0;
   for (int i = 0; i < n; ++i) {
     const Gemm& m = a[i];
-    if (!m.ta || m.tb || !m.c_f32 || m.ldc != m.N || m.epi != EPI_STORE || !gemm_dma_ok(m) || m.K % 64 != 0) return false;
+    if (!m.ta || m.tb || !m.c_f32 || m.ldc != m.N || m.epi != EPI_STORE || !gemm_dma_ok(m)) return false;
     if (m.K != a[0].K || m.ws != a[0].ws || m.ws_floats != a[0].ws_floats || !m.ws) return false;
-    total += (int64_t)cdiv(m.M, 256) * cdiv(m.N, 256);
     per_split += (int64_t)m.M * m.N + m.N;
   }
-  const int nk = a[0].K / 64;
-  int splits = (int)(256 / total);
-  if (splits > nk / 4) splits = nk / 4;
-  if (splits > 16) splits = 16;
-  if (splits < 1) splits = 1;
+  const WgradTiling tl = wgrad_tiling(a, n);
+  const int bm = tl.bm, bn = tl.bn, nk = cdiv(a[0].K, tl.bk);
+  int splits = tl.splits;
   while (splits > 1 && (size_t)(splits * per_split) > a[0].ws_floats) --splits;
   GroupArgs ga{};
   ga.nprob = n;
@@ -787,9 +886,9 @@ bool gemm_wgrad_group(const Gemm* a, int n, hipStream_t st, hipEvent_t mid, Wgra
     ga.colsum[i] = cs;
     ga.slab[i] = splits > 1 ? mn : 0;
     ga.tile0[i] = t0;
-    ga.tiles_n[i] = cdiv(m.N, 256);
+    ga.tiles_n[i] = cdiv(m.N, bn);
     ga.vec_ok[i] = gemm_epilogue_vec_ok(m) && aligned16(cbase) ? 1 : 0;
-    t0 += cdiv(m.M, 256) * cdiv(m.N, 256);
+    t0 += cdiv(m.M, bm) * cdiv(m.N, bn);
     if (splits > 1) ws += splits * (mn + m.N);
   }
   ga.tile0[n] = t0;
@@ -797,7 +896,7 @@ bool gemm_wgrad_group(const Gemm* a, int n, hipStream_t st, hipEvent_t mid, Wgra
   // a carried reduction rides on the workgroups that fit beside this launch's own (one per CU, 256 CUs), in
   // multiples of eight (one per XCD); with fewer than eight to spare it runs on its own first
   int extra = ((256 - own) / 8) * 8;
-  if (extra < 8) extra = 0;
+  if (extra < 8 || bn != 256) extra = 0;
   const bool host_ln = ln && extra > 0 && ln->D <= 1024 && ln->D % 4 == 0 && ln->rows > 0 && ln->partial;
   if (host_ln) {
     ga.ln = LnBwdArgs<bf16, bf16, bf16>{(const bf16*)ln->dy, ln->lddy, (const bf16*)ln->x, ln->ldx, ln->mean, ln->rstd,
@@ -823,7 +922,12 @@ bool gemm_wgrad_group(const Gemm* a, int n, hipStream_t st, hipEvent_t mid, Wgra
       carry->nprob = 0;
     }
   }
-  hipLaunchKernelGGL(gemm_wgrad_group_kernel, dim3(own + extra), dim3(512), 0, st, ga);
+#define PT_WG(K_, T_) hipLaunchKernelGGL((K_), dim3(own + extra), dim3(T_), 0, st, ga)
+  if (bn == 64) PT_WG((gemm_wgrad_group_small_kernel<64, 3, 64>), 256);
+  else if (bn == 128) PT_WG((gemm_wgrad_group_small_kernel<128, 2, 64>), 256);
+  else if (a[0].K % 64 != 0) PT_WG((gemm_wgrad_group_kernel<true>), 512);
+  else PT_WG((gemm_wgrad_group_kernel<false>), 512);
+#undef PT_WG
   if (mid) (void)hipEventRecord(mid, st);
   if (splits > 1) {
     WgradCarry now;
@@ -843,7 +947,8 @@ template <int BM>
 static void dispatch_pp_fwd(const Gemm& a, hipStream_t st) {
 #define PT_L(TB_, EPI_, TC_) launch_pp<BM, false, TB_, EPI_, TC_>(a, 1, nullptr, 0, nullptr, st)
   if (a.tb) {
-    if (a.c_f32) PT_L(true, EPI_RES, float);
+    if (a.c_f32 && a.epi == EPI_STORE) PT_L(true, EPI_STORE, float);
+    else if (a.c_f32) PT_L(true, EPI_RES, float);
     else if (a.epi == EPI_STORE) PT_L(true, EPI_STORE, bf16);
     else PT_L(true, EPI_MUL_DGELU, bf16);
     return;
@@ -860,11 +965,12 @@ static void dispatch_pp_fwd(const Gemm& a, hipStream_t st) {
 }
 
 // forward and input-gradient products (at least one k-major operand)
-template <int BM, int BN, int WGM, int WGN, int NS, int BK>
+template <int BM, int BN, int WGM, int WGN, int NS, int BK, bool TAIL = false>
 static void dispatch_fwd(const Gemm& a, hipStream_t st) {
-#define PT_L(TB_, EPI_, TC_) launch_dma<BM, BN, WGM, WGN, NS, BK, false, TB_, EPI_, TC_>(a, 1, nullptr, 0, nullptr, st)
+#define PT_L(TB_, EPI_, TC_) launch_dma<BM, BN, WGM, WGN, NS, BK, false, TB_, EPI_, TC_, TAIL>(a, 1, nullptr, 0, nullptr, st)
   if (a.tb) {
-    if (a.c_f32) PT_L(true, EPI_RES, float);
+    if (a.c_f32 && a.epi == EPI_STORE) PT_L(true, EPI_STORE, float);
+    else if (a.c_f32) PT_L(true, EPI_RES, float);
     else if (a.epi == EPI_STORE) PT_L(true, EPI_STORE, bf16);
     else PT_L(true, EPI_MUL_DGELU, bf16);
     return;
@@ -881,24 +987,24 @@ static void dispatch_fwd(const Gemm& a, hipStream_t st) {
 }
 
 // Few rows and a long contraction (the products of a top block that works on first-token rows, e.g.
-// 64 x 768 x 3072): the six workgroups of the output would each walk all of K one tile latency at a time
-// (45 us).  K is split over more workgroups into fp32 slabs in the caller's workspace, and a small kernel
+// 64 x 768 x 3072): the twelve 64x64 workgroups of the output would each walk all of K one tile latency at a time
+// (18 us).  K is split over more workgroups into fp32 slabs in the caller's workspace, and a small kernel
 // sums the slabs in order and applies the epilogue.
 bool gemm_dma_skinny(const Gemm& a, hipStream_t st) {
-  if (a.ta || a.M > 128 || !a.ws || !gemm_dma_ok(a)) return false;
-  const int nk = a.K / 32;
-  int splits = nk / 12;   // at least 12 k tiles per split
+  if (a.ta || a.M > 128 || a.K < 1536 || !a.ws || !gemm_dma_ok(a)) return false;
+  int splits = cdiv(a.K, 64) / 6;   // at least six k tiles per split
   if (splits > 16) splits = 16;
   const int64_t mn = (int64_t)a.M * a.N;
   while (splits > 1 && (size_t)(splits * mn) > a.ws_floats) --splits;
   if (splits < 2) return false;
   Gemm p = a;
   p.C = a.ws; p.ldc = a.N; p.c_f32 = true; p.epi = EPI_STORE; p.bias = nullptr; p.aux = nullptr; p.aux_out = nullptr;
-  if (a.tb) launch_dma<128, 128, 2, 2, 3, 32, false, true, EPI_STORE, float>(p, splits, a.ws, mn, nullptr, st);
-  else launch_dma<128, 128, 2, 2, 3, 32, false, false, EPI_STORE, float>(p, splits, a.ws, mn, nullptr, st);
+  if (a.tb) launch_dma<64, 64, 2, 2, 3, 64, false, true, EPI_STORE, float, true>(p, splits, a.ws, mn, nullptr, st);
+  else launch_dma<64, 64, 2, 2, 3, 64, false, false, EPI_STORE, float, true>(p, splits, a.ws, mn, nullptr, st);
 #define PT_SE(EPI_, TC_) launch_split_epilogue<EPI_, TC_>(a, a.ws, splits, st)
   if (a.tb) {
-    if (a.c_f32) PT_SE(EPI_RES, float);
+    if (a.c_f32 && a.epi == EPI_STORE) PT_SE(EPI_STORE, float);
+    else if (a.c_f32) PT_SE(EPI_RES, float);
     else if (a.epi == EPI_STORE) PT_SE(EPI_STORE, bf16);
     else PT_SE(EPI_MUL_DGELU, bf16);
   } else if (a.c_f32) {
@@ -914,21 +1020,64 @@ bool gemm_dma_skinny(const Gemm& a, hipStream_t st) {
 }
 
 void gemm_dma(const Gemm& a, int variant, hipStream_t st) {
-  // variants: 1 = 128x128 tiles, 2 = 256x128, 5 / 6 = the two-group kernel with 256 / 192-row tiles
-  if (a.ta) {   // a single weight gradient (a block's four go through gemm_wgrad_group)
+  // variants: 1 = 128x128 tiles, 2 = 256x128, 3 = 64x64, 4 = 128x128 with eight waves, 5 / 6 = the two-group kernel
+  // with 256 / 192-row tiles
+  if (a.ta) {   // a single weight gradient with a long contraction (a block's four go through gemm_wgrad_group)
     if (variant == 1) dispatch_wgrad<128, 128, 2, 2>(a, st);
     else dispatch_wgrad<256, 128, 4, 2>(a, st);
     return;
   }
-  if ((variant == 5 || variant == 6) && a.K % 64 == 0) {
-    if (variant == 5) dispatch_pp_fwd<256>(a, st);
-    else dispatch_pp_fwd<192>(a, st);
-    return;
+  switch (variant) {
+    case 6: dispatch_pp_fwd<192>(a, st); break;
+    case 5: dispatch_pp_fwd<256>(a, st); break;
+    // The four-wave and 256-row single-role tilings keep 32-wide k tiles and three stages: with 64-wide tiles they
+    // fit one workgroup less per CU and lose more than the whole-line loads gain.
+    case 2: dispatch_fwd<256, 128, 4, 2, 3, 32>(a, st); break;
+    case 1: dispatch_fwd<128, 128, 2, 2, 3, 32>(a, st); break;
+    case 4: dispatch_fwd<128, 128, 4, 2, 2, 64>(a, st); break;
+    default: dispatch_fwd<64, 64, 2, 2, 3, 64, true>(a, st); break;
   }
-  // The single-role tilings keep 32-wide k tiles and three stages: with 64-wide tiles they fit one workgroup
-  // less per CU and lose more than the whole-line loads gain.
-  if (variant == 2 && a.K % 64 == 0) dispatch_fwd<256, 128, 4, 2, 3, 32>(a, st);
-  else dispatch_fwd<128, 128, 2, 2, 3, 32>(a, st);
+}
+
+// Kernel choice for forward and input-gradient products.  Every variant runs the same matrix instructions in the
+// same k order, so a row's result does not depend on the choice (nor, through it, on the batch size).
+int gemm_dma_variant(const Gemm& a) {
+  if (a.K % 64 != 0) return a.K % 32 == 0 && (int64_t)cdiv(a.M, 128) * cdiv(a.N, 128) > 256 ? 1 : 3;
+  if (a.M >= 4096) {
+    // At least 4096 rows: the two-group kernel with 256x256 or 192x256 tiles, one workgroup per CU, whichever
+    // fills whole rounds of 256 CUs better (M = 12608, N = 768: 198 tiles of 192x256 against 150 of 256x256).
+    const int tn = cdiv(a.N, 256);
+    const int t192 = cdiv(a.M, 192) * tn, t256 = cdiv(a.M, 256) * tn;
+    if (a.N >= 3072 && (a.K < 1024 || a.tb)) {
+      // Wide and short: 192- or 256-row tiles only when their last round is (nearly) full, as for 12288 tokens
+      // (768 tiles of 192 rows at N = 3072; 9-10 % faster than 256x128 there) or 25216 (1188 tiles of 256 rows, 93 %
+      // of five rounds: 169 us against 183 with GELU, 149 against 164 with the saved GELU'); otherwise from 9000
+      // rows on 256x128 tiles, two workgroups per CU, whose prologues and epilogues overlap.
+      const int last = t192 % 256;
+      if (last == 0 || last >= 224) return 6;
+      if (t256 * 10 >= cdiv(t256, 256) * 256 * 9) return 5;
+      if (a.M >= 9000) return 2;
+    } else {
+      const int v = cdiv(t192, 256) * 192 < cdiv(t256, 256) * 256 ? 6 : 5;
+      // fewer tiles than 60 % of the CUs of their rounds (8192 tokens at N = 768: 129 tiles): smaller tiles fill the
+      // chip better (6-13 % faster on those five products)
+      const int tiles = v == 6 ? t192 : t256;
+      if (tiles * 10 >= cdiv(tiles, 256) * 256 * 6) return v;
+    }
+  }
+  // Below that, 128x128 or 64x64 tiles.  A workgroup alone on its CU is held to the latency and rate of its own
+  // loads (45-50 GB/s per CU), so what counts is the number of workgroups that the fullest CU gets.  Microseconds
+  // fitted to launches of 17 to 8192 rows with N and K of 768 to 3072, within 15 % (k = K / 1000): a 128x128
+  // workgroup alone 5.7 + 8.9 k, w of them w (5.3 + 7.0 k); a 64x64 workgroup alone 3.5 + 4.7 k, w of them
+  // w (1.9 + 3.05 k).  1379 x 768 x 3072: 66 tiles, 33 us, against 264 small ones, 21 us; 2639 x 3072 x 768: 504
+  // tiles, 24 us, against 2016 small ones, 30 us.
+  const int64_t t128 = (int64_t)cdiv(a.M, 128) * cdiv(a.N, 128), t64 = (int64_t)cdiv(a.M, 64) * cdiv(a.N, 64);
+  const double w128 = (double)((t128 + 255) / 256), w64 = (double)((t64 + 255) / 256), k = 1e-3 * a.K;
+  const double us128 = w128 > 1 ? w128 * (5.3 + 7.0 * k) : 5.7 + 8.9 * k;
+  const double us64 = w64 > 1 ? w64 * (1.9 + 3.05 * k) : 3.5 + 4.7 * k;
+  if (us64 <= us128) return 3;
+  // eight waves and whole-line loads where both operands are k-major and CUs hold two tiles: 5-10 % faster
+  return a.tb && t128 > 256 ? 4 : 1;
 }
 
 }  // namespace pt

@@ -1,0 +1,67 @@
+"""Shapes at which the matrix-core products change kernel: fewer rows than a tile, token counts that are no multiple of a
+k tile, 64- and 128-wide tiles, split and unsplit weight gradients, the eight-wave tiles of the input gradients.  bf16
+mode against the exact oracle (or the bf16 storage model) at 2e-2, value by value; and rows of the frozen prefix bit by
+bit between batches whose products run on different tiles."""
+import numpy as np
+import pytest
+
+from paper_2102_03161_amd import binding
+from tests import gpu_harness as H
+
+pytestmark = pytest.mark.gpu
+
+VIT = dict(arch="vit", img=56, patch=8, chans=3, S=50, vocab=0, max_pos=0, ln_eps=1e-6, optimizer="adamw", dtype="bf16")
+BERT = dict(arch="bert", img=0, patch=0, chans=0, n_out=2, vocab=500, ln_eps=1e-12, optimizer="adamw", dtype="bf16")
+
+CASES = {
+    # one sample: 50 tokens, products of a single row, a contraction over 1000 classes
+    "one_row": (dict(VIT, L=2, D=256, H=4, F=1024, n_out=1000, B=1), 0, 1, 41),
+    # 350 tokens at full width: 64-row tiles, 128-wide weight gradients over five and a half k tiles, seven-row products
+    # with a split contraction
+    "few_rows": (dict(VIT, L=2, D=768, H=12, F=3072, n_out=1000, B=7), 0, 7, 42),
+    # 1078 tokens, narrow matrices: 64-wide weight-gradient tiles with a split contraction
+    "narrow_split": (dict(BERT, L=2, D=256, H=4, F=1024, S=77, max_pos=80, B=14), 0, 14, 43),
+    # 2079 tokens: the two-group weight-gradient kernel with a partial last k tile
+    "group_tail": (dict(BERT, L=2, D=512, H=8, F=2048, S=77, max_pos=80, B=27), 0, 27, 44),
+    # 2639 x 3072 input gradients: 504 tiles of 128x128, eight waves each
+    "eight_waves": (dict(BERT, L=1, D=768, H=12, F=3072, S=203, max_pos=203, B=13), 0, 13, 45),
+}
+
+
+@pytest.fixture(scope="module")
+def torch_mod():
+    import torch
+    assert torch.cuda.is_available()
+    return torch
+
+
+@pytest.mark.parametrize("name", CASES)
+def test_products_at_tile_edges(torch_mod, name):
+    w, k, nb, seed = CASES[name]
+    print(f"tile edges: {name}", flush=True)
+    ctx = binding.Context(binding.make_config(w, B=nb))
+    vals = H.init_values(w, ctx, seed)
+    H.load_params(ctx, vals)
+    x, y = H.batch_for(w, seed, nb)
+    g = H.gpu_step(torch_mod, ctx, w, x, y, k)
+    ctx.close()
+    o = H.oracle_step(w, vals, x, y, k)
+    m = H.storage_model_step(w, vals, x, y, k)
+    H.compare_step(w, g, o, k, 2e-2, check_params=False, model=m, rss=H.summand_rss(w, vals, x, y, k))
+
+
+def test_prefix_rows_do_not_depend_on_the_tiles(torch_mod):
+    """3250 rows take 128x128 tiles in the wide products, 50 and 350 rows 64x64 ones."""
+    torch = torch_mod
+    w = dict(VIT, L=2, D=768, H=12, F=3072, n_out=10, B=65)
+    ctx = binding.Context(binding.make_config(w))
+    H.load_params(ctx, H.init_values(w, ctx, 5))
+    ctx.set_freeze_boundary(2)
+    x = H.to_dev(torch, H.batch_for(w, 5, 65)[0])
+    rows = {}
+    for nb in (65, 7, 1):
+        ctx.frozen_forward(x[:nb].contiguous())
+        rows[nb] = ctx.read_activation(binding.ACT_HK, (nb, w["S"], w["D"]))
+    ctx.close()
+    for nb in (7, 1):
+        assert np.array_equal(rows[nb], rows[65][:nb]), nb
