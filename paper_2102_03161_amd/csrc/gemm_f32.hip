@@ -1,0 +1,244 @@
+// Products on the fp32 matrix instructions (v_mfma_f32_16x16x4_f32): every product of fp32 mode, and in bf16 mode
+// the few whose operands the asynchronous bf16 kernels cannot take (class counts or MLP widths that are no multiple
+// of 8); those are widened to fp32 on their way into LDS.
+//
+// What bounds it: the fp32 matrix rate (64 FLOP per clock and SIMD, 157 TFLOP/s on the chip) is a sixteenth of the
+// bf16 one, so a 64x64 tile needs 38 GB/s of operands per CU where its load path carries 90 to 113; registers as
+// staging and one k tile of lead are enough, and what counts is how evenly the 16x16 units of work fall on the
+// 1024 SIMDs.  Four tile sizes serve that.  Operands lie in LDS as they lie in memory: an operand whose k runs
+// contiguously as [row][BK + 4], read 16 bytes (four k) at a time, one whose rows run contiguously as
+// [k][rows + 4], read one float at a time; both paddings are conflict-free for the sixteen-row fragments.
+//
+// MFMA number j of group q multiplies the k values 16 q + 4 g + j, g = 0..3: the same order for every layout and
+// tile size, so that a row's result depends on neither.
+#include <type_traits>
+
+#include "common.h"
+#include "kernels.h"
+#include "gemm_epilogue.h"
+
+namespace pt {
+
+namespace {
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+constexpr int kMaxPlain = 4;
+struct PlainProb {
+  const void* A; const void* B; void* C;
+  const void* bias; const void* aux; void* aux_out;
+  float* colsum;              // column sums of B over k (strided B only), or null
+  int64_t lda, ldb, ldc, ld_aux;
+  int M, N, K, tile0, tiles_n;
+};
+struct PlainArgs {
+  PlainProb p[kMaxPlain];
+  int nprob, total, epi;
+};
+
+constexpr int kPlainBK = 32;
+
+// one operand tile of ROWS rows and kPlainBK k values: N4 = ROWS / 32 pieces of four elements per thread
+template <typename T, bool STRIDED, bool VEC, int ROWS>
+struct PlainTile {
+  static constexpr int N4 = ROWS / 32;
+  static constexpr int LD = STRIDED ? ROWS + 4 : kPlainBK + 4;
+  static constexpr int FLOATS = STRIDED ? kPlainBK * LD : ROWS * LD;
+  static __device__ __forceinline__ void place(int tid, int i, int* row, int* k) {
+    const int c = tid + 256 * i;
+    if (STRIDED) { *k = c / (ROWS / 4); *row = (c % (ROWS / 4)) * 4; }
+    else { *row = c / (kPlainBK / 4); *k = (c % (kPlainBK / 4)) * 4; }
+  }
+  static __device__ __forceinline__ void load(const T* p, int64_t ld, int R, int K, int r0, int k0, int tid, f32x4 (&reg)[N4]) {
+#pragma unroll
+    for (int i = 0; i < N4; ++i) {
+      int row, k;
+      place(tid, i, &row, &k);
+      row += r0; k += k0;
+      f32x4 v = {0.f, 0.f, 0.f, 0.f};
+      if (VEC) {
+        if (row < R && k < K) v = *reinterpret_cast<const f32x4*>(reinterpret_cast<const float*>(p) + (STRIDED ? (int64_t)k * ld + row : (int64_t)row * ld + k));
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int re = STRIDED ? row + e : row, ke = STRIDED ? k : k + e;
+          if (re < R && ke < K) v[e] = to_f32(p[STRIDED ? (int64_t)ke * ld + re : (int64_t)re * ld + ke]);
+        }
+      }
+      reg[i] = v;
+    }
+  }
+  static __device__ __forceinline__ void store(float* s, int tid, const f32x4 (&reg)[N4]) {
+#pragma unroll
+    for (int i = 0; i < N4; ++i) {
+      int row, k;
+      place(tid, i, &row, &k);
+      *reinterpret_cast<f32x4*>(s + (STRIDED ? k * LD + row : row * LD + k)) = reg[i];
+    }
+  }
+  // the four k values 16 q + 4 g + j (j = 0..3) of row r
+  static __device__ __forceinline__ f32x4 frag(const float* s, int r, int q, int g) {
+    if (!STRIDED) return *reinterpret_cast<const f32x4*>(s + r * LD + 16 * q + 4 * g);
+    f32x4 v;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) v[j] = s[(16 * q + 4 * g + j) * LD + r];
+    return v;
+  }
+};
+
+// Tiles of 32 TM x 32 TN, four waves in two rows of two, each TM x TN units of 16x16.  Up to four problems in one
+// launch; workgroups go to the XCDs round-robin, and each XCD takes a contiguous run of tiles.
+template <typename T, typename TC, bool TA, bool TB, bool VEC, int TM, int TN>
+__global__ __launch_bounds__(256) void gemm_f32_kernel(PlainArgs ga) {
+  constexpr int BM = 32 * TM, BN = 32 * TN;
+  typedef PlainTile<T, TA, VEC, BM> LA;
+  typedef PlainTile<T, !TB, VEC, BN> LB;
+  __shared__ __attribute__((aligned(16))) float lds[2 * (LA::FLOATS + LB::FLOATS)];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wm = wave >> 1, wn = wave & 1;
+  const int per = (ga.total + 7) >> 3;
+  const int work = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
+  if (work >= ga.total) return;
+  int pi = 0;
+  while (pi + 1 < ga.nprob && work >= ga.p[pi + 1].tile0) ++pi;
+  const PlainProb& p = ga.p[pi];
+  const int local = work - p.tile0;
+  const int m0 = (local / p.tiles_n) * BM, n0 = (local % p.tiles_n) * BN;
+  const T* A = reinterpret_cast<const T*>(p.A);
+  const T* B = reinterpret_cast<const T*>(p.B);
+
+  f32x4 acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  f32x4 ra[LA::N4], rb[LB::N4];
+  const bool do_colsum = !TB && p.colsum != nullptr && m0 == 0;
+  float cs = 0.f;
+  const int nk = (p.K + kPlainBK - 1) / kPlainBK;
+  LA::load(A, p.lda, p.M, p.K, m0, 0, tid, ra);
+  LB::load(B, p.ldb, p.N, p.K, n0, 0, tid, rb);
+  for (int t = 0; t < nk; ++t) {
+    float* as = lds + (t & 1) * (LA::FLOATS + LB::FLOATS);
+    float* bs = as + LA::FLOATS;
+    LA::store(as, tid, ra);
+    LB::store(bs, tid, rb);
+    __syncthreads();   // tile t is in LDS; the other buffer is free, its readers passed this barrier
+    if (t + 1 < nk) {
+      LA::load(A, p.lda, p.M, p.K, m0, (t + 1) * kPlainBK, tid, ra);
+      LB::load(B, p.ldb, p.N, p.K, n0, (t + 1) * kPlainBK, tid, rb);
+    }
+    const int g = lane >> 4, l = lane & 15;
+#pragma unroll
+    for (int q = 0; q < kPlainBK / 16; ++q) {
+      f32x4 a[TM], b[TN];
+#pragma unroll
+      for (int i = 0; i < TM; ++i) a[i] = LA::frag(as, wm * 16 * TM + i * 16 + l, q, g);
+#pragma unroll
+      for (int j = 0; j < TN; ++j) b[j] = LB::frag(bs, wn * 16 * TN + j * 16 + l, q, g);
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+          for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][e], b[j][e], acc[i][j], 0, 0, 0);
+    }
+    if constexpr (!TB) {
+      if (do_colsum && tid < BN) {
+#pragma unroll
+        for (int k = 0; k < kPlainBK; ++k) cs += bs[k * LB::LD + tid];
+      }
+    }
+  }
+  if constexpr (!TB) {
+    if (do_colsum && tid < BN && n0 + tid < p.N) p.colsum[n0 + tid] = cs;
+  }
+  // accumulator layout of the 16x16 MFMA: lane holds column lane % 16, rows 4 (lane / 16) + v
+  const GemmDev<T> g{A, B, p.C, p.M, p.N, p.K, p.lda, p.ldb, p.ldc, reinterpret_cast<const T*>(p.bias),
+                     reinterpret_cast<const T*>(p.aux), reinterpret_cast<T*>(p.aux_out), p.ld_aux};
+  auto finish = [&](auto epi) {
+    constexpr int EPI = decltype(epi)::value;
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int row = m0 + (wm * TM + i) * 16 + 4 * (lane >> 4) + v, col = n0 + (wn * TN + j) * 16 + (lane & 15);
+          if (row < p.M && col < p.N) epilogue_store<T, TC, EPI>(g, row, col, acc[i][j][v]);
+        }
+  };
+  switch (ga.epi) {
+    case EPI_STORE: finish(std::integral_constant<int, EPI_STORE>()); break;
+    case EPI_BIAS: finish(std::integral_constant<int, EPI_BIAS>()); break;
+    case EPI_BIAS_RES: finish(std::integral_constant<int, EPI_BIAS_RES>()); break;
+    case EPI_BIAS_GELU: finish(std::integral_constant<int, EPI_BIAS_GELU>()); break;
+    case EPI_MUL_DGELU: finish(std::integral_constant<int, EPI_MUL_DGELU>()); break;
+    default: finish(std::integral_constant<int, EPI_RES>()); break;
+  }
+}
+
+bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
+// float4 loads: four elements along the contiguous index, from 16-byte aligned rows
+bool vec_ok(const Gemm& a) {
+  return aligned16(a.A) && aligned16(a.B) && a.lda % 4 == 0 && a.ldb % 4 == 0 && (a.ta ? a.M : a.K) % 4 == 0 && (a.tb ? a.K : a.N) % 4 == 0;
+}
+
+template <typename T, typename TC, bool VEC, int TM, int TN>
+void launch(const Gemm* a, int n, hipStream_t st) {
+  PlainArgs ga{};
+  int t0 = 0;
+  for (int i = 0; i < n; ++i) {
+    const Gemm& m = a[i];
+    const int tiles_n = cdiv(m.N, 32 * TN);
+    ga.p[i] = PlainProb{m.A, m.B, m.C, m.bias, m.aux, m.aux_out, m.colsum_out, m.lda, m.ldb, m.ldc, m.ld_aux,
+                        m.M, m.N, m.K, t0, tiles_n};
+    t0 += cdiv(m.M, 32 * TM) * tiles_n;
+  }
+  ga.nprob = n;
+  ga.total = t0;
+  ga.epi = a[0].epi;
+  const dim3 grid(8 * cdiv(t0, 8));
+  if (a[0].ta) hipLaunchKernelGGL((gemm_f32_kernel<T, TC, true, false, VEC, TM, TN>), grid, dim3(256), 0, st, ga);
+  else if (a[0].tb) hipLaunchKernelGGL((gemm_f32_kernel<T, TC, false, true, VEC, TM, TN>), grid, dim3(256), 0, st, ga);
+  else hipLaunchKernelGGL((gemm_f32_kernel<T, TC, false, false, VEC, TM, TN>), grid, dim3(256), 0, st, ga);
+}
+
+// Tile size: the fullest CU's share of 16x16 units, weighted by what a tile size reaches of the matrix rate when it
+// has the CU's four SIMDs to itself.
+template <typename T, typename TC, bool VEC>
+void choose(const Gemm* a, int n, hipStream_t st) {
+  auto cost = [&](int tm, int tn, double weight) {
+    int64_t t = 0;
+    for (int i = 0; i < n; ++i) t += (int64_t)cdiv(a[i].M, 32 * tm) * cdiv(a[i].N, 32 * tn);
+    return (double)((t + 255) / 256) * tm * tn * weight;
+  };
+  const double c11 = cost(1, 1, 1.7), c12 = cost(1, 2, 1.3), c22 = cost(2, 2, 1.1), c44 = cost(4, 4, 1.0);
+  if (c44 <= c22 && c44 <= c12 && c44 <= c11) launch<T, TC, VEC, 4, 4>(a, n, st);
+  else if (c22 <= c12 && c22 <= c11) launch<T, TC, VEC, 2, 2>(a, n, st);
+  else if (c12 <= c11) launch<T, TC, VEC, 1, 2>(a, n, st);
+  else launch<T, TC, VEC, 1, 1>(a, n, st);
+}
+
+}  // namespace
+
+void gemm_f32(int dt, const Gemm* a, int n, hipStream_t st) {
+  if (dt != 0) {
+    for (int i = 0; i < n; ++i) {
+      if (a[i].c_f32) launch<bf16, float, false, 1, 1>(a + i, 1, st);
+      else launch<bf16, bf16, false, 1, 1>(a + i, 1, st);
+    }
+    return;
+  }
+  for (int i = 0; i < n;) {
+    int m = 1;   // products of one layout and epilogue over the same contraction share a launch
+    while (m < kMaxPlain && i + m < n && a[i + m].ta == a[i].ta && a[i + m].tb == a[i].tb && a[i + m].epi == a[i].epi) ++m;
+    bool vec = true;
+    for (int j = 0; j < m; ++j) vec = vec && vec_ok(a[i + j]);
+    if (vec) choose<float, float, true>(a + i, m, st);
+    else choose<float, float, false>(a + i, m, st);
+    i += m;
+  }
+}
+
+}  // namespace pt

@@ -115,10 +115,6 @@ void layernorm_bwd(int dt, bool dy_f32, bool x_f32, const void* dy, int64_t lddy
                    int rows, int D, hipStream_t st, LnReduceJob* deferred = nullptr);
 void layernorm_bwd_reduce(const LnReduceJob* jobs, int n, int D, hipStream_t st);
 
-// out[n] = sum_m X[m,n] (fp32), X is T [M,N] with leading dimension ld.
-size_t colsum_partial_floats(int N);
-void colsum(int dt, const void* X, int64_t ld, int M, int N, float* out, float* partial, hipStream_t st);
-
 // ---- ViT front end
 // sample b of the output reads image map[b] (map null = identity)
 void vit_patchify(int dt, const float* images, const int64_t* map, void* patches, int nb, int chans, int img, int patch,

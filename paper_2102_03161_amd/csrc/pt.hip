@@ -208,10 +208,9 @@ void make_plan(const pt_config& c, Plan* p) {
   p->ln_slots = 2 * (L - std::min(c.k_min, L)) + 2;
   p->LNPART = take(ln_partial_floats(D) * 4 * p->ln_slots);
   // scratch of the weight-gradient products: split-K slabs (up to 16 splits, about 768 workgroups in
-  // flight) plus their column-sum partials; also serves the separate column-sum pass of the FMA path
+  // flight) plus their column-sum partials
   {
-    const int maxn = std::max(std::max(3 * D, F), c.n_out);
-    size_t need = colsum_partial_floats(maxn);
+    size_t need = 0;
     const int64_t shapes[6][2] = {{D, 3 * D}, {D, D}, {D, F}, {F, D}, {c.chans * c.patch * c.patch, D}, {D, c.n_out}};
     for (auto& sh : shapes) {
       const int64_t tiles = ((sh[0] + 127) / 128) * ((sh[1] + 127) / 128);

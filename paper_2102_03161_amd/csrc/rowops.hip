@@ -303,31 +303,6 @@ void layernorm_bwd(int dt, bool dy_f32, bool x_f32, const void* dy, int64_t lddy
 }
 
 // ---------------------------------------------------------------------------
-// column sums (bias gradients)
-// ---------------------------------------------------------------------------
-constexpr int kColsumRowBlocks = 128;
-size_t colsum_partial_floats(int N) { return (size_t)kColsumRowBlocks * N; }
-
-template <typename T>
-__global__ __launch_bounds__(256) void colsum_kernel(const T* __restrict__ X, int64_t ld, int M, int N,
-                                                     float* __restrict__ partial) {
-  const int col = blockIdx.x * 256 + threadIdx.x;
-  if (col >= N) return;
-  float s = 0.f;
-  for (int r = blockIdx.y; r < M; r += gridDim.y) s += to_f32(X[(int64_t)r * ld + col]);
-  partial[(size_t)blockIdx.y * N + col] = s;
-}
-
-void colsum(int dt, const void* X, int64_t ld, int M, int N, float* out, float* partial, hipStream_t st) {
-  const int nby = M < kColsumRowBlocks ? M : kColsumRowBlocks;
-  dim3 grid(cdiv(N, 256), nby);
-  if (dt == 0) hipLaunchKernelGGL(colsum_kernel<float>, grid, dim3(256), 0, st, (const float*)X, ld, M, N, partial);
-  else hipLaunchKernelGGL(colsum_kernel<bf16>, grid, dim3(256), 0, st, (const bf16*)X, ld, M, N, partial);
-  hipLaunchKernelGGL(reduce_partials_kernel, dim3(cdiv(N, 32)), dim3(1024), 0, st, partial, nby, N, out, N,
-                     (float*)nullptr, (float*)nullptr);
-}
-
-// ---------------------------------------------------------------------------
 // ViT front end plumbing
 // ---------------------------------------------------------------------------
 template <typename T>

@@ -50,10 +50,28 @@ def test_products_at_tile_edges(torch_mod, name):
     H.compare_step(w, g, o, k, 2e-2, check_params=False, model=m, rss=H.summand_rss(w, vals, x, y, k))
 
 
-def test_prefix_rows_do_not_depend_on_the_tiles(torch_mod):
-    """3250 rows take 128x128 tiles in the wide products, 50 and 350 rows 64x64 ones."""
+@pytest.mark.parametrize("nb,F", [(1, 3072), (9, 3072), (40, 3072), (3, 1028)])
+def test_fp32_products_at_tile_edges(torch_mod, nb, F):
+    """fp32 mode: 50, 450 and 2000 rows take all four tile sizes; ten classes and the widths that are no multiple of
+    the tiles take the element-wise loads and the ragged edges."""
+    w = dict(VIT, L=2, D=768, H=12, F=F, n_out=10, B=nb, dtype="f32")
+    print(f"fp32 tile edges: nb={nb} F={F}", flush=True)
+    ctx = binding.Context(binding.make_config(w))
+    vals = H.init_values(w, ctx, 6)
+    H.load_params(ctx, vals)
+    x, y = H.batch_for(w, 6, nb)
+    g = H.gpu_step(torch_mod, ctx, w, x, y, 0)
+    ctx.close()
+    o = H.oracle_step(w, vals, x, y, 0)
+    H.oracle_update(w, o, vals, g["grads"], 0)
+    H.compare_step(w, g, o, 0, 1e-4, rss=H.summand_rss(w, vals, x, y, 0))
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_prefix_rows_do_not_depend_on_the_tiles(torch_mod, dtype):
+    """3250 rows take 128x128 tiles in the wide products, 50 and 350 rows smaller ones."""
     torch = torch_mod
-    w = dict(VIT, L=2, D=768, H=12, F=3072, n_out=10, B=65)
+    w = dict(VIT, L=2, D=768, H=12, F=3072, n_out=10, B=65, dtype=dtype)
     ctx = binding.Context(binding.make_config(w))
     H.load_params(ctx, H.init_values(w, ctx, 5))
     ctx.set_freeze_boundary(2)
