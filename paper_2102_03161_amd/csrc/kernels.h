@@ -76,9 +76,9 @@ void attention_fwd(int dt, const void* qkv, void* ctx, float* lse /*[nb,H,S] or 
                    int dh, hipStream_t st);
 void attention_bwd(int dt, const void* qkv, const void* ctx, const void* dctx, const float* lse, void* dqkv,
                    float* delta_ws /*[nb,H,S]*/, int nb, int S, int H, int dh, hipStream_t st);
-// Dynamic LDS bytes the kernels without matrix cores (fp32 mode, or a head size other than 64) and the
-// first-query kernels ask for at sequence length S; the orchestrator rejects configurations above the 160 KB
-// of a CU before anything is launched.
+// Bytes that bound the sequence length: for the fp32 kernels (fp32 mode, or a head size other than 64) see the
+// definition, for the first-query kernels the dynamic LDS that they ask for.  The orchestrator rejects
+// configurations above the 160 KB of a CU before anything is launched.
 size_t attention_generic_lds_bytes(int S, int dh);
 size_t attention_first_query_lds_bytes(int S, int dh);
 bool attention_uses_mfma(int dt, int dh);
