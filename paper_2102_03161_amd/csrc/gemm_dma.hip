@@ -21,6 +21,7 @@
 // one: they only feed outputs that are never stored.  With TAIL the lanes whose k
 // lies past the end fetch a line of zeros instead.
 #include <algorithm>
+#include <type_traits>
 #include "common.h"
 #include "kernels.h"
 #include "gemm_epilogue.h"
@@ -184,16 +185,6 @@ struct TileS {
       f[j] = t.v;
     }
   }
-  // sum over the tile's k rows of column n (for the fused bias gradient)
-  static __device__ __forceinline__ float colsum(const unsigned char* lds, int n) {
-    float s = 0.f;
-#pragma unroll
-    for (int k = 0; k < BK; ++k) {
-      const int c = (n >> 3) ^ swz<ROWS>(k);
-      s += to_f32(*reinterpret_cast<const bf16*>(lds + k * ROWB + c * 16 + (n & 7) * 2));
-    }
-    return s;
-  }
 };
 
 template <bool STRIDED, int ROWS, int NW, int NFRAG, int BK> struct TileSel { typedef TileK<ROWS, NW, NFRAG, BK> type; };
@@ -215,6 +206,42 @@ template <int N>
 __device__ __forceinline__ void wait_vm() {
   __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
 }
+
+// Column sums of B over k (the bias gradient of a weight-gradient product), taken from the fragments that the matrix
+// instructions consume: a lane holds eight k values of column lane % 32 as four registers of two, and adds one quarter
+// of them behind each row of MFMAs, in the issue slots that the matrix cores leave free.  Summing the tile's columns from LDS
+// instead (64 two-byte reads by 256 threads per k tile) held the workgroups that do it, and with them the launch, 15 %
+// longer: width 768, 12608 tokens 252 -> 219 us, width 1024, 32768 tokens 969 -> 838 us.
+template <int TN>
+struct ColSum {
+  float lo[TN], hi[TN];   // even and odd k
+  __device__ __forceinline__ ColSum() {
+#pragma unroll
+    for (int j = 0; j < TN; ++j) lo[j] = hi[j] = 0.f;
+  }
+  // registers from .. to - 1 of the four
+  __device__ __forceinline__ void add(const bf16x8 (&f)[TN], int from, int to) {
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+      union { bf16x8 v; unsigned u[4]; } t;
+      t.v = f[j];
+#pragma unroll
+      for (int r = from; r < to; ++r) {
+        lo[j] += __uint_as_float(t.u[r] << 16);
+        hi[j] += __uint_as_float(t.u[r] & 0xffff0000u);
+      }
+    }
+  }
+  // `out`: the sums of this wave's first column; n: columns that exist from there on
+  __device__ __forceinline__ void store(float* out, int n, int lane) const {
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+      float s = lo[j] + hi[j];
+      s += __shfl_xor(s, 32, 64);   // the other eight k values of each k-step
+      if (lane < 32 && j * 32 + lane < n) out[j * 32 + lane] = s;
+    }
+  }
+};
 
 // The LDS footprint allows two workgroups per CU with 256x128 tiles (eight waves each) and three with
 // 128x128 tiles (four waves each).  The second launch bound is the number of waves per SIMD that this
@@ -253,8 +280,8 @@ __device__ __forceinline__ void dma_run(const GemmDev<bf16>& g, const SplitArgs&
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
 
-  const bool do_colsum = !TB && sp.colsum != nullptr && m0 == 0;
-  float cs = 0.f;
+  const bool do_colsum = __builtin_amdgcn_readfirstlane(TA && !TB && sp.colsum != nullptr && m0 == 0 && wm == 0 ? 1 : 0) != 0;
+  ColSum<TN> cs;
 
   LA ta;
   LB tb;
@@ -302,10 +329,14 @@ __device__ __forceinline__ void dma_run(const GemmDev<bf16>& g, const SplitArgs&
       if (ks + 1 < KS) wait_lds<RPS>(fa[ks & 1], fb[ks & 1]);
       else wait_lds<0>(fa[ks & 1], fb[ks & 1]);
 #pragma unroll
-      for (int i = 0; i < TM; ++i)
+      for (int i = 0; i < TM; ++i) {
 #pragma unroll
         for (int j = 0; j < TN; ++j)
           acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[ks & 1][i], fb[ks & 1][j], acc[i][j], 0, 0, 0);
+        if constexpr (TA && !TB) {
+          if (do_colsum) cs.add(fb[ks & 1], 4 * i / TM, 4 * (i + 1) / TM);
+        }
+      }
       // nothing may be scheduled across this point: without it the compiler sinks the MFMAs above below the
       // next wait, and every fragment read of the tile is then waited for before the first MFMA issues
       __builtin_amdgcn_sched_barrier(0);
@@ -314,15 +345,12 @@ __device__ __forceinline__ void dma_run(const GemmDev<bf16>& g, const SplitArgs&
         tb.read(sb, ks + 2, fb[ks & 1]);
       }
     }
-    if constexpr (!TB) {
-      if (do_colsum && tid < BN) cs += LB::colsum(sb, tid);
-    }
   }
   compiler_fence();
   __builtin_amdgcn_s_barrier();   // all fragment reads done: the LDS can be reused for the epilogue
   compiler_fence();
-  if constexpr (!TB) {
-    if (do_colsum && tid < BN && n0 + tid < g.N) sp.colsum[(int64_t)split * g.N + n0 + tid] = cs;
+  if constexpr (TA && !TB) {
+    if (do_colsum) cs.store(sp.colsum + (int64_t)split * g.N + n0 + wn * WTN, g.N - n0 - wn * WTN, lane);
   }
   void* Cbase = sizeof(TC) == 4 ? (void*)(reinterpret_cast<float*>(g.C) + split * sp.slab)
                                 : (void*)(reinterpret_cast<bf16*>(g.C) + split * sp.slab);
@@ -413,8 +441,8 @@ __device__ __forceinline__ void pp_run(const GemmDev<bf16>& g, const SplitArgs& 
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
 
-  const bool do_colsum = !TB && sp.colsum != nullptr && m0 == 0;
-  float cs = 0.f;
+  const bool do_colsum = __builtin_amdgcn_readfirstlane(TA && !TB && sp.colsum != nullptr && m0 == 0 ? 1 : 0) != 0;
+  ColSum<TN> cs;   // group 0: its waves hold every column's fragments
 
   LA ta;
   LB tb;
@@ -437,7 +465,7 @@ __device__ __forceinline__ void pp_run(const GemmDev<bf16>& g, const SplitArgs& 
     for (int ks = 0; ks < KSF; ++ks) wait_lds<0>(fa[ks], fb[ks]);
   };
   // the MFMAs on the fragments held; `load(q)` for q in [0, nq) goes out between them
-  auto compute = [&](bool on, int nq, auto load) {
+  auto compute = [&](auto colsum, bool on, int nq, auto load) {
 #pragma unroll
     for (int ks = 0; ks < KSF; ++ks)
 #pragma unroll
@@ -445,6 +473,10 @@ __device__ __forceinline__ void pp_run(const GemmDev<bf16>& g, const SplitArgs& 
 #pragma unroll
         for (int j = 0; j < TN; ++j)
           acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[ks][i], fb[ks][j], acc[i][j], 0, 0, 0);
+        if constexpr (decltype(colsum)::value) {
+          cs.add(fb[ks], 4 * i / TM, 4 * (i + 1) / TM);
+          __builtin_amdgcn_sched_barrier(0);   // or the additions gather behind the last MFMA
+        }
         const int slot = ks * TM + i;
         if (slot < nq) {
           if (on) load(slot);
@@ -489,7 +521,7 @@ __device__ __forceinline__ void pp_run(const GemmDev<bf16>& g, const SplitArgs& 
 
   // The two groups run separate loops (straight-line code each, which the register allocator handles far
   // better than one loop with a branch per phase); both execute 2 * NH barriers per tile.
-  if (grp == 0) {
+  auto group0 = [&](auto colsum) {
     int ia = 0, ib = 0;   // stages of tile t
     for (int t = 0; t < n; ++t) {
       const bool moreB = t + 1 < n, moreA = t + 2 < n;
@@ -510,16 +542,19 @@ __device__ __forceinline__ void pp_run(const GemmDev<bf16>& g, const SplitArgs& 
         fetched();
         phase_end();
         // compute phase
-        compute(moreA, part_lo(2 * h + 1) - part_lo(2 * h), [&](int q) { ta.template issue_one<TAIL>(dstA, wave, part_lo(2 * h) + q, klim(t + 2)); });
-        if constexpr (!TB) {
-          if (h == 0 && do_colsum) cs += LB::colsum(sb, tid);   // threads 0..255 are this group
-        }
+        compute(colsum, moreA, part_lo(2 * h + 1) - part_lo(2 * h), [&](int q) { ta.template issue_one<TAIL>(dstA, wave, part_lo(2 * h) + q, klim(t + 2)); });
         if (h == NH - 1) tile_done(moreA);
         else phase_end();
       }
       ia = ia + 1 == NSA ? 0 : ia + 1;
       ib ^= 1;
     }
+  };
+  const std::integral_constant<bool, TA && !TB> with_colsum;
+  const std::false_type no_colsum;
+  if (grp == 0) {
+    if (do_colsum) group0(with_colsum);
+    else group0(no_colsum);
   } else {
     int ia = 0, ib = 0;
     // first phase of tile 0: nothing to compute yet
@@ -544,24 +579,24 @@ __device__ __forceinline__ void pp_run(const GemmDev<bf16>& g, const SplitArgs& 
         // compute phase: the next part of A(t+2), or, in the first phase of tile t + 1, B(t+2) into the stage
         // tile t's B has just left
         if (h < NH - 1) {
-          compute(moreA, part_lo(2 * h + 2) - part_lo(2 * h + 1), [&](int q) { ta.template issue_one<TAIL>(dstA, wave, part_lo(2 * h + 1) + q, klim(t + 2)); });
+          compute(no_colsum, moreA, part_lo(2 * h + 2) - part_lo(2 * h + 1), [&](int q) { ta.template issue_one<TAIL>(dstA, wave, part_lo(2 * h + 1) + q, klim(t + 2)); });
           phase_end();
         } else if (t + 1 < n) {
           unsigned char* const dstB = ldsB + ib * LB::BYTES;
-          compute(moreA, LB::LOADS, [&](int q) { tb.template issue_one<TAIL>(dstB, wave, q, klim(t + 2)); });
+          compute(no_colsum, moreA, LB::LOADS, [&](int q) { tb.template issue_one<TAIL>(dstB, wave, q, klim(t + 2)); });
           phase_end();
         }
       }
       ia = ia + 1 == NSA ? 0 : ia + 1;
       ib ^= 1;
     }
-    if (n > 0) compute(false, 0, [](int) {});
+    if (n > 0) compute(no_colsum, false, 0, [](int) {});
   }
   compiler_fence();
   __builtin_amdgcn_s_barrier();   // all fragment reads done: the LDS can be reused for the epilogue
   compiler_fence();
-  if constexpr (!TB) {
-    if (do_colsum && tid < BN && n0 + tid < g.N) sp.colsum[(int64_t)split * g.N + n0 + tid] = cs;
+  if constexpr (TA && !TB) {
+    if (do_colsum && grp == 0) cs.store(sp.colsum + (int64_t)split * g.N + n0 + wn * WTN, g.N - n0 - wn * WTN, lane);
   }
   void* Cbase = sizeof(TC) == 4 ? (void*)(reinterpret_cast<float*>(g.C) + split * sp.slab)
                                 : (void*)(reinterpret_cast<bf16*>(g.C) + split * sp.slab);
