@@ -310,8 +310,12 @@ __device__ __forceinline__ void dma_run(const GemmDev<bf16>& g, const SplitArgs&
     compiler_fence();
     __builtin_amdgcn_s_barrier();   // everybody's loads of tile `it` have landed, and tile it-1 is fully consumed
     compiler_fence();
-    if (it + kNS - 1 < n) issue(it + kNS - 1, fill);
-    fill = fill + 1 == kNS ? 0 : fill + 1;
+    // The next loads go out in front of the fragment reads, but behind them in the TAIL kernels (64x64 tiles, small weight
+    // gradients): there the choice between source and zeros makes the issue as long as the reads' latency, which is
+    // a good part of a tile's chain (1379 x 768 x 2304 15.9 -> 14.5 us, 231 x 256 x 1024 8.3 -> 7.9 us, weight gradients of
+    // width 768 over 2639 tokens 60.9 -> 58.3 us; without TAIL, 2639 x 3072 x 768 on eight waves 20.9 -> 21.2 us).
+    const bool more = it + kNS - 1 < n;
+    if (!TAIL && more) issue(it + kNS - 1, fill);
     const unsigned char* sa = lds + cur * STAGE;
     const unsigned char* sb = sa + LA::BYTES;
     cur = cur + 1 == kNS ? 0 : cur + 1;
@@ -324,6 +328,8 @@ __device__ __forceinline__ void dma_run(const GemmDev<bf16>& g, const SplitArgs&
     tb.read(sb, 0, fb[0]);
     ta.read(sa, 1, fa[1]);
     tb.read(sb, 1, fb[1]);
+    if (TAIL && more) issue(it + kNS - 1, fill);
+    fill = fill + 1 == kNS ? 0 : fill + 1;
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
       if (ks + 1 < KS) wait_lds<RPS>(fa[ks & 1], fb[ks & 1]);
