@@ -860,14 +860,16 @@ static WgradTiling wgrad_tiling(const Gemm* a, int n) {
 #ifdef PT_TUNING_HOOKS
   if (g_wgrad_force.bm) return g_wgrad_force;
 #endif
-  // Microseconds of a launch, fitted to launches over a block's four matrices of widths 256 and 768 with 7 to 12608
+  // Microseconds of a launch, fitted to launches over a block's four matrices of widths 256 and 768 with 231 to 12608
   // tokens (within 15 %; k = tokens / 1000, s splits, w workgroups on the fullest CU):
-  //   64x64 tiles    the larger of 3.6 + 13.7 k / s (one workgroup's own chain) and w (1.2 + 4.8 k / s)
-  //   128x128 tiles  the larger of 4.7 + 21.5 k / s and w (4 + 12.2 k / s)
-  //   256x256 tiles  w (6 + 33.8 k / s)
-  // and for s > 1 the slabs' summation at 4 TB/s, of which the two-group launch hides about half (WgradCarry).
-  // Width 768: 1379 tokens 39 us on 128x128 tiles against 50 on 256x256 ones with two splits, 4096 tokens 102
-  // against 94, 12608 tokens 302 against 235; width 256: 231 tokens 6.8 us on 64x64 tiles against 15.3.
+  //   64x64 tiles    the larger of 3.6 + 7.1 k / s (one workgroup's own chain) and w (1.2 + 3.75 k / s)
+  //   128x128 tiles  the larger of 4.7 + 12.5 k / s and w (4 + 9.8 k / s)
+  //   256x256 tiles  w (10 + 26 k / s)
+  // and for s > 1 the slabs' summation at 4 TB/s, also where it rides on another launch (WgradCarry).
+  // Width 768: 1379 tokens 34 us on 128x128 tiles against 43 on 64x64 ones, 2639 tokens 58 against 67 on 256x256 ones
+  // with two splits (a step of 2 x 2639 tokens, four blocks frozen, 5920 us against 6300), 8192 tokens 131 us on 256x256
+  // ones against 164 by the line above on 128x128; width 256: 231 tokens 5.2 us on 64x64 tiles, 2310 tokens 20 against
+  // 34 on 128x128 ones.
   const double k = 1e-3 * a[0].K;
   double floats = 0;
   for (int i = 0; i < n; ++i) floats += (double)a[i].M * a[i].N;
@@ -882,15 +884,15 @@ static WgradTiling wgrad_tiling(const Gemm* a, int n) {
     if (us < best_us) { best_us = us; best = WgradTiling{b, b, 64, s}; }
   };
   for (int s = 1; s <= 4 && (s == 1 || a[0].K >= 512 * s); s *= 2) {
-    consider(64, s, 3.6, 13.7, 1.2, 4.8, 1.0);
-    consider(128, s, 4.7, 21.5, 4.0, 12.2, 1.0);
+    consider(64, s, 3.6, 7.1, 1.2, 3.75, 1.0);
+    consider(128, s, 4.7, 12.5, 4.0, 9.8, 1.0);
   }
   int64_t t256 = 0;
   for (int i = 0; i < n; ++i) t256 += (int64_t)cdiv(a[i].M, 256) * cdiv(a[i].N, 256);
   int s = (int)(256 / t256);
   if (s > a[0].K / 256) s = a[0].K / 256;
   if (s > 16) s = 16;
-  consider(256, s < 1 ? 1 : s, 6.0, 33.8, 6.0, 33.8, 0.5);
+  consider(256, s < 1 ? 1 : s, 10.0, 26.0, 10.0, 26.0, 1.0);
   return best;
 }
 
