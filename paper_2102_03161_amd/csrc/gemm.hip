@@ -2,7 +2,8 @@
 // split-K slabs.
 //
 //  * gemm_dma.hip: bf16 operands on the bf16 matrix cores, global->LDS pipelines.
-//  * gemm_f32.hip: fp32 mode, and bf16 operands whose rows are not 16-byte aligned, on the fp32 matrix cores.
+//  * gemm_reg.hip: bf16 operands on the bf16 matrix cores, rows that are even but no multiple of 8 elements long.
+//  * gemm_f32.hip: fp32 mode, and what is left of bf16 operands, on the fp32 matrix cores.
 //
 // Forward and input-gradient products run their K loop in a fixed order without split-K (but for the few-row
 // products of an active top block), so every output element is a deterministic function of its own row and column.
@@ -10,6 +11,7 @@
 #include "common.h"
 #include "kernels.h"
 #include "gemm_epilogue.h"
+#include "gemm_rules.h"
 
 namespace pt {
 
@@ -78,26 +80,16 @@ void gemm_splitk_reduce_group(int nprob, int splits, const float* const* part, c
 // ---------------------------------------------------------------------------
 // dispatch
 // ---------------------------------------------------------------------------
-static bool aligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) % a) == 0; }
-
-// whether (layout, epilogue, output type) is one of the combinations the training step uses
-static bool combo_used(const Gemm& a) {
-  if (a.ta && a.tb) return false;
-  if (a.ta) return a.c_f32 && a.epi == EPI_STORE;                                             // weight gradient
-  if (a.tb) return a.c_f32 ? (a.epi == EPI_RES || a.epi == EPI_STORE) : (a.epi == EPI_STORE || a.epi == EPI_MUL_DGELU);  // input gradient
-  return a.c_f32 ? (a.epi == EPI_BIAS || a.epi == EPI_BIAS_RES)                                 // forward
-                 : (a.epi == EPI_BIAS || a.epi == EPI_BIAS_RES || a.epi == EPI_BIAS_GELU);
-}
 // 16-byte epilogue accesses need 8-element alignment of everything the epilogue touches
 bool gemm_epilogue_vec_ok(const Gemm& a) {
-  bool ok = a.N % 8 == 0 && a.ldc % 8 == 0 && aligned(a.C, 16);
-  if (a.bias) ok = ok && aligned(a.bias, 16);
-  if (a.aux) ok = ok && a.ld_aux % 8 == 0 && aligned(a.aux, 16);
-  if (a.aux_out) ok = ok && a.ld_aux % 8 == 0 && aligned(a.aux_out, 16);
+  bool ok = a.N % 8 == 0 && a.ldc % 8 == 0 && aligned_to(a.C, 16);
+  if (a.bias) ok = ok && aligned_to(a.bias, 16);
+  if (a.aux) ok = ok && a.ld_aux % 8 == 0 && aligned_to(a.aux, 16);
+  if (a.aux_out) ok = ok && a.ld_aux % 8 == 0 && aligned_to(a.aux_out, 16);
   return ok;
 }
 
-bool gemm_uses_mfma(int dt, const Gemm& a) { return dt != 0 && gemm_dma_ok(a) && combo_used(a); }
+bool gemm_uses_mfma(int dt, const Gemm& a) { return gemm_path(dt, a) != GEMM_F32; }
 
 // kernel selection; -1 = choose by problem shape, 10 + v: variant v of gemm_dma (tuning hook for experiments)
 #ifdef PT_TUNING_HOOKS   // stand-alone experiments only; the library is built without it
@@ -110,7 +102,9 @@ constexpr int g_cfg_override = -1;
 void gemm(int dt, const Gemm& a, hipStream_t st) {
   if (a.M <= 0 || a.N <= 0) return;
   if (a.c_f32 && (a.epi == EPI_BIAS_GELU || a.epi == EPI_MUL_DGELU)) return;  // not used by the step
-  if (gemm_uses_mfma(dt, a) && (!a.ta || a.ldc == a.N)) {
+  const GemmPath path = gemm_path(dt, a);
+  if (path == GEMM_REG) { gemm_reg(a, st); return; }
+  if (path == GEMM_DMA) {
     if (g_cfg_override >= 10) { gemm_dma(a, g_cfg_override - 10, st); return; }
     if (!a.ta) {
       if (!gemm_dma_skinny(a, st)) gemm_dma(a, gemm_dma_variant(a), st);

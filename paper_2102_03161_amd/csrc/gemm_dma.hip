@@ -25,6 +25,7 @@
 #include "common.h"
 #include "kernels.h"
 #include "gemm_epilogue.h"
+#include "gemm_rules.h"
 #include "ln_bwd_rows.h"
 
 namespace pt {
@@ -804,13 +805,6 @@ void launch_split_epilogue(const Gemm& a, const float* part, int splits, hipStre
 }
 
 }  // namespace
-
-bool gemm_dma_ok(const Gemm& a) {
-  if (!aligned16(a.A) || !aligned16(a.B) || a.lda % 8 || a.ldb % 8 || a.K < 1) return false;
-  if (a.ta && (a.M % 8 || a.M < 8)) return false;      // strided operands: 16-byte pieces along the rows
-  if (!a.tb && (a.N % 8 || a.N < 8)) return false;
-  return (a.ta && !a.tb) || a.K % 8 == 0;              // a k-major operand: 16-byte pieces along k
-}
 
 // workgroups a split-K weight gradient aims for: two 256x128 workgroups per CU
 #ifdef PT_TUNING_HOOKS

@@ -244,9 +244,9 @@ __device__ __forceinline__ void splitk_sum4(const float* __restrict__ part, int 
 bool gemm_epilogue_vec_ok(const Gemm& a);
 void gemm_splitk_reduce(const float* part, int splits, int64_t n, float* out, const float* part2, int64_t n2, float* out2,
                         hipStream_t st);
-bool gemm_dma_ok(const Gemm& a);
 // any strides, sizes and alignment; weight gradients also leave the column sums of B in colsum_out
 void gemm_f32(int dt, const Gemm* a, int n, hipStream_t st);
+void gemm_reg(const Gemm& a, hipStream_t st);
 void gemm_dma(const Gemm& a, int variant, hipStream_t st);
 int gemm_dma_variant(const Gemm& a);   // for forward and input-gradient products
 // few rows, long K, workspace given: split-K with a summing epilogue pass; false if the shape is not taken

@@ -1,6 +1,7 @@
 // Products on the fp32 matrix instructions (v_mfma_f32_16x16x4_f32): every product of fp32 mode, and in bf16 mode
-// the few whose operands the asynchronous bf16 kernels cannot take (class counts or MLP widths that are no multiple
-// of 8); those are widened to fp32 on their way into LDS.
+// those that neither bf16 kernel takes (k-major operands with a K that is no multiple of 8: the second MLP product and
+// the first one's input gradient at such an MLP width, the patch embedding of 14x14x3 patches; odd or very small class
+// counts); those operands are widened to fp32 on their way into LDS.
 //
 // What bounds it: the fp32 matrix rate (64 FLOP per clock and SIMD, 157 TFLOP/s on the chip) is a sixteenth of the
 // bf16 one, so a 64x64 tile needs 38 GB/s of operands per CU where its load path carries 90 to 113; registers as
@@ -16,12 +17,21 @@
 #include "common.h"
 #include "kernels.h"
 #include "gemm_epilogue.h"
+#include "gemm_rules.h"
 
 namespace pt {
 
 namespace {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+// four neighbouring elements, widened
+__device__ __forceinline__ f32x4 load4(const float* p) { return *reinterpret_cast<const f32x4*>(p); }
+__device__ __forceinline__ f32x4 load4(const bf16* p) {
+  union { uint2 u; bf16 h[4]; } t;
+  t.u = *reinterpret_cast<const uint2*>(p);
+  return f32x4{to_f32(t.h[0]), to_f32(t.h[1]), to_f32(t.h[2]), to_f32(t.h[3])};
+}
 
 constexpr int kMaxPlain = 4;
 struct PlainProb {
@@ -57,7 +67,7 @@ struct PlainTile {
       row += r0; k += k0;
       f32x4 v = {0.f, 0.f, 0.f, 0.f};
       if (VEC) {
-        if (row < R && k < K) v = *reinterpret_cast<const f32x4*>(reinterpret_cast<const float*>(p) + (STRIDED ? (int64_t)k * ld + row : (int64_t)row * ld + k));
+        if (row < R && k < K) v = load4(p + (STRIDED ? (int64_t)k * ld + row : (int64_t)row * ld + k));
       } else {
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
@@ -178,10 +188,11 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(PlainArgs ga) {
   }
 }
 
-bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
-// float4 loads: four elements along the contiguous index, from 16-byte aligned rows
-bool vec_ok(const Gemm& a) {
-  return aligned16(a.A) && aligned16(a.B) && a.lda % 4 == 0 && a.ldb % 4 == 0 && (a.ta ? a.M : a.K) % 4 == 0 && (a.tb ? a.K : a.N) % 4 == 0;
+// pieces of four elements along the contiguous index
+bool vec_ok(int dt, const Gemm& a) {
+  const size_t bytes = dt == 0 ? 16 : 8;
+  return aligned_to(a.A, bytes) && aligned_to(a.B, bytes) && a.lda % 4 == 0 && a.ldb % 4 == 0 && (a.ta ? a.M : a.K) % 4 == 0 &&
+         (a.tb ? a.K : a.N) % 4 == 0;
 }
 
 template <typename T, typename TC, bool VEC, int TM, int TN>
@@ -220,13 +231,24 @@ void choose(const Gemm* a, int n, hipStream_t st) {
   else launch<T, TC, VEC, 1, 1>(a, n, st);
 }
 
+// bf16 operands, widened: two tile sizes, the larger one from two workgroups per CU on (4096 x 768 x 3076 485 us on 32x32
+// tiles with single-element loads, 257; 1024 rows 184 against 206), pieces of four where rows allow it (200 rows 139 -> 100 us)
+template <typename TC>
+void choose_bf16(const Gemm& a, hipStream_t st) {
+  const bool vec = vec_ok(1, a), large = (int64_t)cdiv(a.M, 64) * cdiv(a.N, 64) >= 512;
+  if (vec && large) launch<bf16, TC, true, 2, 2>(&a, 1, st);
+  else if (vec) launch<bf16, TC, true, 1, 1>(&a, 1, st);
+  else if (large) launch<bf16, TC, false, 2, 2>(&a, 1, st);
+  else launch<bf16, TC, false, 1, 1>(&a, 1, st);
+}
+
 }  // namespace
 
 void gemm_f32(int dt, const Gemm* a, int n, hipStream_t st) {
   if (dt != 0) {
     for (int i = 0; i < n; ++i) {
-      if (a[i].c_f32) launch<bf16, float, false, 1, 1>(a + i, 1, st);
-      else launch<bf16, bf16, false, 1, 1>(a + i, 1, st);
+      if (a[i].c_f32) choose_bf16<float>(a[i], st);
+      else choose_bf16<bf16>(a[i], st);
     }
     return;
   }
@@ -234,7 +256,7 @@ void gemm_f32(int dt, const Gemm* a, int n, hipStream_t st) {
     int m = 1;   // products of one layout and epilogue over the same contraction share a launch
     while (m < kMaxPlain && i + m < n && a[i + m].ta == a[i].ta && a[i + m].tb == a[i].tb && a[i + m].epi == a[i].epi) ++m;
     bool vec = true;
-    for (int j = 0; j < m; ++j) vec = vec && vec_ok(a[i + j]);
+    for (int j = 0; j < m; ++j) vec = vec && vec_ok(dt, a[i + j]);
     if (vec) choose<float, float, true>(a + i, m, st);
     else choose<float, float, false>(a + i, m, st);
     i += m;

@@ -1,0 +1,63 @@
+"""The library's choice of a kernel for a product (csrc/gemm_rules.h), compiled for the host and asked through ctypes."""
+import ctypes
+import os
+import subprocess
+import tempfile
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2102_03161_amd", "csrc")
+
+F32, REG, DMA = 0, 1, 2                                     # GemmPath
+STORE, BIAS, BIAS_RES, BIAS_GELU, MUL_DGELU, RES = range(6)  # Epi
+
+SOURCE = r"""
+#include "gemm_rules.h"
+using namespace pt;
+static Gemm make(int M, int N, int K, int ta, int tb, int epi, int c_f32, long long ws_floats) {
+  Gemm g;
+  g.A = g.B = g.C = reinterpret_cast<void*>(uintptr_t(4096));
+  g.M = M; g.N = N; g.K = K; g.ta = ta; g.tb = tb; g.epi = Epi(epi); g.c_f32 = c_f32;
+  g.lda = ta ? M : K; g.ldb = tb ? K : N; g.ldc = N;
+  if (ws_floats) { g.ws = reinterpret_cast<float*>(uintptr_t(4096)); g.ws_floats = size_t(ws_floats); }
+  return g;
+}
+extern "C" int path(int dt, int M, int N, int K, int ta, int tb, int epi, int c_f32) {
+  return gemm_path(dt, make(M, N, K, ta, tb, epi, c_f32, 0));
+}
+extern "C" int reg_tiling(int M, int N, int K, int ta, int epi, int c_f32, long long ws_floats) {
+  const GemmRegTiling t = gemm_reg_tiling(make(M, N, K, ta, 0, epi, c_f32, ws_floats));
+  return t.tile * 100 + t.splits;
+}
+"""
+
+_lib = None
+
+
+def lib():
+    global _lib
+    if _lib is None:
+        with tempfile.TemporaryDirectory() as d:
+            so = os.path.join(d, "rules.so")
+            subprocess.run(["g++", "-std=c++17", "-O1", "-fPIC", "-shared", "-I", CSRC, "-x", "c++", "-", "-o", so],
+                           input=SOURCE.encode(), check=True)
+            _lib = ctypes.CDLL(so)
+        _lib.reg_tiling.argtypes = [ctypes.c_int] * 6 + [ctypes.c_longlong]
+    return _lib
+
+
+def forward(tokens, K, N, epi, c_f32=False, dt=1):
+    return lib().path(dt, tokens, N, K, 0, 0, epi, int(c_f32))
+
+
+def input_gradient(tokens, K, N, epi=STORE, c_f32=False, dt=1):
+    return lib().path(dt, tokens, N, K, 0, 1, epi, int(c_f32))
+
+
+def weight_gradient(rows, cols, tokens, dt=1):
+    return lib().path(dt, rows, cols, tokens, 1, 0, STORE, 1)
+
+
+def reg_tiling(M, N, K, ta, epi=STORE, c_f32=False, ws_floats=0):
+    """(tile, splits) of the register-staged kernel"""
+    t = lib().reg_tiling(M, N, K, int(ta), epi, int(c_f32), ws_floats)
+    return t // 100, t % 100

@@ -1,0 +1,37 @@
+"""Which kernel the products of the training step take, without a GPU."""
+import pytest
+
+from tests import gemm_rules as R
+
+
+@pytest.mark.parametrize("tokens", [1, 24, 200, 4096, 12288])
+@pytest.mark.parametrize("F", [100, 1028, 3076, 4300])
+def test_mlp_widths_that_are_no_multiple_of_8_stay_on_the_bf16_matrix_instructions(tokens, F):
+    """F % 4 == 0 is accepted: the first MLP product (for any number of rows: a row's result must not depend on the
+    batch) and both MLP weight gradients have a strided operand of that width."""
+    D = 768
+    assert R.forward(tokens, D, F, R.BIAS_GELU) == R.REG
+    few = tokens <= 32                                   # nothing but the write of the result
+    assert R.weight_gradient(D, F, tokens) == (R.F32 if few else R.REG)      # W1
+    assert R.weight_gradient(F, D, tokens) == (R.F32 if few else R.REG)      # W2
+    assert R.input_gradient(tokens, D, F, R.MUL_DGELU) == R.DMA
+    # k-major operands of that width have no 16-byte pieces
+    assert R.forward(tokens, F, D, R.BIAS_RES) == R.F32
+    assert R.input_gradient(tokens, F, D) == R.F32
+
+
+def test_patch_and_class_counts_that_are_no_multiple_of_8():
+    assert R.weight_gradient(588, 768, 64 * 256) == R.REG             # 14 x 14 x 3 patches
+    assert R.forward(64, 768, 100, R.BIAS, c_f32=True) == R.REG       # 100 classes
+    assert R.weight_gradient(768, 100, 64) == R.REG
+    assert R.weight_gradient(768, 10, 64) == R.F32                    # fewer than 32 columns
+    assert R.forward(64, 768, 10, R.BIAS, c_f32=True) == R.F32
+    assert R.forward(64, 768, 101, R.BIAS, c_f32=True) == R.F32       # odd
+
+
+def test_multiples_of_8_take_the_asynchronous_kernels():
+    for tokens in (1, 231, 12608):
+        assert R.forward(tokens, 768, 3072, R.BIAS_GELU) == R.DMA
+        assert R.input_gradient(tokens, 3072, 768) == R.DMA
+        assert R.weight_gradient(768, 3072, tokens) == R.DMA
+        assert R.forward(tokens, 768, 3072, R.BIAS_GELU, dt=0) == R.F32

@@ -6,6 +6,7 @@ import numpy as np
 import pytest
 
 from paper_2102_03161_amd import binding
+from tests import gemm_rules as R
 from tests import gpu_harness as H
 
 pytestmark = pytest.mark.gpu
@@ -35,19 +36,64 @@ def torch_mod():
     return torch
 
 
-@pytest.mark.parametrize("name", CASES)
-def test_products_at_tile_edges(torch_mod, name):
-    w, k, nb, seed = CASES[name]
+def check_step(torch, name, w, k, nb, seed):
     print(f"tile edges: {name}", flush=True)
     ctx = binding.Context(binding.make_config(w, B=nb))
     vals = H.init_values(w, ctx, seed)
     H.load_params(ctx, vals)
     x, y = H.batch_for(w, seed, nb)
-    g = H.gpu_step(torch_mod, ctx, w, x, y, k)
+    g = H.gpu_step(torch, ctx, w, x, y, k)
     ctx.close()
     o = H.oracle_step(w, vals, x, y, k)
     m = H.storage_model_step(w, vals, x, y, k)
     H.compare_step(w, g, o, k, 2e-2, check_params=False, model=m, rss=H.summand_rss(w, vals, x, y, k))
+
+
+def prefix_rows(torch, w):
+    ctx = binding.Context(binding.make_config(w))
+    H.load_params(ctx, H.init_values(w, ctx, 5))
+    ctx.set_freeze_boundary(2)
+    x = H.to_dev(torch, H.batch_for(w, 5, 65)[0])
+    rows = {}
+    for nb in (65, 7, 1):
+        ctx.frozen_forward(x[:nb].contiguous())
+        rows[nb] = ctx.read_activation(binding.ACT_HK, (nb, w["S"], w["D"]))
+    ctx.close()
+    for nb in (7, 1):
+        assert np.array_equal(rows[nb], rows[65][:nb]), nb
+
+
+@pytest.mark.parametrize("name", CASES)
+def test_products_at_tile_edges(torch_mod, name):
+    w, k, nb, seed = CASES[name]
+    check_step(torch_mod, name, w, k, nb, seed)
+
+
+# rows that are even but no multiple of 8 elements long
+EVEN_CASES = {
+    # patches of 588 values, 1028-wide MLP, 100 classes: register-staged 64x64 tiles, split contractions with a k tail
+    "patch14": (dict(VIT, img=56, patch=14, S=17, L=2, D=256, H=4, F=1028, n_out=100, B=33), 0, 33, 46),
+    # the same on 17 rows, the patch weights frozen
+    "patch14_few_rows": (dict(VIT, img=56, patch=14, S=17, L=2, D=256, H=4, F=1028, n_out=102, B=1), 1, 1, 47),
+    # 2926 tokens: 128x128 tiles in the forward product and (split) in both MLP weight gradients
+    "mlp3076": (dict(BERT, L=1, D=768, H=12, F=3076, S=77, max_pos=80, B=38), 0, 38, 48),
+}
+
+
+@pytest.mark.parametrize("name", EVEN_CASES)
+def test_rows_that_are_no_multiple_of_8_long(torch_mod, name):
+    w, k, nb, seed = EVEN_CASES[name]
+    tokens, D, F = nb * w["S"], w["D"], w["F"]
+    assert R.forward(tokens, D, F, R.BIAS_GELU) == R.REG
+    assert R.weight_gradient(D, F, tokens) == R.weight_gradient(F, D, tokens) == (R.REG if tokens > 32 else R.F32)
+    check_step(torch_mod, name, w, k, nb, seed)
+
+
+def test_even_rows_of_the_prefix_do_not_depend_on_the_tiles(torch_mod):
+    """MLP width 3076: the first product on 128x128 and 64x64 register-staged tiles, the second on 64x64 and 32x32 tiles of
+    the fp32 instructions."""
+    assert [R.reg_tiling(50 * nb, 3076, 768, False, R.BIAS_GELU)[0] for nb in (65, 7, 1)] == [128, 64, 64]
+    prefix_rows(torch_mod, dict(VIT, L=2, D=768, H=12, F=3076, n_out=10, B=65))
 
 
 @pytest.mark.parametrize("nb,F", [(1, 3072), (9, 3072), (40, 3072), (3, 1028)])
@@ -70,16 +116,4 @@ def test_fp32_products_at_tile_edges(torch_mod, nb, F):
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_prefix_rows_do_not_depend_on_the_tiles(torch_mod, dtype):
     """3250 rows take 128x128 tiles in the wide products, 50 and 350 rows smaller ones."""
-    torch = torch_mod
-    w = dict(VIT, L=2, D=768, H=12, F=3072, n_out=10, B=65, dtype=dtype)
-    ctx = binding.Context(binding.make_config(w))
-    H.load_params(ctx, H.init_values(w, ctx, 5))
-    ctx.set_freeze_boundary(2)
-    x = H.to_dev(torch, H.batch_for(w, 5, 65)[0])
-    rows = {}
-    for nb in (65, 7, 1):
-        ctx.frozen_forward(x[:nb].contiguous())
-        rows[nb] = ctx.read_activation(binding.ACT_HK, (nb, w["S"], w["D"]))
-    ctx.close()
-    for nb in (7, 1):
-        assert np.array_equal(rows[nb], rows[65][:nb]), nb
+    prefix_rows(torch_mod, dict(VIT, L=2, D=768, H=12, F=3072, n_out=10, B=65, dtype=dtype))
