@@ -96,6 +96,42 @@ struct PlainTile {
   }
 };
 
+// Column sums of B over k (the bias gradient of a weight-gradient product), from the fragments that the matrix
+// instructions consume.  A column's k values go to four lanes, which add them in three levels: eight tiles (256 k), eight
+// of those, the rest.  Relative error of that order on N(0, 1) columns: 9.9e-8 over 1576 tokens, 1.2e-7 over 12608
+// (128 interleaved chains 1.3e-7 and 2.1e-7, one chain over all tokens 6.6e-7 and 2.0e-6).
+template <int TN>
+struct PlainColSum {
+  float s0[TN], s1[TN], s2[TN];
+  __device__ __forceinline__ PlainColSum() {
+#pragma unroll
+    for (int j = 0; j < TN; ++j) s0[j] = s1[j] = s2[j] = 0.f;
+  }
+  __device__ __forceinline__ void add(const f32x4 (&b)[TN]) {
+#pragma unroll
+    for (int j = 0; j < TN; ++j) s0[j] += (b[j][0] + b[j][1]) + (b[j][2] + b[j][3]);
+  }
+  // behind tile t
+  __device__ __forceinline__ void fold(int t) {
+    if ((t & 7) != 7) return;
+#pragma unroll
+    for (int j = 0; j < TN; ++j) { s1[j] += s0[j]; s0[j] = 0.f; }
+    if ((t & 63) != 63) return;
+#pragma unroll
+    for (int j = 0; j < TN; ++j) { s2[j] += s1[j]; s1[j] = 0.f; }
+  }
+  // `out`: the sums of this wave's first column; n: columns that exist from there on
+  __device__ __forceinline__ void store(float* out, int n, int lane) const {
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+      float v = (s0[j] + s1[j]) + s2[j];
+      v += __shfl_xor(v, 16, 64);
+      v += __shfl_xor(v, 32, 64);
+      if (lane < 16 && j * 16 + lane < n) out[j * 16 + lane] = v;
+    }
+  }
+};
+
 // Tiles of 32 TM x 32 TN, four waves in two rows of two, each TM x TN units of 16x16.  Up to four problems in one
 // launch; workgroups go to the XCDs round-robin, and each XCD takes a contiguous run of tiles.
 template <typename T, typename TC, bool TA, bool TB, bool VEC, int TM, int TN>
@@ -123,8 +159,8 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(PlainArgs ga) {
 #pragma unroll
     for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
   f32x4 ra[LA::N4], rb[LB::N4];
-  const bool do_colsum = !TB && p.colsum != nullptr && m0 == 0;
-  float cs = 0.f;
+  const bool do_colsum = __builtin_amdgcn_readfirstlane(TA && p.colsum != nullptr && m0 == 0 && wm == 0 ? 1 : 0) != 0;
+  PlainColSum<TN> cs;
   const int nk = (p.K + kPlainBK - 1) / kPlainBK;
   LA::load(A, p.lda, p.M, p.K, m0, 0, tid, ra);
   LB::load(B, p.ldb, p.N, p.K, n0, 0, tid, rb);
@@ -152,16 +188,16 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(PlainArgs ga) {
         for (int i = 0; i < TM; ++i)
 #pragma unroll
           for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][e], b[j][e], acc[i][j], 0, 0, 0);
-    }
-    if constexpr (!TB) {
-      if (do_colsum && tid < BN) {
-#pragma unroll
-        for (int k = 0; k < kPlainBK; ++k) cs += bs[k * LB::LD + tid];
+      if constexpr (TA) {
+        if (do_colsum) cs.add(b);
       }
     }
+    if constexpr (TA) {
+      if (do_colsum) cs.fold(t);
+    }
   }
-  if constexpr (!TB) {
-    if (do_colsum && tid < BN && n0 + tid < p.N) p.colsum[n0 + tid] = cs;
+  if constexpr (TA) {
+    if (do_colsum) cs.store(p.colsum + n0 + wn * 16 * TN, p.N - n0 - wn * 16 * TN, lane);
   }
   // accumulator layout of the 16x16 MFMA: lane holds column lane % 16, rows 4 (lane / 16) + v
   const GemmDev<T> g{A, B, p.C, p.M, p.N, p.K, p.lda, p.ldb, p.ldc, reinterpret_cast<const T*>(p.bias),

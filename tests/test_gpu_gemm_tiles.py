@@ -117,3 +117,21 @@ def test_fp32_products_at_tile_edges(torch_mod, nb, F):
 def test_prefix_rows_do_not_depend_on_the_tiles(torch_mod, dtype):
     """3250 rows take 128x128 tiles in the wide products, 50 and 350 rows smaller ones."""
     prefix_rows(torch_mod, dict(VIT, L=2, D=768, H=12, F=3072, n_out=10, B=65, dtype=dtype))
+
+
+def test_fp32_bias_gradients_over_many_tokens(torch_mod):
+    """fp32 mode: the patch bias gradient is the sum of the patch rows' gradients over 12544 tokens, the position
+    gradients are the same rows summed over 49 samples each.  Their sum in 64 bits is the reference: its own error,
+    chains of 49 rows averaged over 256 positions, is about 1e-8.  These rows mostly agree in sign (their sum is 16 times
+    its root-sum-square); on such columns the kernel's order of additions is 5e-8 off, one chain over all tokens
+    1.7e-6 (both emulated on N(1, 1)).  The bar is 4 times the former."""
+    w = dict(VIT, L=2, D=64, H=4, F=256, img=64, patch=4, S=257, n_out=10, B=49, dtype="f32")
+    ctx = binding.Context(binding.make_config(w))
+    H.load_params(ctx, H.init_values(w, ctx, 9))
+    x, y = H.batch_for(w, 9, 49)
+    grads = H.gpu_step(torch_mod, ctx, w, x, y, 0)["grads"]
+    ctx.close()
+    want = grads["front.pos"].astype(np.float64)[1:].sum(0)
+    err = np.linalg.norm(grads["front.b_pe"].ravel() - want) / np.linalg.norm(want)
+    print(f"patch bias gradient over 12544 tokens: {err:.2e}", flush=True)
+    assert err < 2e-7
