@@ -1057,8 +1057,8 @@ bool gemm_dma_skinny(const Gemm& a, hipStream_t st) {
 }
 
 void gemm_dma(const Gemm& a, int variant, hipStream_t st) {
-  // variants: 1 = 128x128 tiles, 2 = 256x128, 3 = 64x64, 4 = 128x128 with eight waves, 5 / 6 = the two-group kernel
-  // with 256 / 192-row tiles
+  // variants: 1 = 128x128 tiles (K a multiple of 32), 2 = 256x128 (of 32), 3 = 64x64 (any K), 4 = 128x128 with eight waves
+  // (any K), 5 / 6 = the two-group kernel with 256 / 192-row tiles (K a multiple of 64)
   if (a.ta) {   // a single weight gradient with a long contraction (a block's four go through gemm_wgrad_group)
     if (variant == 1) dispatch_wgrad<128, 128, 2, 2>(a, st);
     else dispatch_wgrad<256, 128, 4, 2>(a, st);
@@ -1071,50 +1071,12 @@ void gemm_dma(const Gemm& a, int variant, hipStream_t st) {
     // fit one workgroup less per CU and lose more than the whole-line loads gain.
     case 2: dispatch_fwd<256, 128, 4, 2, 3, 32>(a, st); break;
     case 1: dispatch_fwd<128, 128, 2, 2, 3, 32>(a, st); break;
-    case 4: dispatch_fwd<128, 128, 4, 2, 2, 64>(a, st); break;
+    case 4:
+      if (a.K % 64 == 0) dispatch_fwd<128, 128, 4, 2, 2, 64>(a, st);
+      else dispatch_fwd<128, 128, 4, 2, 2, 64, true>(a, st);
+      break;
     default: dispatch_fwd<64, 64, 2, 2, 3, 64, true>(a, st); break;
   }
-}
-
-// Kernel choice for forward and input-gradient products.  Every variant runs the same matrix instructions in the
-// same k order, so a row's result does not depend on the choice (nor, through it, on the batch size).
-int gemm_dma_variant(const Gemm& a) {
-  if (a.K % 64 != 0) return a.K % 32 == 0 && (int64_t)cdiv(a.M, 128) * cdiv(a.N, 128) > 256 ? 1 : 3;
-  if (a.M >= 4096) {
-    // At least 4096 rows: the two-group kernel with 256x256 or 192x256 tiles, one workgroup per CU, whichever
-    // fills whole rounds of 256 CUs better (M = 12608, N = 768: 198 tiles of 192x256 against 150 of 256x256).
-    const int tn = cdiv(a.N, 256);
-    const int t192 = cdiv(a.M, 192) * tn, t256 = cdiv(a.M, 256) * tn;
-    if (a.N >= 3072 && (a.K < 1024 || a.tb)) {
-      // Wide and short: 192- or 256-row tiles only when their last round is (nearly) full, as for 12288 tokens
-      // (768 tiles of 192 rows at N = 3072; 9-10 % faster than 256x128 there) or 25216 (1188 tiles of 256 rows, 93 %
-      // of five rounds: 169 us against 183 with GELU, 149 against 164 with the saved GELU'); otherwise from 9000
-      // rows on 256x128 tiles, two workgroups per CU, whose prologues and epilogues overlap.
-      const int last = t192 % 256;
-      if (last == 0 || last >= 224) return 6;
-      if (t256 * 10 >= cdiv(t256, 256) * 256 * 9) return 5;
-      if (a.M >= 9000) return 2;
-    } else {
-      const int v = cdiv(t192, 256) * 192 < cdiv(t256, 256) * 256 ? 6 : 5;
-      // fewer tiles than 60 % of the CUs of their rounds (8192 tokens at N = 768: 129 tiles): smaller tiles fill the
-      // chip better (6-13 % faster on those five products)
-      const int tiles = v == 6 ? t192 : t256;
-      if (tiles * 10 >= cdiv(tiles, 256) * 256 * 6) return v;
-    }
-  }
-  // Below that, 128x128 or 64x64 tiles.  A workgroup alone on its CU is held to the latency and rate of its own
-  // loads (45-50 GB/s per CU), so what counts is the number of workgroups that the fullest CU gets.  Microseconds
-  // fitted to launches of 17 to 8192 rows with N and K of 768 to 3072, within 15 % (k = K / 1000): a 128x128
-  // workgroup alone 5.7 + 8.9 k, w of them w (5.3 + 7.0 k); a 64x64 workgroup alone 3.5 + 4.7 k, w of them
-  // w (1.9 + 3.05 k).  1379 x 768 x 3072: 66 tiles, 33 us, against 264 small ones, 21 us; 2639 x 3072 x 768: 504
-  // tiles, 24 us, against 2016 small ones, 30 us.
-  const int64_t t128 = (int64_t)cdiv(a.M, 128) * cdiv(a.N, 128), t64 = (int64_t)cdiv(a.M, 64) * cdiv(a.N, 64);
-  const double w128 = (double)((t128 + 255) / 256), w64 = (double)((t64 + 255) / 256), k = 1e-3 * a.K;
-  const double us128 = w128 > 1 ? w128 * (5.3 + 7.0 * k) : 5.7 + 8.9 * k;
-  const double us64 = w64 > 1 ? w64 * (1.9 + 3.05 * k) : 3.5 + 4.7 * k;
-  if (us64 <= us128) return 3;
-  // eight waves and whole-line loads where both operands are k-major and CUs hold two tiles: 5-10 % faster
-  return a.tb && t128 > 256 ? 4 : 1;
 }
 
 }  // namespace pt

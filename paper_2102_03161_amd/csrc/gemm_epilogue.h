@@ -248,7 +248,6 @@ void gemm_splitk_reduce(const float* part, int splits, int64_t n, float* out, co
 void gemm_f32(int dt, const Gemm* a, int n, hipStream_t st);
 void gemm_reg(const Gemm& a, hipStream_t st);
 void gemm_dma(const Gemm& a, int variant, hipStream_t st);
-int gemm_dma_variant(const Gemm& a);   // for forward and input-gradient products
 // few rows, long K, workspace given: split-K with a summing epilogue pass; false if the shape is not taken
 bool gemm_dma_skinny(const Gemm& a, hipStream_t st);
 bool gemm_wgrad_group(const Gemm* a, int n, hipStream_t st, hipEvent_t mid, WgradCarry* carry, LnBwdRide* ln);

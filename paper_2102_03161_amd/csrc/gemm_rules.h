@@ -64,6 +64,52 @@ inline GemmRegTiling gemm_reg_tiling(const Gemm& a) {
   return GemmRegTiling{tile, (int)splits};
 }
 
+// Variant of the asynchronous kernels, forward and input-gradient products: 1 = 128x128 tiles, 2 = 256x128, 3 = 64x64, 4 =
+// 128x128 with eight waves, 5 / 6 = the two-group kernel with 256 / 192-row tiles.
+// Every variant runs the same matrix instructions in the
+// same k order, so a row's result does not depend on the choice (nor, through it, on the batch size).
+inline int gemm_dma_variant(const Gemm& a) {
+  auto cdiv = [](int64_t x, int64_t y) { return (x + y - 1) / y; };
+  if (a.M >= 4096 && a.K % 64 == 0) {
+    // At least 4096 rows: the two-group kernel with 256x256 or 192x256 tiles, one workgroup per CU, whichever
+    // fills whole rounds of 256 CUs better (M = 12608, N = 768: 198 tiles of 192x256 against 150 of 256x256).
+    const int64_t tn = cdiv(a.N, 256);
+    const int64_t t192 = cdiv(a.M, 192) * tn, t256 = cdiv(a.M, 256) * tn;
+    if (a.N >= 3072 && (a.K < 1024 || a.tb)) {
+      // Wide and short: 192- or 256-row tiles only when their last round is (nearly) full, as for 12288 tokens
+      // (768 tiles of 192 rows at N = 3072; 9-10 % faster than 256x128 there) or 25216 (1188 tiles of 256 rows, 93 %
+      // of five rounds: 169 us against 183 with GELU, 149 against 164 with the saved GELU'); otherwise from 9000
+      // rows on 256x128 tiles, two workgroups per CU, whose prologues and epilogues overlap.
+      const int64_t last = t192 % 256;
+      if (last == 0 || last >= 224) return 6;
+      if (t256 * 10 >= cdiv(t256, 256) * 256 * 9) return 5;
+      if (a.M >= 9000) return 2;
+    } else {
+      const int v = cdiv(t192, 256) * 192 < cdiv(t256, 256) * 256 ? 6 : 5;
+      // fewer tiles than 60 % of the CUs of their rounds (8192 tokens at N = 768: 129 tiles): smaller tiles fill the
+      // chip better (6-13 % faster on those five products)
+      const int64_t tiles = v == 6 ? t192 : t256;
+      if (tiles * 10 >= cdiv(tiles, 256) * 256 * 6) return v;
+    }
+  }
+  // Below that, 128x128 or 64x64 tiles.  A workgroup alone on its CU is held to the latency and rate of its own
+  // loads (45-50 GB/s per CU), so what counts is the number of workgroups that the fullest CU gets.  Microseconds
+  // fitted to launches of 17 to 8192 rows with N and K of 768 to 3072, within 15 % (k = K / 1000): a 128x128
+  // workgroup alone 5.7 + 8.9 k, w of them w (5.3 + 7.0 k); a 64x64 workgroup alone 3.5 + 4.7 k, w of them
+  // w (1.9 + 3.05 k).  1379 x 768 x 3072: 66 tiles, 33 us, against 264 small ones, 21 us; 2639 x 3072 x 768: 504
+  // tiles, 24 us, against 2016 small ones, 30 us.
+  const int64_t t128 = cdiv(a.M, 128) * cdiv(a.N, 128), t64 = cdiv(a.M, 64) * cdiv(a.N, 64);
+  const double w128 = (double)((t128 + 255) / 256), w64 = (double)((t64 + 255) / 256), k = 1e-3 * a.K;
+  const double us128 = w128 > 1 ? w128 * (5.3 + 7.0 * k) : 5.7 + 8.9 * k;
+  const double us64 = w64 > 1 ? w64 * (1.9 + 3.05 * k) : 3.5 + 4.7 * k;
+  if (us64 <= us128) return 3;
+  // K no multiple of 32: only eight waves on 64-wide k tiles take it (16384 x 1152 x 4304 228 us against 349 on 64x64 tiles
+  // and 235 on four waves with 32-wide ones; input gradients 254, 346, 273; 8192 x 3072 x 776 65, 98, 74)
+  if (a.K % 32) return 4;
+  // eight waves and whole-line loads where both operands are k-major and CUs hold two tiles: 5-10 % faster
+  return a.K % 64 == 0 && a.tb && t128 > 256 ? 4 : 1;
+}
+
 inline GemmPath gemm_path(int dt, const Gemm& a) {
   if (dt == 0 || !gemm_combo_used(a) || (a.ta && a.ldc != a.N)) return GEMM_F32;   // split-K slabs are dense
   if (gemm_dma_ok(a)) return GEMM_DMA;

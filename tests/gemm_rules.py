@@ -24,6 +24,7 @@ static Gemm make(int M, int N, int K, int ta, int tb, int epi, int c_f32, long l
 extern "C" int path(int dt, int M, int N, int K, int ta, int tb, int epi, int c_f32) {
   return gemm_path(dt, make(M, N, K, ta, tb, epi, c_f32, 0));
 }
+extern "C" int dma_variant(int M, int N, int K, int tb) { return gemm_dma_variant(make(M, N, K, 0, tb, EPI_STORE, 0, 0)); }
 extern "C" int reg_tiling(int M, int N, int K, int ta, int epi, int c_f32, long long ws_floats) {
   const GemmRegTiling t = gemm_reg_tiling(make(M, N, K, ta, 0, epi, c_f32, ws_floats));
   return t.tile * 100 + t.splits;
@@ -55,6 +56,15 @@ def input_gradient(tokens, K, N, epi=STORE, c_f32=False, dt=1):
 
 def weight_gradient(rows, cols, tokens, dt=1):
     return lib().path(dt, rows, cols, tokens, 1, 0, STORE, 1)
+
+
+# variants of the asynchronous kernels
+T128, T256x128, T64, T128_EIGHT_WAVES, TWO_GROUPS_256, TWO_GROUPS_192 = 1, 2, 3, 4, 5, 6
+
+
+def dma_variant(M, N, K, tb=False):
+    """tiles of a forward (tb: input-gradient) product"""
+    return lib().dma_variant(M, N, K, int(tb))
 
 
 def reg_tiling(M, N, K, ta, epi=STORE, c_f32=False, ws_floats=0):

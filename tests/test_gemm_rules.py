@@ -35,3 +35,24 @@ def test_multiples_of_8_take_the_asynchronous_kernels():
         assert R.input_gradient(tokens, 3072, 768) == R.DMA
         assert R.weight_gradient(768, 3072, tokens) == R.DMA
         assert R.forward(tokens, 768, 3072, R.BIAS_GELU, dt=0) == R.F32
+
+
+def test_contractions_that_are_no_multiple_of_64():
+    """Many rows take 128x128 tiles, whatever K; few rows 64x64."""
+    for tb in (False, True):
+        for M, N, K in [(16384, 1152, 4304), (32768, 600, 200), (16384, 984, 328), (8192, 3072, 776), (4096, 800, 200)]:
+            assert R.dma_variant(M, N, K, tb) == R.T128_EIGHT_WAVES, (M, N, K)
+        for M, N, K in [(4096, 768, 3104), (16384, 768, 800)]:
+            assert R.dma_variant(M, N, K, tb) == R.T128, (M, N, K)
+        for M, N, K in [(1024, 1152, 4304), (200, 768, 3080), (4096, 200, 200), (2639, 768, 3104), (4096, 480, 160)]:
+            assert R.dma_variant(M, N, K, tb) == R.T64, (M, N, K)
+
+
+def test_variants_take_the_contractions_they_are_given():
+    for M in (1, 7, 64, 500, 1379, 4096, 5000, 8192, 12608, 25216, 32768):
+        for N in (8, 200, 768, 1152, 2304, 3072, 4096):
+            for K in range(8, 4400, 8):
+                for tb in (False, True):
+                    v = R.dma_variant(M, N, K, tb)
+                    need = {R.T128: 32, R.T256x128: 32, R.TWO_GROUPS_256: 64, R.TWO_GROUPS_192: 64}.get(v, 8)
+                    assert K % need == 0, (M, N, K, tb, v)

@@ -24,6 +24,8 @@ CASES = {
     "narrow_split": (dict(BERT, L=2, D=256, H=4, F=1024, S=77, max_pos=80, B=14), 0, 14, 43),
     # 2079 tokens: the two-group weight-gradient kernel with a partial last k tile
     "group_tail": (dict(BERT, L=2, D=512, H=8, F=2048, S=77, max_pos=80, B=27), 0, 27, 44),
+    # 3850 x 800 x 200: 128x128 tiles of eight waves with an eighth of a k tile at the end, forward and backward
+    "eight_waves_tail": (dict(BERT, L=1, D=200, H=25, F=800, S=77, max_pos=80, B=50), 0, 50, 49),
     # 2639 x 3072 input gradients: 504 tiles of 128x128, eight waves each
     "eight_waves": (dict(BERT, L=1, D=768, H=12, F=3072, S=203, max_pos=203, B=13), 0, 13, 45),
 }
@@ -94,6 +96,13 @@ def test_even_rows_of_the_prefix_do_not_depend_on_the_tiles(torch_mod):
     the fp32 instructions."""
     assert [R.reg_tiling(50 * nb, 3076, 768, False, R.BIAS_GELU)[0] for nb in (65, 7, 1)] == [128, 64, 64]
     prefix_rows(torch_mod, dict(VIT, L=2, D=768, H=12, F=3076, n_out=10, B=65))
+
+
+def test_prefix_rows_with_a_k_tail_do_not_depend_on_the_tiles(torch_mod):
+    """Width 200, MLP width 1000: the first MLP product on 128x128 tiles of eight waves and on 64x64 tiles, both with a
+    partial last k tile."""
+    assert [R.dma_variant(50 * nb, 1000, 200) for nb in (65, 7, 1)] == [R.T128_EIGHT_WAVES, R.T64, R.T64]
+    prefix_rows(torch_mod, dict(VIT, L=2, D=200, H=25, F=1000, n_out=10, B=65))
 
 
 @pytest.mark.parametrize("nb,F", [(1, 3072), (9, 3072), (40, 3072), (3, 1028)])
