@@ -138,15 +138,4 @@ void gemm_wgrad_batch(int dt, const Gemm* g, int n, hipStream_t st, hipEvent_t m
   if (mid) (void)hipEventRecord(mid, st);
 }
 
-size_t gemm_wgrad_batch_ws_floats(int D, int F) {
-  const int64_t shapes[4][2] = {{D, 3 * D}, {D, D}, {D, F}, {F, D}};
-  int64_t tiles = 0, per_split = 0;
-  for (auto& sh : shapes) {
-    tiles += ((sh[0] + 255) / 256) * ((sh[1] + 255) / 256);
-    per_split += sh[0] * sh[1] + sh[1];
-  }
-  const int64_t splits = std::min<int64_t>(16, std::max<int64_t>(1, 256 / std::max<int64_t>(tiles, 1)));
-  return (size_t)(splits * per_split);
-}
-
 }  // namespace pt

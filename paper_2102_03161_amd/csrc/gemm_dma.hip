@@ -842,67 +842,15 @@ static void dispatch_wgrad(const Gemm& a, hipStream_t st) {
   }
 }
 
-// How the weight gradients of a launch are tiled and split.
-struct WgradTiling {
-  int bm, bn, bk, splits;   // bn == 256: the two-group kernel, otherwise the single-role pipeline
-};
-#ifdef PT_TUNING_HOOKS
-WgradTiling g_wgrad_force{};
-void gemm_set_wgrad(int bm, int bn, int bk, int splits) { g_wgrad_force = WgradTiling{bm, bn, bk, splits}; }
-#endif
-static WgradTiling wgrad_tiling(const Gemm* a, int n) {
-#ifdef PT_TUNING_HOOKS
-  if (g_wgrad_force.bm) return g_wgrad_force;
-#endif
-  // Microseconds of a launch, fitted to launches over a block's four matrices of widths 256 and 768 with 231 to 12608
-  // tokens (within 15 %; k = tokens / 1000, s splits, w workgroups on the fullest CU):
-  //   64x64 tiles    the larger of 3.6 + 7.1 k / s (one workgroup's own chain) and w (1.2 + 3.75 k / s)
-  //   128x128 tiles  the larger of 4.7 + 12.5 k / s and w (4 + 9.8 k / s)
-  //   256x256 tiles  w (10 + 26 k / s)
-  // and for s > 1 the slabs' summation at 4 TB/s, also where it rides on another launch (WgradCarry).
-  // Width 768: 1379 tokens 34 us on 128x128 tiles against 43 on 64x64 ones, 2639 tokens 58 against 67 on 256x256 ones
-  // with two splits (a step of 2 x 2639 tokens, four blocks frozen, 5920 us against 6300), 8192 tokens 131 us on 256x256
-  // ones against 164 by the line above on 128x128; width 256: 231 tokens 5.2 us on 64x64 tiles, 2310 tokens 20 against
-  // 34 on 128x128 ones.
-  const double k = 1e-3 * a[0].K;
-  double floats = 0;
-  for (int i = 0; i < n; ++i) floats += (double)a[i].M * a[i].N;
-  WgradTiling best{64, 64, 64, 1};
-  double best_us = 1e30;
-  auto consider = [&](int b, int s, double chain0, double chain, double each0, double each, double red) {
-    int64_t t = 0;
-    for (int i = 0; i < n; ++i) t += (int64_t)cdiv(a[i].M, b) * cdiv(a[i].N, b);
-    const double w = (double)((t * s + 255) / 256);
-    double us = std::max(chain0 + chain * k / s, w * (each0 + each * k / s));
-    if (s > 1) us += red * (4.0 + (s + 1) * floats * 1e-6);
-    if (us < best_us) { best_us = us; best = WgradTiling{b, b, 64, s}; }
-  };
-  for (int s = 1; s <= 4 && (s == 1 || a[0].K >= 512 * s); s *= 2) {
-    consider(64, s, 3.6, 7.1, 1.2, 3.75, 1.0);
-    consider(128, s, 4.7, 12.5, 4.0, 9.8, 1.0);
-  }
-  int64_t t256 = 0;
-  for (int i = 0; i < n; ++i) t256 += (int64_t)cdiv(a[i].M, 256) * cdiv(a[i].N, 256);
-  int s = (int)(256 / t256);
-  if (s > a[0].K / 256) s = a[0].K / 256;
-  if (s > 16) s = 16;
-  consider(256, s < 1 ? 1 : s, 10.0, 26.0, 10.0, 26.0, 1.0);
-  return best;
-}
-
 bool gemm_wgrad_group(const Gemm* a, int n, hipStream_t st, hipEvent_t mid, WgradCarry* carry, LnBwdRide* ln) {
   if (n < 1 || n > kMaxGroup) return false;
-  int64_t per_split = 0;
   for (int i = 0; i < n; ++i) {
     const Gemm& m = a[i];
     if (!m.ta || m.tb || !m.c_f32 || m.ldc != m.N || m.epi != EPI_STORE || !gemm_dma_ok(m)) return false;
     if (m.K != a[0].K || m.ws != a[0].ws || m.ws_floats != a[0].ws_floats || !m.ws) return false;
-    per_split += (int64_t)m.M * m.N + m.N;
   }
   const WgradTiling tl = wgrad_tiling(a, n);
-  const int bm = tl.bm, bn = tl.bn, nk = cdiv(a[0].K, tl.bk);
-  int splits = tl.splits;
-  while (splits > 1 && (size_t)(splits * per_split) > a[0].ws_floats) --splits;
+  const int tile = tl.tile, splits = tl.splits, nk = cdiv(a[0].K, 64);
   GroupArgs ga{};
   ga.nprob = n;
   ga.splits = splits;
@@ -923,9 +871,9 @@ bool gemm_wgrad_group(const Gemm* a, int n, hipStream_t st, hipEvent_t mid, Wgra
     ga.colsum[i] = cs;
     ga.slab[i] = splits > 1 ? mn : 0;
     ga.tile0[i] = t0;
-    ga.tiles_n[i] = cdiv(m.N, bn);
+    ga.tiles_n[i] = cdiv(m.N, tile);
     ga.vec_ok[i] = gemm_epilogue_vec_ok(m) && aligned16(cbase) ? 1 : 0;
-    t0 += cdiv(m.M, bm) * cdiv(m.N, bn);
+    t0 += cdiv(m.M, tile) * cdiv(m.N, tile);
     if (splits > 1) ws += splits * (mn + m.N);
   }
   ga.tile0[n] = t0;
@@ -933,7 +881,7 @@ bool gemm_wgrad_group(const Gemm* a, int n, hipStream_t st, hipEvent_t mid, Wgra
   // a carried reduction rides on the workgroups that fit beside this launch's own (one per CU, 256 CUs), in
   // multiples of eight (one per XCD); with fewer than eight to spare it runs on its own first
   int extra = ((256 - own) / 8) * 8;
-  if (extra < 8 || bn != 256) extra = 0;
+  if (extra < 8 || tile != 256) extra = 0;
   const bool host_ln = ln && extra > 0 && ln->D <= 1024 && ln->D % 4 == 0 && ln->rows > 0 && ln->partial;
   if (host_ln) {
     ga.ln = LnBwdArgs<bf16, bf16, bf16>{(const bf16*)ln->dy, ln->lddy, (const bf16*)ln->x, ln->ldx, ln->mean, ln->rstd,
@@ -960,8 +908,8 @@ bool gemm_wgrad_group(const Gemm* a, int n, hipStream_t st, hipEvent_t mid, Wgra
     }
   }
 #define PT_WG(K_, T_) hipLaunchKernelGGL((K_), dim3(own + extra), dim3(T_), 0, st, ga)
-  if (bn == 64) PT_WG((gemm_wgrad_group_small_kernel<64, 3, 64>), 256);
-  else if (bn == 128) PT_WG((gemm_wgrad_group_small_kernel<128, 2, 64>), 256);
+  if (tile == 64) PT_WG((gemm_wgrad_group_small_kernel<64, 3, 64>), 256);
+  else if (tile == 128) PT_WG((gemm_wgrad_group_small_kernel<128, 2, 64>), 256);
   else if (a[0].K % 64 != 0) PT_WG((gemm_wgrad_group_kernel<true>), 512);
   else PT_WG((gemm_wgrad_group_kernel<false>), 512);
 #undef PT_WG

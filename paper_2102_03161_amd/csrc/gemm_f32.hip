@@ -251,20 +251,13 @@ void launch(const Gemm* a, int n, hipStream_t st) {
   else hipLaunchKernelGGL((gemm_f32_kernel<T, TC, false, false, VEC, TM, TN>), grid, dim3(256), 0, st, ga);
 }
 
-// Tile size: the fullest CU's share of 16x16 units, weighted by what a tile size reaches of the matrix rate when it
-// has the CU's four SIMDs to itself.
-template <typename T, typename TC, bool VEC>
-void choose(const Gemm* a, int n, hipStream_t st) {
-  auto cost = [&](int tm, int tn, double weight) {
-    int64_t t = 0;
-    for (int i = 0; i < n; ++i) t += (int64_t)cdiv(a[i].M, 32 * tm) * cdiv(a[i].N, 32 * tn);
-    return (double)((t + 255) / 256) * tm * tn * weight;
-  };
-  const double c11 = cost(1, 1, 1.7), c12 = cost(1, 2, 1.3), c22 = cost(2, 2, 1.1), c44 = cost(4, 4, 1.0);
-  if (c44 <= c22 && c44 <= c12 && c44 <= c11) launch<T, TC, VEC, 4, 4>(a, n, st);
-  else if (c22 <= c12 && c22 <= c11) launch<T, TC, VEC, 2, 2>(a, n, st);
-  else if (c12 <= c11) launch<T, TC, VEC, 1, 2>(a, n, st);
-  else launch<T, TC, VEC, 1, 1>(a, n, st);
+template <bool VEC>
+void choose_f32(const Gemm* a, int n, hipStream_t st) {
+  const F32Tile t = gemm_f32_tile(a, n);
+  if (t.tm == 4) launch<float, float, VEC, 4, 4>(a, n, st);
+  else if (t.tm == 2) launch<float, float, VEC, 2, 2>(a, n, st);
+  else if (t.tn == 2) launch<float, float, VEC, 1, 2>(a, n, st);
+  else launch<float, float, VEC, 1, 1>(a, n, st);
 }
 
 // bf16 operands, widened: two tile sizes, the larger one from two workgroups per CU on (4096 x 768 x 3076 485 us on 32x32
@@ -293,8 +286,8 @@ void gemm_f32(int dt, const Gemm* a, int n, hipStream_t st) {
     while (m < kMaxPlain && i + m < n && a[i + m].ta == a[i].ta && a[i + m].tb == a[i].tb && a[i + m].epi == a[i].epi) ++m;
     bool vec = true;
     for (int j = 0; j < m; ++j) vec = vec && vec_ok(dt, a[i + j]);
-    if (vec) choose<float, float, true>(a + i, m, st);
-    else choose<float, float, false>(a + i, m, st);
+    if (vec) choose_f32<true>(a + i, m, st);
+    else choose_f32<false>(a + i, m, st);
     i += m;
   }
 }

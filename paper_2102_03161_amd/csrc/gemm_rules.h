@@ -110,6 +110,76 @@ inline int gemm_dma_variant(const Gemm& a) {
   return a.K % 64 == 0 && a.tb && t128 > 256 ? 4 : 1;
 }
 
+// A block's weight gradients in one launch of the asynchronous kernels: square tiles (256: the two-group kernel, 64 and 128:
+// the single-role pipeline) and the number of parts that the contraction is cut into, as far as the workspace of the
+// first product has room for their slabs.
+// Microseconds of a launch, fitted to launches over a block's four matrices of widths 256 and 768 with 231 to 12608
+// tokens (within 15 %; k = tokens / 1000, s splits, w workgroups on the fullest CU):
+//   64x64 tiles    the larger of 3.6 + 7.1 k / s (one workgroup's own chain) and w (1.2 + 3.75 k / s)
+//   128x128 tiles  the larger of 4.7 + 12.5 k / s and w (4 + 9.8 k / s)
+//   256x256 tiles  w (10 + 26 k / s)
+// and for s > 1 the slabs' summation at 4 TB/s, also where it rides on another launch (WgradCarry).
+// Width 768: 1379 tokens 34 us on 128x128 tiles against 43 on 64x64 ones, 2639 tokens 58 against 67 on 256x256 ones
+// with two splits (a step of 2 x 2639 tokens, four blocks frozen, 5920 us against 6300), 8192 tokens 131 us on 256x256
+// ones against 164 by the line above on 128x128; width 256: 231 tokens 5.2 us on 64x64 tiles, 2310 tokens 20 against
+// 34 on 128x128 ones.
+struct WgradTiling { int tile, splits; };
+inline WgradTiling wgrad_tiling(const Gemm* a, int n) {
+  const double k = 1e-3 * a[0].K;
+  int64_t floats = 0, per_split = 0;
+  for (int i = 0; i < n; ++i) {
+    floats += (int64_t)a[i].M * a[i].N;
+    per_split += (int64_t)a[i].M * a[i].N + a[i].N;
+  }
+  auto tiles = [&](int b) {
+    int64_t t = 0;
+    for (int i = 0; i < n; ++i) t += (int64_t)((a[i].M + b - 1) / b) * ((a[i].N + b - 1) / b);
+    return t;
+  };
+  WgradTiling best{64, 1};
+  double best_us = 1e30;
+  auto consider = [&](int b, int s, double chain0, double chain, double each0, double each) {
+    const double w = (double)((tiles(b) * s + 255) / 256);
+    double us = std::max(chain0 + chain * k / s, w * (each0 + each * k / s));
+    if (s > 1) us += 4.0 + (s + 1) * floats * 1e-6;
+    if (us < best_us) { best_us = us; best = WgradTiling{b, s}; }
+  };
+  for (int s = 1; s <= 4 && (s == 1 || a[0].K >= 512 * s); s *= 2) {
+    consider(64, s, 3.6, 7.1, 1.2, 3.75);
+    consider(128, s, 4.7, 12.5, 4.0, 9.8);
+  }
+  const int s = (int)std::min<int64_t>(std::min<int64_t>(256 / tiles(256), a[0].K / 256), 16);
+  consider(256, s < 1 ? 1 : s, 10.0, 26.0, 10.0, 26.0);
+  while (best.splits > 1 && (size_t)(best.splits * per_split) > a[0].ws_floats) --best.splits;
+  return best;
+}
+// workspace floats that a block's four weight gradients (D x 3D, D x D, D x F, F x D) may use
+inline size_t gemm_wgrad_batch_ws_floats(int D, int F) {
+  const int64_t shapes[4][2] = {{D, 3 * D}, {D, D}, {D, F}, {F, D}};
+  int64_t tiles = 0, per_split = 0;
+  for (auto& sh : shapes) {
+    tiles += ((sh[0] + 255) / 256) * ((sh[1] + 255) / 256);
+    per_split += sh[0] * sh[1] + sh[1];
+  }
+  const int64_t splits = std::min<int64_t>(16, std::max<int64_t>(1, 256 / std::max<int64_t>(tiles, 1)));
+  return (size_t)(splits * per_split);
+}
+
+// Tiles of a launch on the fp32 matrix instructions, in units of 32 rows and columns: the fullest CU's share of 16x16
+// units, weighted by what a tile size reaches of the matrix rate when it has the CU's four SIMDs to itself.
+struct F32Tile { int tm, tn; };
+inline F32Tile gemm_f32_tile(const Gemm* a, int n) {
+  auto cost = [&](int tm, int tn, double weight) {
+    int64_t t = 0;
+    for (int i = 0; i < n; ++i) t += (int64_t)((a[i].M + 32 * tm - 1) / (32 * tm)) * ((a[i].N + 32 * tn - 1) / (32 * tn));
+    return (double)((t + 255) / 256) * tm * tn * weight;
+  };
+  const double c11 = cost(1, 1, 1.7), c12 = cost(1, 2, 1.3), c22 = cost(2, 2, 1.1), c44 = cost(4, 4, 1.0);
+  if (c44 <= c22 && c44 <= c12 && c44 <= c11) return F32Tile{4, 4};
+  if (c22 <= c12 && c22 <= c11) return F32Tile{2, 2};
+  return F32Tile{1, c12 <= c11 ? 2 : 1};
+}
+
 inline GemmPath gemm_path(int dt, const Gemm& a) {
   if (dt == 0 || !gemm_combo_used(a) || (a.ta && a.ldc != a.N)) return GEMM_F32;   // split-K slabs are dense
   if (gemm_dma_ok(a)) return GEMM_DMA;

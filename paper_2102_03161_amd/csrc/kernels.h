@@ -38,8 +38,6 @@ struct LnBwdRide {
 void gemm_wgrad_batch(int dt, const Gemm* g, int n, hipStream_t st, hipEvent_t mid = nullptr, WgradCarry* carry = nullptr,
                       LnBwdRide* ln = nullptr);
 void gemm_wgrad_flush(WgradCarry* carry, hipStream_t st);
-// workspace floats gemm_wgrad_batch may use for a block's four matrices (D x 3D, D x D, D x F, F x D)
-size_t gemm_wgrad_batch_ws_floats(int D, int F);
 // true when gemm() will run the matrix-core kernel for this problem
 bool gemm_uses_mfma(int dt, const Gemm& g);
 

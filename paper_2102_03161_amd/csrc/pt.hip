@@ -17,6 +17,7 @@
 #include <vector>
 
 #include "kernels.h"
+#include "gemm_rules.h"
 
 using namespace pt;
 

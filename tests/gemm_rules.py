@@ -25,6 +25,25 @@ extern "C" int path(int dt, int M, int N, int K, int ta, int tb, int epi, int c_
   return gemm_path(dt, make(M, N, K, ta, tb, epi, c_f32, 0));
 }
 extern "C" int dma_variant(int M, int N, int K, int tb) { return gemm_dma_variant(make(M, N, K, 0, tb, EPI_STORE, 0, 0)); }
+// a block's four weight gradients with the workspace that the plan gives them at least
+extern "C" int block_wgrads(int D, int F, int tokens) {
+  const size_t ws = gemm_wgrad_batch_ws_floats(D, F);
+  const Gemm g[4] = {make(F, D, tokens, 1, 0, EPI_STORE, 1, ws), make(D, F, tokens, 1, 0, EPI_STORE, 1, ws),
+                     make(D, D, tokens, 1, 0, EPI_STORE, 1, ws), make(D, 3 * D, tokens, 1, 0, EPI_STORE, 1, ws)};
+  const WgradTiling t = wgrad_tiling(g, 4);
+  return t.tile * 100 + t.splits;
+}
+extern "C" int f32_tile(int M, int N, int K, int ta, int tb) {
+  const Gemm g = make(M, N, K, ta, tb, EPI_STORE, 1, 0);
+  const F32Tile t = gemm_f32_tile(&g, 1);
+  return t.tm * 10 + t.tn;
+}
+extern "C" int f32_block_wgrads(int D, int F, int tokens) {
+  const Gemm g[4] = {make(F, D, tokens, 1, 0, EPI_STORE, 1, 0), make(D, F, tokens, 1, 0, EPI_STORE, 1, 0),
+                     make(D, D, tokens, 1, 0, EPI_STORE, 1, 0), make(D, 3 * D, tokens, 1, 0, EPI_STORE, 1, 0)};
+  const F32Tile t = gemm_f32_tile(g, 4);
+  return t.tm * 10 + t.tn;
+}
 extern "C" int reg_tiling(int M, int N, int K, int ta, int epi, int c_f32, long long ws_floats) {
   const GemmRegTiling t = gemm_reg_tiling(make(M, N, K, ta, 0, epi, c_f32, ws_floats));
   return t.tile * 100 + t.splits;
@@ -71,3 +90,18 @@ def reg_tiling(M, N, K, ta, epi=STORE, c_f32=False, ws_floats=0):
     """(tile, splits) of the register-staged kernel"""
     t = lib().reg_tiling(M, N, K, int(ta), epi, int(c_f32), ws_floats)
     return t // 100, t % 100
+
+
+def block_wgrads(D, F, tokens):
+    """(tile, splits) of a block's four weight gradients in bf16 mode"""
+    t = lib().block_wgrads(D, F, tokens)
+    return t // 100, t % 100
+
+
+def f32_tile(M, N, K, tb=False):
+    """tile of an fp32 forward (tb: input-gradient) product, in units of 32"""
+    return divmod(lib().f32_tile(M, N, K, 0, int(tb)), 10)
+
+
+def f32_block_wgrads(D, F, tokens):
+    return divmod(lib().f32_block_wgrads(D, F, tokens), 10)

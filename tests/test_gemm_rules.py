@@ -2,6 +2,9 @@
 import pytest
 
 from tests import gemm_rules as R
+from tests import test_gpu_gemm_tiles as G
+from tests.test_gpu_parity import MANY_TOKENS
+from tests.test_gpu_wgrad_riders import CASE as RIDERS
 
 
 @pytest.mark.parametrize("tokens", [1, 24, 200, 4096, 12288])
@@ -56,3 +59,29 @@ def test_variants_take_the_contractions_they_are_given():
                     v = R.dma_variant(M, N, K, tb)
                     need = {R.T128: 32, R.T256x128: 32, R.TWO_GROUPS_256: 64, R.TWO_GROUPS_192: 64}.get(v, 8)
                     assert K % need == 0, (M, N, K, tb, v)
+
+
+@pytest.mark.parametrize("name", G.CASES)
+def test_gpu_cases_take_the_kernels_they_are_there_for(name):
+    G.takes_its_kernels(name)
+
+
+def test_other_gpu_tests_take_the_weight_gradients_they_are_there_for():
+    w = RIDERS[0]
+    assert R.block_wgrads(w["D"], w["F"], w["B"] * w["S"]) == (256, 3)
+    for D, (B, wgrads, tiles) in MANY_TOKENS.items():
+        assert R.block_wgrads(D, 1728, 65 * B) == wgrads and R.dma_variant(65 * B, 1728, D) == tiles
+    assert R.block_wgrads(768, 3072, 64 * 197) == (256, 2)
+
+
+def test_fp32_tiles():
+    rows = {50: (1, 1), 450: (1, 2), 2000: (2, 2), 4081: (4, 4)}
+    assert {m: R.f32_tile(m, 1024, 768) for m in rows} == rows
+
+
+def test_weight_gradients_are_not_cut_finer_than_their_k_tiles():
+    for D, F in [(64, 256), (200, 800), (256, 1024), (384, 1536), (512, 2048), (768, 3072), (1024, 4096), (2048, 8192)]:
+        for tokens in list(range(1, 600, 7)) + list(range(600, 40000, 131)):
+            tile, splits = R.block_wgrads(D, F, tokens)
+            nk = -(-tokens // 64)
+            assert tile in (64, 128, 256) and 1 <= splits <= 16 and splits <= nk, (D, F, tokens)

@@ -20,15 +20,33 @@ CASES = {
     # 350 tokens at full width: 64-row tiles, 128-wide weight gradients over five and a half k tiles, seven-row products
     # with a split contraction
     "few_rows": (dict(VIT, L=2, D=768, H=12, F=3072, n_out=1000, B=7), 0, 7, 42),
-    # 1078 tokens, narrow matrices: 64-wide weight-gradient tiles with a split contraction
-    "narrow_split": (dict(BERT, L=2, D=256, H=4, F=1024, S=77, max_pos=80, B=14), 0, 14, 43),
-    # 2079 tokens: the two-group weight-gradient kernel with a partial last k tile
-    "group_tail": (dict(BERT, L=2, D=512, H=8, F=2048, S=77, max_pos=80, B=27), 0, 27, 44),
+    # 2156 tokens, narrow matrices: 64-wide weight-gradient tiles, the contraction in four parts
+    "narrow_split": (dict(BERT, L=2, D=256, H=4, F=1024, S=77, max_pos=80, B=28), 0, 28, 43),
+    # 7161 tokens of width 384: 128-wide ones in four parts
+    "medium_split": (dict(BERT, L=1, D=384, H=6, F=1536, S=77, max_pos=80, B=93), 0, 93, 50),
+    # 4851 tokens: the two-group weight-gradient kernel with a partial last k tile, in five parts, whose slabs the next
+    # block's launch adds
+    "group_tail": (dict(BERT, L=2, D=512, H=8, F=2048, S=77, max_pos=80, B=63), 0, 63, 44),
     # 3850 x 800 x 200: 128x128 tiles of eight waves with an eighth of a k tile at the end, forward and backward
     "eight_waves_tail": (dict(BERT, L=1, D=200, H=25, F=800, S=77, max_pos=80, B=50), 0, 50, 49),
     # 2639 x 3072 input gradients: 504 tiles of 128x128, eight waves each
     "eight_waves": (dict(BERT, L=1, D=768, H=12, F=3072, S=203, max_pos=203, B=13), 0, 13, 45),
 }
+
+# what the cases above are there for: the tile and the parts of a block's weight gradients ...
+BLOCK_WGRADS = {"few_rows": (128, 1), "narrow_split": (64, 4), "medium_split": (128, 4), "group_tail": (256, 5)}
+# ... and the tiles of an input gradient, (rows, columns, contraction)
+INPUT_GRADIENT = {"few_rows": ((350, 768, 3072), R.T64), "eight_waves": ((2639, 3072, 768), R.T128_EIGHT_WAVES),
+                  "eight_waves_tail": ((3850, 800, 200), R.T128_EIGHT_WAVES)}
+
+
+def takes_its_kernels(name):
+    w, _, nb, _ = CASES[name]
+    if name in BLOCK_WGRADS:
+        assert R.block_wgrads(w["D"], w["F"], nb * w["S"]) == BLOCK_WGRADS[name]
+    if name in INPUT_GRADIENT:
+        (M, N, K), variant = INPUT_GRADIENT[name]
+        assert R.dma_variant(M, N, K, tb=True) == variant
 
 
 @pytest.fixture(scope="module")
@@ -68,6 +86,7 @@ def prefix_rows(torch, w):
 @pytest.mark.parametrize("name", CASES)
 def test_products_at_tile_edges(torch_mod, name):
     w, k, nb, seed = CASES[name]
+    takes_its_kernels(name)
     check_step(torch_mod, name, w, k, nb, seed)
 
 
@@ -105,21 +124,30 @@ def test_prefix_rows_with_a_k_tail_do_not_depend_on_the_tiles(torch_mod):
     prefix_rows(torch_mod, dict(VIT, L=2, D=200, H=25, F=1000, n_out=10, B=65))
 
 
-@pytest.mark.parametrize("nb,F", [(1, 3072), (9, 3072), (40, 3072), (3, 1028)])
-def test_fp32_products_at_tile_edges(torch_mod, nb, F):
-    """fp32 mode: 50, 450 and 2000 rows take all four tile sizes; ten classes and the widths that are no multiple of
-    the tiles take the element-wise loads and the ragged edges."""
-    w = dict(VIT, L=2, D=768, H=12, F=F, n_out=10, B=nb, dtype="f32")
-    print(f"fp32 tile edges: nb={nb} F={F}", flush=True)
+def check_fp32_step(torch, w, seed):
     ctx = binding.Context(binding.make_config(w))
-    vals = H.init_values(w, ctx, 6)
+    vals = H.init_values(w, ctx, seed)
     H.load_params(ctx, vals)
-    x, y = H.batch_for(w, 6, nb)
-    g = H.gpu_step(torch_mod, ctx, w, x, y, 0)
+    x, y = H.batch_for(w, seed, w["B"])
+    g = H.gpu_step(torch, ctx, w, x, y, 0)
     ctx.close()
     o = H.oracle_step(w, vals, x, y, 0)
     H.oracle_update(w, o, vals, g["grads"], 0)
     H.compare_step(w, g, o, 0, 1e-4, rss=H.summand_rss(w, vals, x, y, 0))
+
+
+@pytest.mark.parametrize("nb,F", [(1, 3072), (9, 3072), (40, 3072), (3, 1028)])
+def test_fp32_products_at_tile_edges(torch_mod, nb, F):
+    """fp32 mode: 50, 450 and 2000 rows take 32x32, 32x64 and 64x64 tiles; ten classes and the widths that are no
+    multiple of the tiles take the element-wise loads and the ragged edges."""
+    print(f"fp32 tile edges: nb={nb} F={F}", flush=True)
+    check_fp32_step(torch_mod, dict(VIT, L=2, D=768, H=12, F=F, n_out=10, B=nb, dtype="f32"), 6)
+
+
+def test_fp32_products_on_the_largest_tiles(torch_mod):
+    """fp32 mode: 4081 x 1024 forward products and input gradients are 256 tiles of 128x128."""
+    assert R.f32_tile(4081, 1024, 256) == R.f32_tile(4081, 1024, 256, tb=True) == (4, 4)
+    check_fp32_step(torch_mod, dict(BERT, L=1, D=256, H=4, F=1024, S=77, max_pos=80, B=53, dtype="f32"), 8)
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])

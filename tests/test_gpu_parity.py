@@ -7,6 +7,7 @@ import pytest
 
 from oracle import encoder as orc
 from paper_2102_03161_amd import binding, synth
+from tests import gemm_rules as R
 from tests import gpu_harness as H
 from tests.helpers import oracle_cfg, rel_err
 
@@ -556,13 +557,19 @@ def test_first_token_rows_with_64_samples(torch_mod, name, dtype):
     run_case(torch_mod, w, 0, w["B"], seed=23, tol=TOL[dtype])
 
 
-def test_many_tokens_with_ragged_widths(torch_mod):
-    """8320 tokens (a multiple of 64) with widths that are no multiple of the 256-column tiles: forward and
-    input-gradient products go through the two-group matrix-core kernels (192- and 256-row tiles, clamped
-    edge tiles in both directions) and the block's weight gradients through the grouped launch with a
-    15-way split over the tokens."""
-    w = dict(arch="vit", L=2, D=128, H=2, F=1728, S=65, n_out=10, img=32, patch=4, chans=3, vocab=0, max_pos=0,
-             ln_eps=1e-6, B=128, optimizer="adamw", dtype="bf16")
+# width: batch, tile and parts of a block's weight gradients, tiles of the first MLP product
+MANY_TOKENS = {128: (128, (64, 4), R.TWO_GROUPS_256), 192: (192, (256, 14), R.TWO_GROUPS_192)}
+
+
+@pytest.mark.parametrize("D", MANY_TOKENS)
+def test_many_tokens_with_ragged_widths(torch_mod, D):
+    """8320 and 12480 tokens (multiples of 64) with widths that are no multiple of the 256-column tiles: wide products
+    go through the two-group matrix-core kernels (256- and 192-row tiles, clamped edge tiles in both directions) and
+    the block's weight gradients through the grouped launches with a deep split over the tokens."""
+    B, wgrads, tiles = MANY_TOKENS[D]
+    assert R.block_wgrads(D, 1728, 65 * B) == wgrads and R.dma_variant(65 * B, 1728, D) == tiles
+    w = dict(arch="vit", L=2, D=D, H=D // 64, F=1728, S=65, n_out=10, img=32, patch=4, chans=3, vocab=0, max_pos=0,
+             ln_eps=1e-6, B=B, optimizer="adamw", dtype="bf16")
     for k in (0, 1):
         run_case(torch_mod, w, k, w["B"], seed=19, tol=TOL["bf16"])
 
