@@ -580,15 +580,9 @@ void attention_fwd_mfma(const void* qkv, void* ctx, float* lse, int nb, int S, i
 void attention_bwd_mfma(const void* qkv, const void* ctx, const void* dctx, const float* lse, void* dqkv, float* delta,
                         int nb, int S, int H, hipStream_t st);
 
-// Bounds the sequence length that the fp32 kernels are offered: a context is accepted while a score matrix of 32
-// queries would fit a CU's LDS beside two operand tiles.  The kernels themselves take any length.
-size_t attention_generic_lds_bytes(int S, int dh) {
-  const size_t Spad = (size_t)cdiv(S, 64) * 64;
-  const size_t fwd = sizeof(float) * ((size_t)32 * dh + (size_t)64 * (dh + 1) + (size_t)32 * Spad + 32);
-  const size_t dq = sizeof(float) * ((size_t)2 * 32 * dh + (size_t)2 * 64 * (dh + 1) + (size_t)32 * 64 + 2 * 32);
-  const size_t dkv = sizeof(float) * ((size_t)4 * 32 * (dh + 1) + (size_t)2 * 32 * 32 + 2 * 32);
-  return std::max(std::max(fwd, dq), dkv);
-}
+// Longest sequence that a context with the fp32 kernels is accepted for.  The kernels stream any length; this is the
+// supported range, the lengths whose scores for 32 queries and operand tiles fit 160 KB together.
+int attention_f32_max_tokens(int dh) { return (1277 - 3 * dh) / 64 * 64; }
 size_t attention_first_query_lds_bytes(int S, int dh) {
   const size_t fwd = sizeof(float) * ((size_t)dh + S + (dh % 8 == 0 ? (size_t)(256 / (dh / 8)) * dh : 0));
   const size_t bwd = sizeof(float) * ((size_t)2 * dh + S);

@@ -46,10 +46,10 @@ void attention_fwd(int dt, const void* qkv, void* ctx, float* lse /*[nb,H,S] or 
                    int dh, hipStream_t st);
 void attention_bwd(int dt, const void* qkv, const void* ctx, const void* dctx, const float* lse, void* dqkv,
                    float* delta_ws /*[nb,H,S]*/, int nb, int S, int H, int dh, hipStream_t st);
-// Bytes that bound the sequence length: for the fp32 kernels (fp32 mode, or a head size other than 64) see the
-// definition, for the first-query kernels the dynamic LDS that they ask for.  The orchestrator rejects
-// configurations above the 160 KB of a CU before anything is launched.
-size_t attention_generic_lds_bytes(int S, int dh);
+// What bounds the sequence length: the supported range of the fp32 kernels (fp32 mode, or a head size other than 64), and
+// the dynamic LDS that the first-query kernels ask for.  The orchestrator rejects configurations beyond either
+// (160 KB a CU) before anything is launched.
+int attention_f32_max_tokens(int dh);
 size_t attention_first_query_lds_bytes(int S, int dh);
 bool attention_uses_mfma(int dt, int dh);
 // the same for each sample's first query only (nothing else of the output is read, or has a gradient):

@@ -90,9 +90,9 @@ bool validate(const pt_config& c, std::string* why) {
   if (!(c.ln_eps >= 0.f)) return bad("ln_eps");
   if (c.k_min < 0 || c.k_min > c.L) return bad("k_min outside 0..L");
   if ((int64_t)c.B * c.S > (1 << 24)) return bad("B*S too large");
-  // sequence length: see attention_generic_lds_bytes; the first-token kernels keep a score row of the sequence in LDS
+  // sequence length: the supported range of the fp32 kernels; the first-token kernels keep a score row of the sequence in LDS
   constexpr size_t kLdsPerCu = 160 * 1024;
-  if (!attention_uses_mfma(c.dtype == PT_BF16 ? 1 : 0, dh) && attention_generic_lds_bytes(c.S, dh) > kLdsPerCu)
+  if (!attention_uses_mfma(c.dtype == PT_BF16 ? 1 : 0, dh) && c.S > attention_f32_max_tokens(dh))
     return bad("sequence too long for the attention kernels of this mode (fp32, or head size other than 64)");
   if (c.S >= 4 && (c.arch == PT_VIT_PRELN || c.head == PT_HEAD_CLS) && attention_first_query_lds_bytes(c.S, dh) > kLdsPerCu)
     return bad("sequence too long for the first-token attention kernels");

@@ -10,7 +10,8 @@ from tests import gpu_harness as H
 pytestmark = pytest.mark.gpu
 
 # (tokens, heads, head size)
-CASES = [(16, 2, 16), (17, 3, 8), (63, 2, 32), (64, 2, 64), (65, 2, 128), (80, 2, 24), (129, 2, 40), (197, 3, 64), (257, 2, 104)]
+CASES = [(16, 2, 16), (17, 3, 8), (63, 2, 32), (64, 2, 64), (65, 2, 128), (80, 2, 24), (129, 2, 40), (197, 3, 64), (257, 2, 104),
+         (1216, 2, 8), (832, 1, 128)]   # the longest sequences of these head sizes
 
 
 @pytest.fixture(scope="module")

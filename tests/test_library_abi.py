@@ -167,9 +167,9 @@ def test_a_frozen_block_costs_a_fraction_of_an_active_one():
 
 
 def test_sequences_too_long_for_the_lds_resident_attention_kernels_are_rejected_up_front():
-    """Without matrix-core attention (fp32 mode, or a head size other than 64) a strip of score rows over the
-    whole sequence lives in LDS, and the first-token kernels keep one score row: configurations that would not
-    fit the 160 KB of a CU are refused by pt_query_arena_bytes / pt_create, before anything is enqueued."""
+    """The kernels on the fp32 matrix instructions (fp32 mode, or a head size other than 64) are offered sequences up to a
+    fixed length, and the first-token kernels keep one score row in LDS: configurations beyond that, or that would not
+    fit the 160 KB of a CU, are refused by pt_query_arena_bytes / pt_create, before anything is enqueued."""
     base = dict(synth.workload("bert_base_qa"), max_pos=1 << 20, vocab=100)
     ok = binding.make_config(dict(base, dtype="f32", S=1024, B=1))
     binding.query_arena_bytes(ok)
@@ -181,3 +181,21 @@ def test_sequences_too_long_for_the_lds_resident_attention_kernels_are_rejected_
         assert e.value.status == binding.PT_EINVAL
     # the matrix-core path streams keys through LDS: long sequences are fine there
     binding.query_arena_bytes(binding.make_config(dict(base, dtype="bf16", S=4096, B=1)))
+
+
+@pytest.mark.parametrize("dtype,dh", [("f32", 8), ("f32", 40), ("f32", 64), ("f32", 128), ("bf16", 8), ("bf16", 72), ("bf16", 120), ("bf16", 128)])
+def test_the_longest_sequence_of_the_fp32_attention_kernels(dtype, dh):
+    """The accepted range is that of the first release: a strip of 32 score rows, padded to 64 keys, and the tiles of
+    queries and keys in 160 KB."""
+    def fits(S):
+        padded = -(-S // 64) * 64
+        return 4 * (32 * dh + 64 * (dh + 1) + 32 * padded + 32) <= 160 * 1024
+    w = dict(synth.workload("bert_base_qa"), max_pos=1 << 20, vocab=100, dtype=dtype, H=4, D=4 * dh, B=1)
+    for S in range(64, 1500, 13):
+        for s in (S, -(-S // 64) * 64, -(-S // 64) * 64 + 1):
+            try:
+                binding.query_arena_bytes(binding.make_config(dict(w, S=s)))
+                accepted = True
+            except binding.PtError:
+                accepted = False
+            assert accepted == fits(s), (dtype, dh, s)
