@@ -1332,11 +1332,6 @@ __global__ __launch_bounds__(512) void attn_bwd_pipe_kernel(const bf16* __restri
 constexpr int g_attn_resident_max_s = 224;
 constexpr int g_attn_resident_max_s_bwd = 512;
 constexpr int g_attn_fused_max_s_bwd = 256;   // four [S,64] images and two float rows in 160 KB, eight waves
-#ifdef PT_TUNING_HOOKS   // stand-alone experiments only; the library is built without it
-int g_attn_bwd_pipe = 1;
-#else
-constexpr int g_attn_bwd_pipe = 1;            // the pipelined fused backward where its six images fit (S <= 208)
-#endif
 struct ResPlan { int ntile, nw, nblk; size_t lds; };
 ResPlan resident_plan(int S, bool with_rows) {
   ResPlan r;
@@ -1365,9 +1360,6 @@ hipError_t allow_lds(K kernel, size_t bytes) {
 
 }  // namespace
 
-#ifdef PT_TUNING_HOOKS
-void attention_set_bwd_pipe(int v) { g_attn_bwd_pipe = v; }
-#endif
 void attention_fwd_mfma(const void* qkv, void* ctx, float* lse, int nb, int S, int H, hipStream_t st) {
   if (S <= g_attn_resident_max_s) {
     const ResPlan r = resident_plan(S, false);
@@ -1392,7 +1384,7 @@ void attention_bwd_mfma(const void* qkv, const void* ctx, const void* dctx, cons
     const size_t lds = (size_t)6 * rows_pad * kImgRowBytes + kImgPadBytes + (size_t)2 * ntile * 32 * sizeof(float);
     const int cus = device_cu_count();
     const int nheads = nb * H;
-    if (g_attn_bwd_pipe && ntile >= 5 && ntile <= 8 && lds <= 160 * 1024 && cus > 0 && nheads > cus &&
+    if (ntile >= 5 && ntile <= 8 && lds <= 160 * 1024 && cus > 0 && nheads > cus &&
         allow_lds(attn_bwd_pipe_kernel, lds) == hipSuccess) {
       hipLaunchKernelGGL(attn_bwd_pipe_kernel, dim3(nheads < cus ? nheads : cus), dim3(64 * ntile), lds, st,
                          (const bf16*)qkv, (const bf16*)ctx, (const bf16*)dctx, lse, (bf16*)dqkv, S, H, ntile, rows_pad,

@@ -91,21 +91,12 @@ bool gemm_epilogue_vec_ok(const Gemm& a) {
 
 bool gemm_uses_mfma(int dt, const Gemm& a) { return gemm_path(dt, a) != GEMM_F32; }
 
-// kernel selection; -1 = choose by problem shape, 10 + v: variant v of gemm_dma (tuning hook for experiments)
-#ifdef PT_TUNING_HOOKS   // stand-alone experiments only; the library is built without it
-static int g_cfg_override = -1;
-void gemm_set_config(int c) { g_cfg_override = c; }
-#else
-constexpr int g_cfg_override = -1;
-#endif
-
 void gemm(int dt, const Gemm& a, hipStream_t st) {
   if (a.M <= 0 || a.N <= 0) return;
   if (a.c_f32 && (a.epi == EPI_BIAS_GELU || a.epi == EPI_MUL_DGELU)) return;  // not used by the step
   const GemmPath path = gemm_path(dt, a);
   if (path == GEMM_REG) { gemm_reg(a, st); return; }
   if (path == GEMM_DMA) {
-    if (g_cfg_override >= 10) { gemm_dma(a, g_cfg_override - 10, st); return; }
     if (!a.ta) {
       if (!gemm_dma_skinny(a, st)) gemm_dma(a, gemm_dma_variant(a), st);
       return;

@@ -684,8 +684,9 @@ __global__ __launch_bounds__(512) void gemm_wgrad_group_kernel(GroupArgs ga) {
 }
 
 // The same with BT x BT tiles of the single-role pipeline, for few tokens or narrow matrices, where the large tiles
-// leave most CUs without work or write split-K slabs that cost more than the products (wgrad_tiling has the line).  Two
-// workgroups per CU hide each other's loads, which bound them (8 KB per 128x64 operand tile at 45-50 GB/s per CU).
+// leave most CUs without work or write split-K slabs that cost more than the products (wgrad_tiling has the line).  What
+// bounds a workgroup is the chain of a k tile, barrier, fragment reads, MFMAs (more stages are slower: 64x64 tiles with
+// five 42.8 -> 49.2 us, 128x128 35.0 -> 36.6); two workgroups per CU hide part of each other's.
 template <int BT, int NS, int BK>
 __global__ __launch_bounds__(256, 2) void gemm_wgrad_group_small_kernel(GroupArgs ga) {
   const int total_tiles = ga.tile0[ga.nprob], total_work = total_tiles * ga.splits;
@@ -727,13 +728,7 @@ __global__ __launch_bounds__(512) void gemm_pp_kernel(GemmDev<bf16> g, SplitArgs
   pp_run<BM, WHOLE, TA, TB, EPI, TC, false>(g, sp, split, kt0, n, m0, n0, vec_ok);
 }
 
-#ifdef PT_TUNING_HOOKS   // stand-alone experiments only; the library is built without it
-int g_group_n = 0;                  // forced column-group width; 0 = derive from g_group_bytes
-int64_t g_group_bytes = 1536 << 10;
-#else
-constexpr int g_group_n = 0;
-constexpr int64_t g_group_bytes = 1536 << 10;  // L2 bytes a column group's B panels may take
-#endif
+constexpr int64_t kGroupBytes = 1536 << 10;  // L2 bytes a column group's B panels may take
 
 template <int BM, int BN, int WGM, int WGN, int NS, int BK, bool TA, bool TB, int EPI, typename TC, bool TAIL = false>
 void launch_dma(const Gemm& a, int splits, float* cbase, int64_t slab, float* colsum_part, hipStream_t st) {
@@ -744,12 +739,9 @@ void launch_dma(const Gemm& a, int splits, float* cbase, int64_t slab, float* co
   SplitArgs sp{splits, cdiv(nk, splits), slab, colsum_part};
   dim3 grid(8 * cdiv(total * splits, 8), 1, 1);
   // column-group width: the B panels of a group (whole K) should fit beside the streaming A panels in a 4 MB L2
-  int group_n = g_group_n;
-  if (group_n <= 0) {
-    const int64_t panel = (int64_t)BN * (a.K / splits) * 2;
-    group_n = (int)(g_group_bytes / (panel > 0 ? panel : 1));
-    if (group_n < 1) group_n = 1;
-  }
+  const int64_t panel = (int64_t)BN * (a.K / splits) * 2;
+  int group_n = (int)(kGroupBytes / (panel > 0 ? panel : 1));
+  if (group_n < 1) group_n = 1;
   if (group_n > tiles_n) group_n = tiles_n;
   hipLaunchKernelGGL((gemm_dma_kernel<BM, BN, WGM, WGN, NS, BK, TA, TB, EPI, TC, TAIL>), grid, dim3(64 * WGM * WGN), 0, st, g, sp,
                      tiles_m, tiles_n, group_n, gemm_epilogue_vec_ok(a) ? 1 : 0);
@@ -764,12 +756,9 @@ void launch_pp(const Gemm& a, int splits, float* cbase, int64_t slab, float* col
   const int nk = a.K / BK;
   SplitArgs sp{splits, cdiv(nk, splits), slab, colsum_part};
   dim3 grid(8 * cdiv(total * splits, 8), 1, 1);
-  int group_n = g_group_n;
-  if (group_n <= 0) {
-    const int64_t panel = (int64_t)BN * (a.K / splits) * 2;
-    group_n = (int)(g_group_bytes / (panel > 0 ? panel : 1));
-    if (group_n < 1) group_n = 1;
-  }
+  const int64_t panel = (int64_t)BN * (a.K / splits) * 2;
+  int group_n = (int)(kGroupBytes / (panel > 0 ? panel : 1));
+  if (group_n < 1) group_n = 1;
   if (group_n > tiles_n) group_n = tiles_n;
   // 192-row tiles leave room for a whole k tile of fragments in registers (whole-tile phases, 4-5 % faster);
   // 256-row tiles do not
@@ -807,16 +796,7 @@ void launch_split_epilogue(const Gemm& a, const float* part, int splits, hipStre
 }  // namespace
 
 // workgroups a split-K weight gradient aims for: two 256x128 workgroups per CU
-#ifdef PT_TUNING_HOOKS
-int g_split_target = 512;
-void gemm_set_split_target(int t) { g_split_target = t; }
-void gemm_set_group(int tiles, long bytes) {
-  g_group_n = tiles;
-  if (bytes > 0) g_group_bytes = bytes;
-}
-#else
-constexpr int g_split_target = 512;
-#endif
+constexpr int kSplitTarget = 512;
 
 // weight gradients (both operands strided in memory: whole cache lines whatever BK): BK = 32, three stages
 template <int BM, int BN, int WGM, int WGN>
@@ -826,7 +806,7 @@ static void dispatch_wgrad(const Gemm& a, hipStream_t st) {
   int splits = 1;
   const int64_t mn = (int64_t)a.M * a.N;
   if (a.ws) {
-    splits = g_split_target / tiles;
+    splits = kSplitTarget / tiles;
     if (splits > nk / 8) splits = nk / 8;
     if (splits > 16) splits = 16;
     if (splits < 1) splits = 1;

@@ -92,8 +92,9 @@ inline int gemm_dma_variant(const Gemm& a) {
       if (tiles * 10 >= cdiv(tiles, 256) * 256 * 6) return v;
     }
   }
-  // Below that, 128x128 or 64x64 tiles.  A workgroup alone on its CU is held to the latency and rate of its own
-  // loads (45-50 GB/s per CU), so what counts is the number of workgroups that the fullest CU gets.  Microseconds
+  // Below that, 128x128 or 64x64 tiles.  A workgroup alone on its CU is held to the chain of each k tile (barrier, fragment
+  // reads, MFMAs; pipelines of four or five stages instead of three gain nothing: 231 x 256 x 1024 8.3, 8.4, 8.4 us), so
+  // what counts is the number of workgroups that the fullest CU gets.  Microseconds
   // fitted to launches of 17 to 8192 rows with N and K of 768 to 3072, within 15 % (k = K / 1000): a 128x128
   // workgroup alone 5.7 + 8.9 k, w of them w (5.3 + 7.0 k); a 64x64 workgroup alone 3.5 + 4.7 k, w of them
   // w (1.9 + 3.05 k).  1379 x 768 x 3072: 66 tiles, 33 us, against 264 small ones, 21 us; 2639 x 3072 x 768: 504
