@@ -100,6 +100,7 @@ struct TileK {
   }
   // fragments of all row blocks for one k-step, issued as inline assembly (see TileS::read)
   static constexpr int READS = NFRAG;   // LDS instructions per k-step
+  template <bool FOLD>
   __device__ __forceinline__ void read(const unsigned char* tile, int ks, bf16x8 (&f)[NFRAG]) const {
     const unsigned addr = lds_addr(tile) + foff[ks];
 #pragma unroll
@@ -173,16 +174,21 @@ struct TileS {
     for (int i = 0; i < LOADS; ++i) issue_one<TAIL>(tile, wave, i, klim);
   }
   static constexpr int READS = 2 * NFRAG;
-  // ks is a compile-time constant at every call site (unrolled), so the offsets fold to immediates
+  // FOLD: the k-step's offset goes into the instruction, which leaves one address register per row block.  With an address
+  // of its own in front of every pair of reads the forward pass through six blocks (ViT-B/16, B = 64) takes 1670 us
+  // instead of 1641; in the weight gradients, where both operands are read this way, the compiler's schedule around fewer
+  // address registers is the slower one (a whole step 0.4 to 0.7 %).
+  template <bool FOLD>
   __device__ __forceinline__ void read(const unsigned char* tile, int ks, bf16x8 (&f)[NFRAG]) const {
     const unsigned base = lds_addr(tile);
 #pragma unroll
     for (int j = 0; j < NFRAG; ++j) {
       union { u32x2 h[2]; bf16x8 v; } t;
-      const unsigned addr = base + foff[j] + 16 * ks * ROWB;
       // k rows 16*ks + 8*half + {0..3} and {4..7}: +4 and +16*ks rows are constant offsets (swz uses bits 0, 1, 3 of k)
-      asm volatile("ds_read_b64_tr_b16 %0, %1" : "=v"(t.h[0]) : "v"(addr));
-      asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(t.h[1]) : "v"(addr), "n"(4 * ROWB));
+      const int imm = FOLD ? 16 * ks * ROWB : 0;
+      const unsigned addr = base + foff[j] + (FOLD ? 0 : 16 * ks * ROWB);
+      asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(t.h[0]) : "v"(addr), "n"(imm));
+      asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(t.h[1]) : "v"(addr), "n"(imm + 4 * ROWB));
       f[j] = t.v;
     }
   }
@@ -325,10 +331,10 @@ __device__ __forceinline__ void dma_run(const GemmDev<bf16>& g, const SplitArgs&
     // MFMAs of k-step s into the set those MFMAs have just consumed, so LDS reads overlap matrix work.
     // LDS operations return in order: "at most RPS outstanding" means the older set has arrived.
     bf16x8 fa[2][TM], fb[2][TN];
-    ta.read(sa, 0, fa[0]);
-    tb.read(sb, 0, fb[0]);
-    ta.read(sa, 1, fa[1]);
-    tb.read(sb, 1, fb[1]);
+    ta.template read<!TA>(sa, 0, fa[0]);
+    tb.template read<!TA>(sb, 0, fb[0]);
+    ta.template read<!TA>(sa, 1, fa[1]);
+    tb.template read<!TA>(sb, 1, fb[1]);
     if (TAIL && more) issue(it + kNS - 1, fill);
     fill = fill + 1 == kNS ? 0 : fill + 1;
 #pragma unroll
@@ -348,8 +354,8 @@ __device__ __forceinline__ void dma_run(const GemmDev<bf16>& g, const SplitArgs&
       // next wait, and every fragment read of the tile is then waited for before the first MFMA issues
       __builtin_amdgcn_sched_barrier(0);
       if (ks + 2 < KS) {
-        ta.read(sa, ks + 2, fa[ks & 1]);
-        tb.read(sb, ks + 2, fb[ks & 1]);
+        ta.template read<!TA>(sa, ks + 2, fa[ks & 1]);
+        tb.template read<!TA>(sb, ks + 2, fb[ks & 1]);
       }
     }
   }
@@ -463,8 +469,8 @@ __device__ __forceinline__ void pp_run(const GemmDev<bf16>& g, const SplitArgs& 
   auto fetch = [&](const unsigned char* sa, const unsigned char* sb, int half) {
 #pragma unroll
     for (int ks = 0; ks < KSF; ++ks) {
-      ta.read(sa, KSF * half + ks, fa[ks]);
-      tb.read(sb, KSF * half + ks, fb[ks]);
+      ta.template read<!TA>(sa, KSF * half + ks, fa[ks]);
+      tb.template read<!TA>(sb, KSF * half + ks, fb[ks]);
     }
   };
   auto fetched = [&]() {
