@@ -65,9 +65,8 @@ inline GemmRegTiling gemm_reg_tiling(const Gemm& a) {
 }
 
 // Variant of the asynchronous kernels, forward and input-gradient products: 1 = 128x128 tiles, 2 = 256x128, 3 = 64x64, 4 =
-// 128x128 with eight waves, 5 / 6 = the two-group kernel with 256 / 192-row tiles.
-// Every variant runs the same matrix instructions in the
-// same k order, so a row's result does not depend on the choice (nor, through it, on the batch size).
+// 128x128 with eight waves, 5 / 6 = the two-group kernel with 256 / 192-row tiles.  Every variant runs the same matrix
+// instructions in the same k order, so a row's result does not depend on the choice (nor, through it, on the batch size).
 inline int gemm_dma_variant(const Gemm& a) {
   auto cdiv = [](int64_t x, int64_t y) { return (x + y - 1) / y; };
   if (a.M >= 4096 && a.K % 64 == 0) {
