@@ -81,14 +81,18 @@ struct TileK {
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) foff[ks] = row * ROWB + (((2 * ks + (lane >> 5)) ^ swzk(row)) << 4);
   }
+  static constexpr bool K_MAJOR = true;
+  static constexpr int KW = BK;
+  // first k of the piece that this lane fetches with load i
+  static __device__ __forceinline__ int load_k(int wave, int i, int lane) {
+    return 8 * ((lane % CPR) ^ swzk(RPL * (wave * LOADS + i) + lane / CPR));
+  }
   // klim (TAIL only): k values of this tile that exist, a multiple of 8
   template <bool TAIL = false>
   __device__ __forceinline__ void issue_one(unsigned char* tile, int wave, int i, int klim = BK) {
     const bf16* src = gp[i];
     if (TAIL) {
-      const int lane = threadIdx.x & 63;
-      const int c = (lane % CPR) ^ swzk(RPL * (wave * LOADS + i) + lane / CPR);
-      if (8 * c >= klim) src = reinterpret_cast<const bf16*>(g_zeros);
+      if (load_k(wave, i, threadIdx.x & 63) >= klim) src = reinterpret_cast<const bf16*>(g_zeros);
     }
     __builtin_amdgcn_global_load_lds(PT_GLB(src), PT_LDS(tile + (wave * LOADS + i) * 1024), 16, 0, 0);
     gp[i] += BK;
@@ -102,10 +106,15 @@ struct TileK {
   static constexpr int READS = NFRAG;   // LDS instructions per k-step
   template <bool FOLD>
   __device__ __forceinline__ void read(const unsigned char* tile, int ks, bf16x8 (&f)[NFRAG]) const {
-    const unsigned addr = lds_addr(tile) + foff[ks];
+    read_at<FOLD, 0>(lds_addr(tile), ks, f);
+  }
+  // OFF: part of the tile's LDS address that goes into the instructions
+  template <bool FOLD, int OFF>
+  __device__ __forceinline__ void read_at(unsigned base, int ks, bf16x8 (&f)[NFRAG]) const {
+    const unsigned addr = base + foff[ks];
 #pragma unroll
     for (int i = 0; i < NFRAG; ++i)
-      asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(f[i]) : "v"(addr), "n"(i * 32 * ROWB));
+      asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(f[i]) : "v"(addr), "n"(OFF + i * 32 * ROWB));
   }
 };
 
@@ -158,12 +167,14 @@ struct TileS {
       foff[j] = k * ROWB + (((col >> 3) ^ swz<ROWS>(k)) << 4) + (col & 7) * 2;
     }
   }
+  static constexpr bool K_MAJOR = false;
+  static constexpr int KW = BK;
+  static __device__ __forceinline__ int load_k(int wave, int i, int lane) { return KPL * (wave * LOADS + i) + lane / CPR; }
   template <bool TAIL = false>
   __device__ __forceinline__ void issue_one(unsigned char* tile, int wave, int i, int klim = BK) {
     const bf16* src = gp[i];
     if (TAIL) {
-      const int lane = threadIdx.x & 63;
-      if (KPL * (wave * LOADS + i) + lane / CPR >= klim) src = reinterpret_cast<const bf16*>(g_zeros);
+      if (load_k(wave, i, threadIdx.x & 63) >= klim) src = reinterpret_cast<const bf16*>(g_zeros);
     }
     __builtin_amdgcn_global_load_lds(PT_GLB(src), PT_LDS(tile + (wave * LOADS + i) * 1024), 16, 0, 0);
     gp[i] += gstep;
@@ -180,12 +191,15 @@ struct TileS {
   // address registers is the slower one (a whole step 0.4 to 0.7 %).
   template <bool FOLD>
   __device__ __forceinline__ void read(const unsigned char* tile, int ks, bf16x8 (&f)[NFRAG]) const {
-    const unsigned base = lds_addr(tile);
+    read_at<FOLD, 0>(lds_addr(tile), ks, f);
+  }
+  template <bool FOLD, int OFF>
+  __device__ __forceinline__ void read_at(unsigned base, int ks, bf16x8 (&f)[NFRAG]) const {
 #pragma unroll
     for (int j = 0; j < NFRAG; ++j) {
       union { u32x2 h[2]; bf16x8 v; } t;
       // k rows 16*ks + 8*half + {0..3} and {4..7}: +4 and +16*ks rows are constant offsets (swz uses bits 0, 1, 3 of k)
-      const int imm = FOLD ? 16 * ks * ROWB : 0;
+      const int imm = OFF + (FOLD ? 16 * ks * ROWB : 0);
       const unsigned addr = base + foff[j] + (FOLD ? 0 : 16 * ks * ROWB);
       asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(t.h[0]) : "v"(addr), "n"(imm));
       asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(t.h[1]) : "v"(addr), "n"(imm + 4 * ROWB));
@@ -373,6 +387,181 @@ __device__ __forceinline__ void dma_run(const GemmDev<bf16>& g, const SplitArgs&
                                                    m0 + wm * WTM, n0 + wn * WTN, lane, vec_ok);
 }
 
+// ---- the same pipeline with few instructions per k tile, for tiles of 64 columns and small weight gradients ----
+// A wave of a 64x64 tile has four MFMAs in a k tile and spent 88 instructions on it, at five to eight cycles each where it
+// is alone on its SIMD.  Here a tile's source is one pointer per wave, with 32-bit lane offsets that never change, the loop
+// has a copy of its body per stage, so that LDS addresses are immediates, and whole k tiles and a last partial one go
+// separate ways: 54 instructions.  231 x 256 x 1024 7.7 -> 5.5 us, 77 x 768 x 3072 16.5 -> 13.3, 1379 x 2304 x 768 16.8 ->
+// 14.4; weight gradients of width 768 over 2639 tokens 62.3 -> 58.4.  Tiles of 128 columns and more gain up to 6 % alone and
+// lose up to 1 % of a whole step, launches around them included (BERT-base classification 6710 -> 6785 us): they keep
+// dma_run and pp_run.
+// Fragments read one whole k tile ahead into a second register set (which takes the LDS latency out of a tile's chain)
+// were slower: 1344 x 768 x 3072 13.1 -> 14.4 us.
+template <typename L>
+struct LeanTile {
+  L tile;                     // fragment offsets; its pointers are dead after setup
+  unsigned voff[L::LOADS];    // this lane's sources within a tile, bytes
+  const char* src;            // first byte of the tile that is loaded next
+  int64_t step;
+  __device__ __forceinline__ void setup(const bf16* p, int64_t ld, int R, int r0, int k0, unsigned lds0, int rbase, int wave, int lane) {
+    tile.setup(p, ld, R, r0, k0, rbase, wave, lane);
+    src = reinterpret_cast<const char*>(p + (L::K_MAJOR ? r0 * ld + k0 : k0 * ld + r0));
+    step = L::K_MAJOR ? L::KW * 2 : L::KW * ld * 2;
+#pragma unroll
+    for (int i = 0; i < L::LOADS; ++i) voff[i] = (unsigned)(reinterpret_cast<const char*>(tile.gp[i]) - src);   // below 2^31: gemm_dma_ok
+    for (auto& f : tile.foff) f += lds0;
+  }
+  // klim (TAIL only): k values of the tile that exist; lanes whose k lies past them fetch zeros
+  template <bool TAIL>
+  __device__ __forceinline__ void issue(unsigned char* to, int wave, int klim) {
+#pragma unroll
+    for (int i = 0; i < L::LOADS; ++i) {
+      const char* from = src + voff[i];
+      if (TAIL && L::load_k(wave, i, threadIdx.x & 63) >= klim) from = reinterpret_cast<const char*>(g_zeros);
+      __builtin_amdgcn_global_load_lds(PT_GLB(from), PT_LDS(to + (wave * L::LOADS + i) * 1024), 16, 0, 0);
+    }
+    src += step;
+  }
+};
+template <int BM, int BN, int WGM, int WGN, int kNS, int BK, bool TA, bool TB, int EPI, typename TC, bool TAIL>
+__device__ __forceinline__ void lean_run(const GemmDev<bf16>& g, const SplitArgs& sp, int split, int kt0, int n, int m0, int n0,
+                                         int vec_ok) {
+  constexpr int NW = WGM * WGN;
+  constexpr int WTM = BM / WGM, WTN = BN / WGN, TM = WTM / 32, TN = WTN / 32;
+  typedef typename TileSel<TA, BM, NW, TM, BK>::type LA;
+  typedef typename TileSel<!TB, BN, NW, TN, BK>::type LB;
+  constexpr int KS = BK / 16;
+  constexpr int STAGE = LA::BYTES + LB::BYTES;
+  constexpr int STAGE_LD = WTN + 4;
+  constexpr int EPI_BYTES = NW * 32 * STAGE_LD * 4;
+  constexpr int LDS_BYTES = kNS * STAGE > EPI_BYTES ? kNS * STAGE : EPI_BYTES;
+  constexpr int LPT = LA::LOADS + LB::LOADS;
+  constexpr int RPS = LA::READS + LB::READS;
+  static_assert(LPT * (kNS - 2) < 64, "vmcnt is a 6-bit counter");
+  static_assert(RPS <= 15, "lgkmcnt is a 4-bit counter");
+  static_assert(kNS >= 2 && kNS <= 4 && (kNS - 1) * STAGE < 56 * 1024, "a stage is a 16-bit offset in the reads");
+  static_assert(LDS_BYTES <= 160 * 1024, "stages must fit the LDS");
+  __shared__ __attribute__((aligned(1024))) unsigned char lds[LDS_BYTES];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wm = wave / WGN, wn = wave % WGN;
+
+  f32x16 acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+
+  const bool do_colsum = __builtin_amdgcn_readfirstlane(TA && !TB && sp.colsum != nullptr && m0 == 0 && wm == 0 ? 1 : 0) != 0;
+  ColSum<TN> cs;
+
+  LeanTile<LA> ta;
+  LeanTile<LB> tb;
+  ta.setup(g.A, g.lda, g.M, m0, kt0 * BK, lds_addr(lds), wm * WTM, wave, lane);
+  tb.setup(g.B, g.ldb, g.N, n0, kt0 * BK, lds_addr(lds) + LA::BYTES, wn * WTN, wave, lane);
+  // the k tiles that exist in full; behind them there may be one of klim k values (TAIL only)
+  const int klim = TAIL ? g.K - (kt0 + n - 1) * BK : BK;
+  const int nfull = TAIL && klim < BK ? n - 1 : n;
+  auto issue = [&](auto tail, int stage) {
+    ta.template issue<decltype(tail)::value>(lds + stage * STAGE, wave, klim);
+    tb.template issue<decltype(tail)::value>(lds + stage * STAGE + LA::BYTES, wave, klim);
+  };
+  const std::false_type full;
+  const std::bool_constant<TAIL> partial;
+#pragma unroll
+  for (int s = 0; s < kNS - 1; ++s) {
+    if (s < nfull) issue(full, s);
+    else if (TAIL && s < n) issue(partial, s);
+  }
+
+  // One tile, whose stage lies OFF (or `base`, where the stage is not known at compile time) bytes into the LDS; `next` requests
+  // the tile kNS - 1 further on.
+  // Two fragment sets in registers.  The reads of k-steps 0 and 1 are issued up front; the MFMAs of a k-step start as
+  // soon as its fragments are in, and the reads of k-step s+2 are issued behind the MFMAs of k-step s into the set those
+  // MFMAs have just consumed, so LDS reads overlap matrix work.  LDS operations return in order: "at most RPS
+  // outstanding" means the older set has arrived.
+  auto tile = [&](auto colsum, auto off, unsigned base, auto next) {
+    constexpr int OFF = decltype(off)::value;
+    bf16x8 fa[2][TM], fb[2][TN];
+    if (!TAIL) next();
+    ta.tile.template read_at<!TA, OFF>(base, 0, fa[0]);
+    tb.tile.template read_at<!TA, OFF>(base, 0, fb[0]);
+    ta.tile.template read_at<!TA, OFF>(base, 1, fa[1]);
+    tb.tile.template read_at<!TA, OFF>(base, 1, fb[1]);
+    if (TAIL) next();
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      if (ks + 1 < KS) wait_lds<RPS>(fa[ks & 1], fb[ks & 1]);
+      else wait_lds<0>(fa[ks & 1], fb[ks & 1]);
+#pragma unroll
+      for (int i = 0; i < TM; ++i) {
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[ks & 1][i], fb[ks & 1][j], acc[i][j], 0, 0, 0);
+        if constexpr (decltype(colsum)::value) cs.add(fb[ks & 1], 4 * i / TM, 4 * (i + 1) / TM);
+      }
+      // nothing may be scheduled across this point: without it the compiler sinks the MFMAs above below the
+      // next wait, and every fragment read of the tile is then waited for before the first MFMA issues
+      __builtin_amdgcn_sched_barrier(0);
+      if (ks + 2 < KS) {
+        ta.tile.template read_at<!TA, OFF>(base, ks + 2, fa[ks & 1]);
+        tb.tile.template read_at<!TA, OFF>(base, ks + 2, fb[ks & 1]);
+      }
+    }
+  };
+  auto barrier = [&]() {
+    compiler_fence();
+    __builtin_amdgcn_s_barrier();   // everybody's loads of the tile have landed, and the tile before it is fully consumed
+    compiler_fence();
+  };
+  auto run = [&](auto colsum) {
+    int t = 0, cur = 0;   // the tile that is next and its stage
+    // While there is a full tile to request: one copy of the body per stage, so that a stage's offset is part of the read
+    // instructions.
+    auto steady = [&](auto stage) {
+      constexpr int S = decltype(stage)::value;
+      wait_vm<(kNS - 2) * LPT>();   // this wave's loads of tile t have landed
+      barrier();
+      tile(colsum, std::integral_constant<int, S * STAGE>(), 0, [&]() { issue(full, (S + kNS - 1) % kNS); });
+      cur = (S + 1) % kNS;
+      return ++t < nfull - (kNS - 1);
+    };
+    if (nfull > kNS - 1) {
+      for (;;) {
+        if (!steady(std::integral_constant<int, 0>())) break;
+        if (!steady(std::integral_constant<int, 1>())) break;
+        if constexpr (kNS >= 3) { if (!steady(std::integral_constant<int, 2>())) break; }
+        if constexpr (kNS >= 4) { if (!steady(std::integral_constant<int, 3>())) break; }
+      }
+    }
+    for (; t < n; ++t) {
+      if (kNS >= 4 && t + 2 < n) wait_vm<(kNS >= 4 ? 2 : 0) * LPT>();
+      else if (kNS >= 3 && t + 1 < n) wait_vm<LPT>();
+      else wait_vm<0>();
+      barrier();
+      tile(colsum, std::integral_constant<int, 0>(), cur * STAGE, [&]() {
+        if (TAIL && t + kNS - 1 == n - 1 && nfull < n) issue(partial, cur == 0 ? kNS - 1 : cur - 1);
+      });
+      cur = cur + 1 == kNS ? 0 : cur + 1;
+    }
+  };
+  // the columns' sums in a copy of the loop of their own
+  if (do_colsum) run(std::bool_constant<TA && !TB>());
+  else run(std::false_type());
+  compiler_fence();
+  __builtin_amdgcn_s_barrier();   // all fragment reads done: the LDS can be reused for the epilogue
+  compiler_fence();
+  if constexpr (TA && !TB) {
+    if (do_colsum) cs.store(sp.colsum + (int64_t)split * g.N + n0 + wn * WTN, g.N - n0 - wn * WTN, lane);
+  }
+  void* Cbase = sizeof(TC) == 4 ? (void*)(reinterpret_cast<float*>(g.C) + split * sp.slab)
+                                : (void*)(reinterpret_cast<bf16*>(g.C) + split * sp.slab);
+  constexpr int NBUF = (EPI == EPI_MUL_DGELU || dma_waves_per_simd((BM + BN) * BK * 2 * kNS, NW) < 4) ? 2 : 1;
+  staged_epilogue<TM, TN, WTM, WTN, EPI, TC, NBUF>(g, Cbase, acc, reinterpret_cast<float*>(lds) + wave * 32 * STAGE_LD,
+                                                   m0 + wm * WTM, n0 + wn * WTN, lane, vec_ok);
+}
+
 // Workgroups are dealt to the 8 XCDs round-robin by their index, and each XCD has an L2 of its own.  The
 // index is remapped so that one XCD works through a contiguous range of the sequence
 //   for split: for column group (group_n tile columns): for tile row: for tile column in the group
@@ -394,7 +583,8 @@ void gemm_dma_kernel(GemmDev<bf16> g, SplitArgs sp, int tiles_m, int tiles_n, in
   const int nk_all = TAIL ? (g.K + BK - 1) / BK : g.K / BK;
   const int kt0 = split * sp.tiles_per_split;
   const int kt1 = (kt0 + sp.tiles_per_split < nk_all) ? kt0 + sp.tiles_per_split : nk_all;
-  dma_run<BM, BN, WGM, WGN, kNS, BK, TA, TB, EPI, TC, TAIL>(g, sp, split, kt0, kt1 > kt0 ? kt1 - kt0 : 0, m0, n0, vec_ok);
+  if constexpr (BN == 64) lean_run<BM, BN, WGM, WGN, kNS, BK, TA, TB, EPI, TC, TAIL>(g, sp, split, kt0, kt1 > kt0 ? kt1 - kt0 : 0, m0, n0, vec_ok);
+  else dma_run<BM, BN, WGM, WGN, kNS, BK, TA, TB, EPI, TC, TAIL>(g, sp, split, kt0, kt1 > kt0 ? kt1 - kt0 : 0, m0, n0, vec_ok);
 }
 
 // ---- 256x256x64 (or 192x256x64) tiles, two wave groups in alternating roles ----
@@ -708,8 +898,8 @@ __global__ __launch_bounds__(256, 2) void gemm_wgrad_group_small_kernel(GroupArg
   const int nk_all = (ga.g[p].K + BK - 1) / BK;
   const int kt0 = split * ga.tiles_per_split;
   const int kt1 = (kt0 + ga.tiles_per_split < nk_all) ? kt0 + ga.tiles_per_split : nk_all;
-  dma_run<BT, BT, 2, 2, NS, BK, true, false, EPI_STORE, float, true>(ga.g[p], sp, split, kt0, kt1 > kt0 ? kt1 - kt0 : 0,
-                                                                         (local / ga.tiles_n[p]) * BT, (local % ga.tiles_n[p]) * BT, ga.vec_ok[p]);
+  lean_run<BT, BT, 2, 2, NS, BK, true, false, EPI_STORE, float, true>(ga.g[p], sp, split, kt0, kt1 > kt0 ? kt1 - kt0 : 0,
+                                                                      (local / ga.tiles_n[p]) * BT, (local % ga.tiles_n[p]) * BT, ga.vec_ok[p]);
 }
 
 // Workgroups are dealt to the 8 XCDs round-robin by their index; the index is remapped so that one XCD works
@@ -992,7 +1182,7 @@ bool gemm_dma_skinny(const Gemm& a, hipStream_t st) {
 
 void gemm_dma(const Gemm& a, int variant, hipStream_t st) {
   // variants: 1 = 128x128 tiles (K a multiple of 32), 2 = 256x128 (of 32), 3 = 64x64 (any K), 4 = 128x128 with eight waves
-  // (any K), 5 / 6 = the two-group kernel with 256 / 192-row tiles (K a multiple of 64)
+  // (any K), 5 / 6 = the two-group kernel with 256 / 192-row tiles, 7 = 128x64 (K a multiple of 64)
   if (a.ta) {   // a single weight gradient with a long contraction (a block's four go through gemm_wgrad_group)
     if (variant == 1) dispatch_wgrad<128, 128, 2, 2>(a, st);
     else dispatch_wgrad<256, 128, 4, 2>(a, st);
@@ -1009,7 +1199,14 @@ void gemm_dma(const Gemm& a, int variant, hipStream_t st) {
       if (a.K % 64 == 0) dispatch_fwd<128, 128, 4, 2, 2, 64>(a, st);
       else dispatch_fwd<128, 128, 4, 2, 2, 64, true>(a, st);
       break;
-    default: dispatch_fwd<64, 64, 2, 2, 3, 64, true>(a, st); break;
+    case 7: dispatch_fwd<128, 64, 4, 2, 3, 64>(a, st); break;
+    default:
+      // One workgroup on a CU has three tiles in flight instead of two: 1344 x 768 x 3072 15.4 -> 13.1 us, 231 x 768 x 3072
+      // 13.4 -> 11.1, 900 x 1024 x 1024 6.6 -> 6.0; with more than one the third workgroup that fits beside 48 KB counts
+      // for more (1379 x 3072 x 768 17.7 -> 19.6), and a short K has nothing to hide (231 x 256 x 256 3.7 -> 3.9).
+      if ((int64_t)cdiv(a.M, 64) * cdiv(a.N, 64) <= 256 && a.K >= 512) dispatch_fwd<64, 64, 2, 2, 4, 64, true>(a, st);
+      else dispatch_fwd<64, 64, 2, 2, 3, 64, true>(a, st);
+      break;
   }
 }
 

@@ -26,6 +26,7 @@ inline bool gemm_combo_used(const Gemm& a) {
 // what the asynchronous kernels need: 16-byte pieces of every operand
 inline bool gemm_dma_ok(const Gemm& a) {
   if (!aligned_to(a.A, 16) || !aligned_to(a.B, 16) || a.lda % 8 || a.ldb % 8 || a.K < 1) return false;
+  if (a.lda >= (1 << 23) || a.ldb >= (1 << 23)) return false;   // 128 rows lie within 2^31 bytes: 32-bit offsets
   if (a.ta && (a.M % 8 || a.M < 8)) return false;      // strided operands: 16-byte pieces along the rows
   if (!a.tb && (a.N % 8 || a.N < 8)) return false;
   return (a.ta && !a.tb) || a.K % 8 == 0;              // a k-major operand: 16-byte pieces along k
@@ -65,10 +66,11 @@ inline GemmRegTiling gemm_reg_tiling(const Gemm& a) {
 }
 
 // Variant of the asynchronous kernels, forward and input-gradient products: 1 = 128x128 tiles, 2 = 256x128, 3 = 64x64, 4 =
-// 128x128 with eight waves, 5 / 6 = the two-group kernel with 256 / 192-row tiles.  Every variant runs the same matrix
+// 128x128 with eight waves, 5 / 6 = the two-group kernel with 256 / 192-row tiles, 7 = 128x64.  Every variant runs the same matrix
 // instructions in the same k order, so a row's result does not depend on the choice (nor, through it, on the batch size).
 inline int gemm_dma_variant(const Gemm& a) {
   auto cdiv = [](int64_t x, int64_t y) { return (x + y - 1) / y; };
+  int pp = 0;   // the two-group kernel whose tiles fill the CUs well
   if (a.M >= 4096 && a.K % 64 == 0) {
     // At least 4096 rows: the two-group kernel with 256x256 or 192x256 tiles, one workgroup per CU, whichever
     // fills whole rounds of 256 CUs better (M = 12608, N = 768: 198 tiles of 192x256 against 150 of 256x256).
@@ -80,34 +82,64 @@ inline int gemm_dma_variant(const Gemm& a) {
       // of five rounds: 169 us against 183 with GELU, 149 against 164 with the saved GELU'); otherwise from 9000
       // rows on 256x128 tiles, two workgroups per CU, whose prologues and epilogues overlap.
       const int64_t last = t192 % 256;
-      if (last == 0 || last >= 224) return 6;
-      if (t256 * 10 >= cdiv(t256, 256) * 256 * 9) return 5;
-      if (a.M >= 9000) return 2;
+      if (last == 0 || last >= 224) pp = 6;
+      else if (t256 * 10 >= cdiv(t256, 256) * 256 * 9) pp = 5;
+      else if (a.M >= 9000) return 2;
     } else {
       const int v = cdiv(t192, 256) * 192 < cdiv(t256, 256) * 256 ? 6 : 5;
       // fewer tiles than 60 % of the CUs of their rounds (8192 tokens at N = 768: 129 tiles): smaller tiles fill the
       // chip better (6-13 % faster on those five products)
       const int64_t tiles = v == 6 ? t192 : t256;
-      if (tiles * 10 >= cdiv(tiles, 256) * 256 * 6) return v;
+      if (tiles * 10 >= cdiv(tiles, 256) * 256 * 6) pp = v;
     }
+    if (pp && (a.M > 12288 || a.K < 256)) return pp;   // beyond what the cost lines below were fitted to
   }
-  // Below that, 128x128 or 64x64 tiles.  A workgroup alone on its CU is held to the chain of each k tile (barrier, fragment
-  // reads, MFMAs; pipelines of four or five stages instead of three gain nothing: 231 x 256 x 1024 8.3, 8.4, 8.4 us), so
-  // what counts is the number of workgroups that the fullest CU gets.  Microseconds
-  // fitted to launches of 17 to 8192 rows with N and K of 768 to 3072, within 15 % (k = K / 1000): a 128x128
-  // workgroup alone 5.7 + 8.9 k, w of them w (5.3 + 7.0 k); a 64x64 workgroup alone 3.5 + 4.7 k, w of them
-  // w (1.9 + 3.05 k).  1379 x 768 x 3072: 66 tiles, 33 us, against 264 small ones, 21 us; 2639 x 3072 x 768: 504
-  // tiles, 24 us, against 2016 small ones, 30 us.
+  // Below that, 64x64, 128x64 or 128x128 tiles.  What bounds them is the way of the operands into LDS: the CU that gets the
+  // most tiles brings in (rows + columns) * K of each, at 20 to 30 bytes per clock, and all CUs together share what the L2s
+  // get from the memory side (loads alone take 20 of the 20.5 us of 1379 x 768 x 3072 on 64x64 tiles, and 14 when they
+  // all hit the L2).
+  const double k = 1e-3 * a.K;
   const int64_t t128 = cdiv(a.M, 128) * cdiv(a.N, 128), t64 = cdiv(a.M, 64) * cdiv(a.N, 64);
-  const double w128 = (double)((t128 + 255) / 256), w64 = (double)((t64 + 255) / 256), k = 1e-3 * a.K;
-  const double us128 = w128 > 1 ? w128 * (5.3 + 7.0 * k) : 5.7 + 8.9 * k;
-  const double us64 = w64 > 1 ? w64 * (1.9 + 3.05 * k) : 3.5 + 4.7 * k;
-  if (us64 <= us128) return 3;
-  // K no multiple of 32: only eight waves on 64-wide k tiles take it (16384 x 1152 x 4304 228 us against 349 on 64x64 tiles
-  // and 235 on four waves with 32-wide ones; input gradients 254, 346, 273; 8192 x 3072 x 776 65, 98, 74)
-  if (a.K % 32) return 4;
-  // eight waves and whole-line loads where both operands are k-major and CUs hold two tiles: 5-10 % faster
-  return a.K % 64 == 0 && a.tb && t128 > 256 ? 4 : 1;
+  if (a.K % 64) {
+    // Microseconds fitted to launches of 17 to 8192 rows with N and K of 768 to 3072, within 15 % (k = K / 1000): a 128x128
+    // workgroup alone 5.7 + 8.9 k, w of them w (5.3 + 7.0 k); a 64x64 workgroup alone 3.5 + 4.7 k, w of them w (1.9 + 3.05 k).
+    const double w128 = (double)((t128 + 255) / 256), w64 = (double)((t64 + 255) / 256);
+    const double us128 = w128 > 1 ? w128 * (5.3 + 7.0 * k) : 5.7 + 8.9 * k;
+    const double us64 = w64 > 1 ? w64 * (1.9 + 3.05 * k) : 3.5 + 4.7 * k;
+    if (us64 <= us128) return 3;
+    // K no multiple of 32: only eight waves on 64-wide k tiles take it (16384 x 1152 x 4304 228 us against 349 on 64x64
+    // tiles and 235 on four waves with 32-wide ones; input gradients 254, 346, 273; 8192 x 3072 x 776 65, 98, 74)
+    return a.K % 32 ? 4 : 1;
+  }
+  // Microseconds fitted to launches of 77 to 10400 rows with N and K of 256 to 4096, within 10 to 12 % (w: tiles on the
+  // fullest CU).  1379 x 768 x 3072: 264 tiles of 64x64, 20.5 us, against 132 of 128x64, 18.0; 2639 x 768 x 3072 23.5 against
+  // 19.5; 2639 x 3072 x 768 24.3 on 128x128 tiles against 25.6; 520 x 1024 x 4096 14.3 on 64x64 tiles against 20.9 on 128x64.
+  // Over these launches the choice is 1.3 % off the fastest tile on average; with the two lines above it was 2.9 %.
+  auto cost = [&](int bm, int bn, double one0, double one, double more0, double more, double load, double store) {
+    const int64_t t = cdiv(a.M, bm) * cdiv(a.N, bn);
+    return one0 + one * k + (double)(cdiv(t, 256) - 1) * (more0 + more * k) + load * 1e-8 * (double)t * (bm + bn) * a.K +
+           store * 1e-6 * (double)a.M * a.N;
+  };
+  const double us64 = cost(64, 64, 3.07, 2.35, 0.1, 2.53, 2.69, 0.35), us128x64 = cost(128, 64, 3.33, 3.73, 0.7, 3.84, 3.64, 0.24);
+  const double us128 = cost(128, 128, 4.24, 6.78, 2.09, 5.52, 7.24, 0.0);
+  // eight waves and whole-line loads where both operands are k-major: 5-10 % faster where CUs hold two tiles
+  const double us128x8 = a.tb ? cost(128, 128, 3.17, 8.44, 1.96, 4.15, 5.69, 0.22) : 1e30;
+  struct Choice { int variant; double us; };
+  const Choice small[4] = {{3, us64}, {7, us128x64}, {1, us128}, {4, us128x8}};
+  Choice best = small[0];
+  for (const Choice& c : small) if (c.us < best.us) best = c;
+  if (a.M >= 4096) {
+    // 5300 x 1536 x 384 21.7 us on 192x256 tiles, which fill 66 % of two rounds, against 17.1 on 128x128 ones; 5300 x 4096 x
+    // 1024 (input gradient) 75.6 on 128x128 tiles against 63.9.  The lines are a few per cent off, so tiles that fill the CUs
+    // well, and 128x128 ones (8192 x 768 x 3072 58.6 us, on 128x64 ones 61), have the benefit of the doubt.
+    const double us256 = cost(256, 256, 5.74, 19.28, 12.33, 11.44, 3.69, 0.71), us192 = cost(192, 256, 5.98, 14.2, 19.37, 0.0, 7.65, 0.24);
+    if (pp) return 0.93 * (pp == 5 ? us256 : us192) <= best.us ? pp : best.variant;
+    if (us256 < best.us) best = Choice{5, us256};
+    if (us192 < best.us) best = Choice{6, us192};
+    const Choice square = us128x8 < us128 ? small[3] : small[2];
+    if (0.85 * square.us <= best.us) best = square;
+  }
+  return best.variant;
 }
 
 // A block's weight gradients in one launch of the asynchronous kernels: square tiles (256: the two-group kernel, 64 and 128:

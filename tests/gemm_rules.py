@@ -78,7 +78,7 @@ def weight_gradient(rows, cols, tokens, dt=1):
 
 
 # variants of the asynchronous kernels
-T128, T256x128, T64, T128_EIGHT_WAVES, TWO_GROUPS_256, TWO_GROUPS_192 = 1, 2, 3, 4, 5, 6
+T128, T256x128, T64, T128_EIGHT_WAVES, TWO_GROUPS_256, TWO_GROUPS_192, T128x64 = 1, 2, 3, 4, 5, 6, 7
 
 
 def dma_variant(M, N, K, tb=False):

@@ -90,6 +90,30 @@ def test_products_at_tile_edges(torch_mod, name):
     check_step(torch_mod, name, w, k, nb, seed)
 
 
+# 64-column tiles: (rows, columns, contraction) of an input gradient and its tiles
+NARROW_CASES = {
+    # 128x64 tiles with 79 rows in the last one; 128-wide weight-gradient tiles with a partial k tile
+    "narrow": (dict(BERT, L=1, D=768, H=12, F=3072, S=203, max_pos=203, B=13), 51, (2639, 768, 3072), R.T128x64),
+    # 64x64 tiles, one to a CU, four stages: 520 = 8 k tiles and an eighth
+    "four_stages_tail": (dict(BERT, L=2, D=256, H=4, F=520, S=77, max_pos=80, B=6), 52, (462, 256, 520), R.T64),
+    # three stages: 392 = 6 k tiles and an eighth
+    "three_stages_tail": (dict(BERT, L=2, D=256, H=4, F=392, S=77, max_pos=80, B=6), 53, (462, 256, 392), R.T64),
+}
+
+
+@pytest.mark.parametrize("name", NARROW_CASES)
+def test_64_column_tiles(torch_mod, name):
+    w, seed, (M, N, K), variant = NARROW_CASES[name]
+    assert w["B"] * w["S"] == M and R.dma_variant(M, N, K, tb=True) == variant
+    check_step(torch_mod, name, w, 0, w["B"], seed)
+
+
+def test_prefix_rows_do_not_depend_on_128x64_tiles(torch_mod):
+    """3250 rows of width 1024 take 128x64 tiles in the second MLP product, 350 and 50 rows 64x64 ones."""
+    assert [R.dma_variant(50 * nb, 1024, 4096) for nb in (65, 7, 1)] == [R.T128x64, R.T64, R.T64]
+    prefix_rows(torch_mod, dict(VIT, L=2, D=1024, H=16, F=4096, n_out=10, B=65))
+
+
 # rows that are even but no multiple of 8 elements long
 EVEN_CASES = {
     # patches of 588 values, 1028-wide MLP, 100 classes: register-staged 64x64 tiles, split contractions with a k tail
