@@ -18,8 +18,10 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fvisibility=hi
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 # Per-file additions.  The attention kernels keep long-lived MFMA accumulators next to short-lived score tiles;
 # with the default AGPR form of the MFMA result the compiler shuttles the long-lived ones between register
-# files every iteration, so these kernels are built with MFMA results in ordinary VGPRs.
-EXTRA_FLAGS = {"attention_mfma.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
+# files every iteration, so these kernels are built with MFMA results in ordinary VGPRs; so are the fp32 products, whose
+# k loop had 24 such moves beside 32 MFMAs.
+EXTRA_FLAGS = {"attention_mfma.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
+               "gemm_f32.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
 
 
 def _hipcc() -> str:

@@ -4,14 +4,15 @@
 // counts); those operands are widened to fp32 on their way into LDS.
 //
 // What bounds it: the fp32 matrix rate (64 FLOP per clock and SIMD, 157 TFLOP/s on the chip) is a sixteenth of the
-// bf16 one, so a 64x64 tile needs 38 GB/s of operands per CU where its load path carries 90 to 113; registers as
-// staging and one k tile of lead are enough, and what counts is how evenly the 16x16 units of work fall on the
-// 1024 SIMDs.  Four tile sizes serve that.  Operands lie in LDS as they lie in memory: an operand whose k runs
-// contiguously as [row][BK + 4], read 16 bytes (four k) at a time, one whose rows run contiguously as
-// [k][rows + 4], read one float at a time; both paddings are conflict-free for the sixteen-row fragments.
+// bf16 one, so what counts is how evenly the 16x16 units of work fall on the 1024 SIMDs, and that a wave alone on its SIMD
+// never waits between two halves of a k tile.  Five tile sizes serve the first (gemm_f32_tile).  gemm_f32_dma_kernel serves
+// the second; it takes fp32 operands whose rows are 16-byte pieces.  The kernel that stages tiles through registers takes
+// everything else: the operands lie in LDS as they lie in memory, an operand whose k runs contiguously as [row][BK + 4],
+// read 16 bytes (four k) at a time, one whose rows run contiguously as [k][rows + 4], read one float at a time; both
+// paddings are conflict-free for the sixteen-row fragments.
 //
-// MFMA number j of group q multiplies the k values 16 q + 4 g + j, g = 0..3: the same order for every layout and
-// tile size, so that a row's result depends on neither.
+// MFMA number j of group q multiplies the k values 16 q + 4 g + j, g = 0..3: the same order for every kernel, layout and
+// tile size, so that a row's result depends on none of them.
 #include <type_traits>
 
 #include "common.h"
@@ -40,6 +41,7 @@ struct PlainProb {
   float* colsum;              // column sums of B over k (strided B only), or null
   int64_t lda, ldb, ldc, ld_aux;
   int M, N, K, tile0, tiles_n;
+  int vec;                    // fp32 results and what the epilogue reads: 16-byte pieces
 };
 struct PlainArgs {
   PlainProb p[kMaxPlain];
@@ -132,6 +134,34 @@ struct PlainColSum {
   }
 };
 
+// stores a wave's TM x TN units, whose first row and column are row0 and col0
+template <typename T, typename TC, int TM, int TN>
+__device__ __forceinline__ void f32_epilogue(const PlainProb& p, int epi_, int row0, int col0, int lane, const f32x4 (&acc)[TM][TN]) {
+  // accumulator layout of the 16x16 MFMA: lane holds column lane % 16, rows 4 (lane / 16) + v
+  const GemmDev<T> g{reinterpret_cast<const T*>(p.A), reinterpret_cast<const T*>(p.B), p.C, p.M, p.N, p.K, p.lda, p.ldb, p.ldc,
+                     reinterpret_cast<const T*>(p.bias), reinterpret_cast<const T*>(p.aux), reinterpret_cast<T*>(p.aux_out), p.ld_aux};
+  auto finish = [&](auto epi) {
+    constexpr int EPI = decltype(epi)::value;
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int row = row0 + i * 16 + 4 * (lane >> 4) + v, col = col0 + j * 16 + (lane & 15);
+          if (row < p.M && col < p.N) epilogue_store<T, TC, EPI>(g, row, col, acc[i][j][v]);
+        }
+  };
+  switch (epi_) {
+    case EPI_STORE: finish(std::integral_constant<int, EPI_STORE>()); break;
+    case EPI_BIAS: finish(std::integral_constant<int, EPI_BIAS>()); break;
+    case EPI_BIAS_RES: finish(std::integral_constant<int, EPI_BIAS_RES>()); break;
+    case EPI_BIAS_GELU: finish(std::integral_constant<int, EPI_BIAS_GELU>()); break;
+    case EPI_MUL_DGELU: finish(std::integral_constant<int, EPI_MUL_DGELU>()); break;
+    default: finish(std::integral_constant<int, EPI_RES>()); break;
+  }
+}
+
 // Tiles of 32 TM x 32 TN, four waves in two rows of two, each TM x TN units of 16x16.  Up to four problems in one
 // launch; workgroups go to the XCDs round-robin, and each XCD takes a contiguous run of tiles.
 template <typename T, typename TC, bool TA, bool TB, bool VEC, int TM, int TN>
@@ -199,22 +229,155 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(PlainArgs ga) {
   if constexpr (TA) {
     if (do_colsum) cs.store(p.colsum + n0 + wn * 16 * TN, p.N - n0 - wn * 16 * TN, lane);
   }
-  // accumulator layout of the 16x16 MFMA: lane holds column lane % 16, rows 4 (lane / 16) + v
-  const GemmDev<T> g{A, B, p.C, p.M, p.N, p.K, p.lda, p.ldb, p.ldc, reinterpret_cast<const T*>(p.bias),
-                     reinterpret_cast<const T*>(p.aux), reinterpret_cast<T*>(p.aux_out), p.ld_aux};
+  f32_epilogue<T, TC, TM, TN>(p, ga.epi, m0 + wm * 16 * TM, n0 + wn * 16 * TN, lane, acc);
+}
+
+// ---- fp32 operands with 16-byte pieces: the same products through an asynchronous pipeline ----
+// Operand tiles of 32 k values travel from global memory straight into LDS, three of them deep.  A k tile has two halves of
+// 16 k; a half's MFMAs (512 clocks of a SIMD for 64x64 tiles) run while the next half's fragments are read into the other of
+// two register sets, and the one barrier of a tile stands in front of its second half's MFMAs, where no wave has to wait for
+// LDS.  Staged through registers, every tile had its LDS writes, barrier and fragment reads in a row in front of its MFMAs:
+// 1576 x 768 x 3072 113 -> 89 us (83 TFLOP/s; 32x32 tiles), 231 x 768 x 3072 51 -> 27, 1576 x 2304 x 768 75 -> 65, 4081 x 1024 x
+// 4096 362 -> 295 (116 TFLOP/s); a block's weight gradients at width 1024 over 1576 tokens 454 -> 380, at width 256 51 -> 36.
+// Two or four tiles deep are the same within 3 %.
+#define PT_LDS(p) ((__attribute__((address_space(3))) void*)(p))
+#define PT_GLB(p) ((const __attribute__((address_space(1))) void*)(p))
+// what lanes past the end of the contraction fetch
+__device__ __attribute__((aligned(64))) const unsigned int f32_zeros[16] = {};
+
+template <int N>
+__device__ __forceinline__ void wait_vm() { __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14)); }
+
+// One operand tile.  k contiguous in memory: LDS image [ROWS][32], 128 bytes a row, 16-byte chunk c of row r in slot
+// c ^ (r / 2 % 8); rows contiguous: image [32][ROWS], chunk c of row k in slot (c + 4 (k / 4 % 4)) mod (ROWS / 4), which
+// keeps the four k groups of a fragment in different banks (two by two for 32 rows).
+template <bool STRIDED, int ROWS>
+struct DmaTile {
+  static constexpr int LOADS = ROWS / 32, BYTES = ROWS * 128, UNITS = ROWS / 32;   // wave-wide loads per wave; 16-row units per wave
+  static constexpr int CPR = STRIDED ? ROWS / 4 : 8;
+  unsigned voff[LOADS];            // this lane's sources within a tile, bytes
+  unsigned foff[STRIDED ? UNITS : 2];
+  const char* src;                 // first byte of the tile that is loaded next
+  int64_t step;
+  static __device__ __forceinline__ int line(int wave, int i, int lane) { return (64 * (wave * LOADS + i) + lane) / CPR; }
+  static __device__ __forceinline__ int chunk(int wave, int i, int lane) {
+    const int slot = (64 * (wave * LOADS + i) + lane) % CPR, l = line(wave, i, lane);
+    return STRIDED ? (slot + CPR - (4 * ((l >> 2) & 3)) % CPR) % CPR : slot ^ ((l >> 1) & 7);
+  }
+  static __device__ __forceinline__ int load_k(int wave, int i, int lane) {   // first k of the piece that this lane fetches
+    return STRIDED ? line(wave, i, lane) : 4 * chunk(wave, i, lane);
+  }
+  // rows past the end are clamped to the last one (of a strided operand, to the last four): they feed outputs that are not stored
+  __device__ __forceinline__ void setup(const float* p, int64_t ld, int R, int r0, unsigned lds0, int rbase, int wave, int lane) {
+#pragma unroll
+    for (int i = 0; i < LOADS; ++i) {
+      int r = STRIDED ? 4 * chunk(wave, i, lane) : line(wave, i, lane);
+      const int k = load_k(wave, i, lane), last = R - (STRIDED ? 4 : 1) - r0;
+      r = r < last ? r : last;
+      voff[i] = 4u * (STRIDED ? (unsigned)k * (unsigned)ld + r : (unsigned)r * (unsigned)ld + k);
+    }
+    src = reinterpret_cast<const char*>(p + (STRIDED ? r0 : r0 * ld));
+    step = STRIDED ? 128 * ld : 128;
+    const int g = lane >> 4, l = lane & 15;
+    if constexpr (STRIDED) {
+#pragma unroll
+      for (int i = 0; i < UNITS; ++i) {
+        const int r = rbase + 16 * i + l;
+        foff[i] = lds0 + 4 * g * ROWS * 4 + (((r >> 2) + 4 * g) % CPR) * 16 + (r & 3) * 4;
+      }
+    } else {
+      const int r = rbase + l;
+#pragma unroll
+      for (int q = 0; q < 2; ++q) foff[q] = lds0 + r * 128 + (((4 * q + g) ^ ((r >> 1) & 7)) << 4);
+    }
+  }
+  template <bool TAIL>
+  __device__ __forceinline__ void issue(unsigned char* to, int wave, int klim) {
+#pragma unroll
+    for (int i = 0; i < LOADS; ++i) {
+      const char* from = src + voff[i];
+      if (TAIL && load_k(wave, i, threadIdx.x & 63) >= klim) from = reinterpret_cast<const char*>(f32_zeros);
+      __builtin_amdgcn_global_load_lds(PT_GLB(from), PT_LDS(to + (wave * LOADS + i) * 1024), 16, 0, 0);
+    }
+    src += step;
+  }
+  // The k values 16 q + 4 g + j of every unit's rows, j = 0..3.  Inline assembly, because the compiler would wait for every
+  // load into LDS in front of a read; the values are there behind arrived(), and nothing moves them before.
+  struct Frag {
+    typename std::conditional<STRIDED, float[4], f32x4>::type f[UNITS];
+    __device__ __forceinline__ float at(int i, int j) const { return f[i][j]; }
+    __device__ __forceinline__ void arrived() {
+#pragma unroll
+      for (int i = 0; i < UNITS; ++i) {
+        if constexpr (STRIDED) {
+#pragma unroll
+          for (int j = 0; j < 4; ++j) asm volatile("" : "+v"(f[i][j]));
+        } else {
+          asm volatile("" : "+v"(f[i]));
+        }
+      }
+    }
+  };
+  __device__ __forceinline__ void read(unsigned stage, int q, Frag& to) const {
+#pragma unroll
+    for (int i = 0; i < UNITS; ++i) {
+      if constexpr (STRIDED) {
+        const unsigned a = stage + foff[i];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) asm volatile("ds_read_b32 %0, %1 offset:%2" : "=v"(to.f[i][j]) : "v"(a), "n"((16 * q + j) * ROWS * 4));
+      } else {
+        const unsigned a = stage + foff[q];
+        asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(to.f[i]) : "v"(a), "n"(i * 16 * 128));
+      }
+    }
+  }
+};
+
+// Stores a wave's TM x TN units, whose first row and column are row0 and col0.  The matrix instructions got the operands the
+// other way round, so a lane holds four neighbouring columns 4 (lane / 16) + v of row lane % 16 and moves 16 bytes at a
+// time; one element at a time, 4081 x 3072 x 768 with GELU takes 231 us and 1576 x 3072 x 768 94.  vec: sizes and
+// alignment allow it.
+template <int TM, int TN>
+__device__ __forceinline__ void f32_store(const PlainProb& p, int epi_, bool vec, int row0, int col0, int lane, const f32x4 (&acc)[TM][TN]) {
+  const GemmDev<float> g{reinterpret_cast<const float*>(p.A), reinterpret_cast<const float*>(p.B), p.C, p.M, p.N, p.K, p.lda, p.ldb, p.ldc,
+                         reinterpret_cast<const float*>(p.bias), reinterpret_cast<const float*>(p.aux), reinterpret_cast<float*>(p.aux_out), p.ld_aux};
   auto finish = [&](auto epi) {
     constexpr int EPI = decltype(epi)::value;
+    constexpr bool BIAS = EPI == EPI_BIAS || EPI == EPI_BIAS_RES || EPI == EPI_BIAS_GELU;
+    constexpr bool AUX = EPI == EPI_BIAS_RES || EPI == EPI_RES || EPI == EPI_MUL_DGELU;
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
-      for (int j = 0; j < TN; ++j)
+      for (int j = 0; j < TN; ++j) {
+        const int row = row0 + i * 16 + (lane & 15), col = col0 + j * 16 + 4 * (lane >> 4);
+        if (row >= p.M || col >= p.N) continue;
+        if (vec) {   // N is a multiple of four
+          f32x4 v = acc[i][j];
+          if (BIAS) {
+            const f32x4 b = load4(g.bias + col);
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const int row = m0 + (wm * TM + i) * 16 + 4 * (lane >> 4) + v, col = n0 + (wn * TN + j) * 16 + (lane & 15);
-          if (row < p.M && col < p.N) epilogue_store<T, TC, EPI>(g, row, col, acc[i][j][v]);
+            for (int e = 0; e < 4; ++e) v[e] += b[e];
+          }
+          if (AUX) {
+            const f32x4 x = load4(g.aux + (int64_t)row * g.ld_aux + col);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = EPI == EPI_MUL_DGELU ? v[e] * x[e] : v[e] + x[e];
+          }
+          if (EPI == EPI_BIAS_GELU) {
+            f32x4 dg;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) { float d; v[e] = gelu_both(v[e], &d); dg[e] = d; }
+            if (g.aux_out) *reinterpret_cast<f32x4*>(g.aux_out + (int64_t)row * g.ld_aux + col) = dg;
+          }
+          *reinterpret_cast<f32x4*>(reinterpret_cast<float*>(g.C) + (int64_t)row * g.ldc + col) = v;
+        } else {
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (col + e < p.N) epilogue_store<float, float, EPI>(g, row, col + e, acc[i][j][e]);
         }
+      }
   };
-  switch (ga.epi) {
+  switch (epi_) {
     case EPI_STORE: finish(std::integral_constant<int, EPI_STORE>()); break;
     case EPI_BIAS: finish(std::integral_constant<int, EPI_BIAS>()); break;
     case EPI_BIAS_RES: finish(std::integral_constant<int, EPI_BIAS_RES>()); break;
@@ -224,6 +387,120 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(PlainArgs ga) {
   }
 }
 
+// The same tiles, waves and order of k as gemm_f32_kernel.
+template <bool TA, bool TB, int TM, int TN, int NS>
+__global__ __launch_bounds__(256) void gemm_f32_dma_kernel(PlainArgs ga) {
+  constexpr int BM = 32 * TM, BN = 32 * TN;
+  typedef DmaTile<TA, BM> LA;
+  typedef DmaTile<!TB, BN> LB;
+  constexpr int STAGE = LA::BYTES + LB::BYTES, LPT = LA::LOADS + LB::LOADS;
+  static_assert(NS >= 2 && NS <= 4 && NS * STAGE <= 160 * 1024 && LPT * (NS - 1) < 64, "LDS and vmcnt");
+  __shared__ __attribute__((aligned(1024))) unsigned char lds[NS * STAGE];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wm = wave >> 1, wn = wave & 1;
+  const int per = (ga.total + 7) >> 3;
+  const int work = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
+  if (work >= ga.total) return;
+  int pi = 0;
+  while (pi + 1 < ga.nprob && work >= ga.p[pi + 1].tile0) ++pi;
+  const PlainProb& p = ga.p[pi];
+  const int local = work - p.tile0;
+  const int m0 = (local / p.tiles_n) * BM, n0 = (local % p.tiles_n) * BN;
+
+  f32x4 acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const bool do_colsum = __builtin_amdgcn_readfirstlane(TA && p.colsum != nullptr && m0 == 0 && wm == 0 ? 1 : 0) != 0;
+  PlainColSum<TN> cs;
+
+  const int n = (p.K + kPlainBK - 1) / kPlainBK, klim = p.K - (n - 1) * kPlainBK;
+  const unsigned lds0 = (unsigned)(size_t)((__attribute__((address_space(3))) const void*)lds);
+  LA ta;
+  LB tb;
+  ta.setup(reinterpret_cast<const float*>(p.A), p.lda, p.M, m0, lds0, wm * 16 * TM, wave, lane);
+  tb.setup(reinterpret_cast<const float*>(p.B), p.ldb, p.N, n0, lds0 + LA::BYTES, wn * 16 * TN, wave, lane);
+  auto issue = [&](int t, int stage) {
+    unsigned char* const to = lds + stage * STAGE;
+    if (t == n - 1 && klim < kPlainBK) {
+      ta.template issue<true>(to, wave, klim);
+      tb.template issue<true>(to + LA::BYTES, wave, klim);
+    } else {
+      ta.template issue<false>(to, wave, kPlainBK);
+      tb.template issue<false>(to + LA::BYTES, wave, kPlainBK);
+    }
+  };
+  // at most the loads of the `later` youngest tiles are pending
+  auto landed = [&](int later) {
+    if (NS >= 4 && later >= 3) wait_vm<(NS >= 4 ? 3 : 0) * LPT>();
+    else if (NS >= 3 && later >= 2) wait_vm<(NS >= 3 ? 2 : 0) * LPT>();
+    else if (later >= 1) wait_vm<LPT>();
+    else wait_vm<0>();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+  };
+  typename LA::Frag fa[2];
+  typename LB::Frag fb[2];
+  auto read = [&](int stage, int q) {
+    ta.read(stage * STAGE, q, fa[q]);
+    tb.read(stage * STAGE, q, fb[q]);
+  };
+  auto arrived = [&](int q) {
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    fa[q].arrived();
+    fb[q].arrived();
+  };
+  auto half = [&](auto colsum, int q) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[q].at(j, e), fa[q].at(i, e), acc[i][j], 0, 0, 0);
+    if constexpr (decltype(colsum)::value) {
+      f32x4 b[TN];
+#pragma unroll
+      for (int j = 0; j < TN; ++j) b[j] = f32x4{fb[q].at(j, 0), fb[q].at(j, 1), fb[q].at(j, 2), fb[q].at(j, 3)};
+      cs.add(b);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto run = [&](auto colsum) {
+#pragma unroll
+    for (int s = 0; s < NS; ++s)
+      if (s < n) issue(s, s);
+    landed(n - 1 < NS - 1 ? n - 1 : NS - 1);
+    read(0, 0);
+    arrived(0);
+    int cur = 0;
+    for (int t = 0; t < n; ++t) {
+      const int nxt = cur + 1 == NS ? 0 : cur + 1;
+      read(cur, 1);
+      __builtin_amdgcn_sched_barrier(0);
+      half(colsum, 0);
+      arrived(1);
+      // this wave is done with tile t's stage; behind the barrier everybody is, and tile t + 1 has landed
+      const int later = n - 2 - t;
+      landed(later < NS - 2 ? later : NS - 2);
+      if (t + NS < n) issue(t + NS, cur);
+      read(nxt, 0);   // behind the last tile: stale, nothing multiplies it
+      __builtin_amdgcn_sched_barrier(0);
+      half(colsum, 1);
+      arrived(0);
+      if constexpr (decltype(colsum)::value) cs.fold(t);
+      cur = nxt;
+    }
+  };
+  if (do_colsum) run(std::bool_constant<TA>());
+  else run(std::false_type());
+  if constexpr (TA) {
+    if (do_colsum) cs.store(p.colsum + n0 + wn * 16 * TN, p.N - n0 - wn * 16 * TN, lane);
+  }
+  f32_store<TM, TN>(p, ga.epi, p.vec != 0, m0 + wm * 16 * TM, n0 + wn * 16 * TN, lane, acc);
+}
+
 // pieces of four elements along the contiguous index
 bool vec_ok(int dt, const Gemm& a) {
   const size_t bytes = dt == 0 ? 16 : 8;
@@ -231,33 +508,59 @@ bool vec_ok(int dt, const Gemm& a) {
          (a.tb ? a.K : a.N) % 4 == 0;
 }
 
-template <typename T, typename TC, bool VEC, int TM, int TN>
-void launch(const Gemm* a, int n, hipStream_t st) {
+bool f32_out_vec_ok(const Gemm& m) {
+  return m.N % 4 == 0 && m.ldc % 4 == 0 && aligned_to(m.C, 16) && (!m.bias || aligned_to(m.bias, 16)) &&
+         ((!m.aux && !m.aux_out) || (m.ld_aux % 4 == 0 && aligned_to(m.aux, 16) && aligned_to(m.aux_out, 16)));
+}
+
+PlainArgs plain_args(const Gemm* a, int n, int bm, int bn) {
   PlainArgs ga{};
   int t0 = 0;
   for (int i = 0; i < n; ++i) {
     const Gemm& m = a[i];
-    const int tiles_n = cdiv(m.N, 32 * TN);
+    const int tiles_n = cdiv(m.N, bn);
     ga.p[i] = PlainProb{m.A, m.B, m.C, m.bias, m.aux, m.aux_out, m.colsum_out, m.lda, m.ldb, m.ldc, m.ld_aux,
-                        m.M, m.N, m.K, t0, tiles_n};
-    t0 += cdiv(m.M, 32 * TM) * tiles_n;
+                        m.M, m.N, m.K, t0, tiles_n, f32_out_vec_ok(m) ? 1 : 0};
+    t0 += cdiv(m.M, bm) * tiles_n;
   }
   ga.nprob = n;
   ga.total = t0;
   ga.epi = a[0].epi;
-  const dim3 grid(8 * cdiv(t0, 8));
+  return ga;
+}
+
+template <typename T, typename TC, bool VEC, int TM, int TN>
+void launch(const Gemm* a, int n, hipStream_t st) {
+  const PlainArgs ga = plain_args(a, n, 32 * TM, 32 * TN);
+  const dim3 grid(8 * cdiv(ga.total, 8));
   if (a[0].ta) hipLaunchKernelGGL((gemm_f32_kernel<T, TC, true, false, VEC, TM, TN>), grid, dim3(256), 0, st, ga);
   else if (a[0].tb) hipLaunchKernelGGL((gemm_f32_kernel<T, TC, false, true, VEC, TM, TN>), grid, dim3(256), 0, st, ga);
   else hipLaunchKernelGGL((gemm_f32_kernel<T, TC, false, false, VEC, TM, TN>), grid, dim3(256), 0, st, ga);
 }
 
-template <bool VEC>
-void choose_f32(const Gemm* a, int n, hipStream_t st) {
+template <int TM, int TN, int NS>
+void launch_dma(const Gemm* a, int n, hipStream_t st) {
+  const PlainArgs ga = plain_args(a, n, 32 * TM, 32 * TN);
+  const dim3 grid(8 * cdiv(ga.total, 8));
+  if (a[0].ta) hipLaunchKernelGGL((gemm_f32_dma_kernel<true, false, TM, TN, NS>), grid, dim3(256), 0, st, ga);
+  else if (a[0].tb) hipLaunchKernelGGL((gemm_f32_dma_kernel<false, true, TM, TN, NS>), grid, dim3(256), 0, st, ga);
+  else hipLaunchKernelGGL((gemm_f32_dma_kernel<false, false, TM, TN, NS>), grid, dim3(256), 0, st, ga);
+}
+
+void choose_f32(const Gemm* a, int n, bool vec, hipStream_t st) {
   const F32Tile t = gemm_f32_tile(a, n);
-  if (t.tm == 4) launch<float, float, VEC, 4, 4>(a, n, st);
-  else if (t.tm == 2) launch<float, float, VEC, 2, 2>(a, n, st);
-  else if (t.tn == 2) launch<float, float, VEC, 1, 2>(a, n, st);
-  else launch<float, float, VEC, 1, 1>(a, n, st);
+  if (vec) {
+    if (t.tm == 4) launch_dma<4, 4, 3>(a, n, st);
+    else if (t.tn == 3) launch_dma<2, 3, 3>(a, n, st);
+    else if (t.tm == 2) launch_dma<2, 2, 3>(a, n, st);
+    else if (t.tn == 2) launch_dma<1, 2, 3>(a, n, st);
+    else launch_dma<1, 1, 3>(a, n, st);
+    return;
+  }
+  if (t.tm == 4) launch<float, float, false, 4, 4>(a, n, st);
+  else if (t.tm == 2) launch<float, float, false, 2, 2>(a, n, st);
+  else if (t.tn == 2) launch<float, float, false, 1, 2>(a, n, st);
+  else launch<float, float, false, 1, 1>(a, n, st);
 }
 
 // bf16 operands, widened: two tile sizes, the larger one from two workgroups per CU on (4096 x 768 x 3076 485 us on 32x32
@@ -285,9 +588,8 @@ void gemm_f32(int dt, const Gemm* a, int n, hipStream_t st) {
     int m = 1;   // products of one layout and epilogue over the same contraction share a launch
     while (m < kMaxPlain && i + m < n && a[i + m].ta == a[i].ta && a[i + m].tb == a[i].tb && a[i + m].epi == a[i].epi) ++m;
     bool vec = true;
-    for (int j = 0; j < m; ++j) vec = vec && vec_ok(dt, a[i + j]);
-    if (vec) choose_f32<true>(a + i, m, st);
-    else choose_f32<false>(a + i, m, st);
+    for (int j = 0; j < m; ++j) vec = vec && vec_ok(dt, a[i + j]) && a[i + j].K >= 1 && a[i + j].lda < (1 << 22) && a[i + j].ldb < (1 << 22);   // 128 rows within 2^31 bytes
+    choose_f32(a + i, m, vec, st);
     i += m;
   }
 }
