@@ -237,9 +237,10 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(PlainArgs ga) {
 // 16 k; a half's MFMAs (512 clocks of a SIMD for 64x64 tiles) run while the next half's fragments are read into the other of
 // two register sets, and the one barrier of a tile stands in front of its second half's MFMAs, where no wave has to wait for
 // LDS.  Staged through registers, every tile had its LDS writes, barrier and fragment reads in a row in front of its MFMAs:
-// 1576 x 768 x 3072 113 -> 89 us (83 TFLOP/s; 32x32 tiles), 231 x 768 x 3072 51 -> 27, 1576 x 2304 x 768 75 -> 65, 4081 x 1024 x
-// 4096 362 -> 295 (116 TFLOP/s); a block's weight gradients at width 1024 over 1576 tokens 454 -> 380, at width 256 51 -> 36.
-// Two or four tiles deep are the same within 3 %.
+// 1576 x 768 x 3072 112 -> 87 us (86 TFLOP/s; 32x32 tiles), 231 x 768 x 3072 51 -> 27, 1576 x 2304 x 768 74 -> 64, 4081 x 1024 x
+// 4096 354 -> 279 (123 TFLOP/s); a block's weight gradients at width 1024 over 1576 tokens 453 -> 384, at width 256 50 -> 35.
+// With the reads in front of a half's MFMAs instead of between them the larger tiles are 5 to 7 % slower (4081 x 1024 x 4096
+// 295); two or four tiles deep are the same within 3 %.
 #define PT_LDS(p) ((__attribute__((address_space(3))) void*)(p))
 #define PT_GLB(p) ((const __attribute__((address_space(1))) void*)(p))
 // what lanes past the end of the contraction fetch
@@ -318,17 +319,14 @@ struct DmaTile {
       }
     }
   };
-  __device__ __forceinline__ void read(unsigned stage, int q, Frag& to) const {
+  __device__ __forceinline__ void read(unsigned stage, int q, int i, Frag& to) const {   // unit i
+    if constexpr (STRIDED) {
+      const unsigned a = stage + foff[i];
 #pragma unroll
-    for (int i = 0; i < UNITS; ++i) {
-      if constexpr (STRIDED) {
-        const unsigned a = stage + foff[i];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) asm volatile("ds_read_b32 %0, %1 offset:%2" : "=v"(to.f[i][j]) : "v"(a), "n"((16 * q + j) * ROWS * 4));
-      } else {
-        const unsigned a = stage + foff[q];
-        asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(to.f[i]) : "v"(a), "n"(i * 16 * 128));
-      }
+      for (int j = 0; j < 4; ++j) asm volatile("ds_read_b32 %0, %1 offset:%2" : "=v"(to.f[i][j]) : "v"(a), "n"((16 * q + j) * ROWS * 4));
+    } else {
+      const unsigned a = stage + foff[q];
+      asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(to.f[i]) : "v"(a), "n"(i * 16 * 128));
     }
   }
 };
@@ -443,22 +441,29 @@ __global__ __launch_bounds__(256) void gemm_f32_dma_kernel(PlainArgs ga) {
   };
   typename LA::Frag fa[2];
   typename LB::Frag fb[2];
-  auto read = [&](int stage, int q) {
-    ta.read(stage * STAGE, q, fa[q]);
-    tb.read(stage * STAGE, q, fb[q]);
+  auto read = [&](int stage, int q, int u) {   // one unit of the A fragments, then of the B fragments
+    if (u < TM) ta.read(stage * STAGE, q, u, fa[q]);
+    else tb.read(stage * STAGE, q, u - TM, fb[q]);
   };
   auto arrived = [&](int q) {
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     fa[q].arrived();
     fb[q].arrived();
   };
-  auto half = [&](auto colsum, int q) {
+  // The MFMAs of half q, and between the first of them the reads of the next half (of tile `stage`), so that the matrix cores
+  // do not stand still while those are issued; `load` goes out behind the reads.
+  auto half = [&](auto colsum, int q, int stage, auto load) {
+    constexpr int COUNT = 4 * TM * TN, READS = TM + TN, EVERY = COUNT / 2 / READS < 1 ? 1 : COUNT / 2 / READS;   // within the first half of them
 #pragma unroll
-    for (int e = 0; e < 4; ++e)
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[q].at(j, e), fa[q].at(i, e), acc[i][j], 0, 0, 0);
+    for (int x = 0; x < COUNT; ++x) {
+      const int e = x / (TM * TN), i = x / TN % TM, j = x % TN;
+      if (x % EVERY == 0 && x / EVERY < READS) {
+        read(stage, q ^ 1, x / EVERY);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[q].at(j, e), fa[q].at(i, e), acc[i][j], 0, 0, 0);
+      if (x == COUNT / 2) load();
+    }
     if constexpr (decltype(colsum)::value) {
       f32x4 b[TN];
 #pragma unroll
@@ -472,22 +477,19 @@ __global__ __launch_bounds__(256) void gemm_f32_dma_kernel(PlainArgs ga) {
     for (int s = 0; s < NS; ++s)
       if (s < n) issue(s, s);
     landed(n - 1 < NS - 1 ? n - 1 : NS - 1);
-    read(0, 0);
+#pragma unroll
+    for (int u = 0; u < TM + TN; ++u) read(0, 0, u);
     arrived(0);
     int cur = 0;
     for (int t = 0; t < n; ++t) {
       const int nxt = cur + 1 == NS ? 0 : cur + 1;
-      read(cur, 1);
-      __builtin_amdgcn_sched_barrier(0);
-      half(colsum, 0);
+      half(colsum, 0, cur, []() {});
       arrived(1);
       // this wave is done with tile t's stage; behind the barrier everybody is, and tile t + 1 has landed
       const int later = n - 2 - t;
       landed(later < NS - 2 ? later : NS - 2);
-      if (t + NS < n) issue(t + NS, cur);
-      read(nxt, 0);   // behind the last tile: stale, nothing multiplies it
-      __builtin_amdgcn_sched_barrier(0);
-      half(colsum, 1);
+      // behind the last tile the reads bring stale values that nothing multiplies
+      half(colsum, 1, nxt, [&]() { if (t + NS < n) issue(t + NS, cur); });
       arrived(0);
       if constexpr (decltype(colsum)::value) cs.fold(t);
       cur = nxt;

@@ -198,18 +198,18 @@ inline size_t gemm_wgrad_batch_ws_floats(int D, int F) {
 }
 
 // Tiles of a launch of up to four products on the fp32 matrix instructions, in units of 32 rows and columns.  Microseconds
-// fitted to launches of 17 to 8000 rows (weight gradients: tokens) with widths of 64 to 4096 in all three layouts, within 4 to
-// 7 % (k = K / 1000, w: tiles on the fullest CU): a k tile's MFMAs, once for each tile that shares the SIMDs, the loads of
-// all tiles, the stores.  The choice is 0.7 % off the fastest tile on average.  1576 x 768 x 768: 1200 tiles of 32x32 27 us,
-// 300 of 64x64 36; 4081 x 768 x 3072: 512 of 64x96 175 us, 768 of 64x64 190, 3072 of 32x32 227; 4081 x 1024 x 4096: 256 of
-// 128x128 300 us, 704 of 64x96 422.
+// fitted to launches of 17 to 8000 rows (weight gradients: tokens) with widths of 64 to 4096 in all three layouts, within 5 to
+// 8 % (k = K / 1000, w: tiles on the fullest CU): a k tile's MFMAs, once for each tile that shares the SIMDs, the loads of
+// all tiles, the stores.  The choice is 0.7 % off the fastest tile on average.  1576 x 768 x 768: 1200 tiles of 32x32 25 us,
+// 300 of 64x64 33; 4081 x 768 x 3072: 512 of 64x96 176 us, 768 of 64x64 181, 3072 of 32x32 224; 4081 x 1024 x 4096: 256 of
+// 128x128 279 us, 1024 of 64x64 324.
 struct F32Tile { int tm, tn; };
 inline F32Tile gemm_f32_tile(const Gemm* a, int n) {
   const double k = 1e-3 * a[0].K;
   struct Line { int tm, tn; double one0, one, more0, more, load, store; };
-  static const Line lines[5] = {{1, 1, 2.85, 7.52, 0.07, 5.71, 0.63, 0.76}, {1, 2, 3.29, 11.37, 0.49, 10.23, 2.95, 0.28},
-                                {2, 2, 3.72, 18.72, 0.22, 18.03, 6.08, 0.93}, {2, 3, 4.82, 26.12, 1.92, 23.98, 8.13, 0.35},
-                                {4, 4, 6.56, 63.63, 0.12, 69.49, 9.59, 1.32}};
+  static const Line lines[5] = {{1, 1, 2.85, 7.44, 0.11, 5.4, 0.0, 0.67}, {1, 2, 3.27, 11.37, 0.4, 9.87, 1.52, 0.43},
+                                {2, 2, 3.72, 18.18, 0.18, 16.85, 5.75, 0.97}, {2, 3, 4.45, 26.08, 1.08, 24.85, 6.45, 0.79},
+                                {4, 4, 6.49, 62.45, 0.0, 70.09, 7.21, 1.36}};
   F32Tile best{1, 1};
   double best_us = 1e300;
   for (const Line& l : lines) {
@@ -221,7 +221,7 @@ inline F32Tile gemm_f32_tile(const Gemm* a, int n) {
     }
     const int64_t w = (t + 255) / 256;
     double us = l.one0 + l.one * k + (double)(w - 1) * (l.more0 + l.more * k) + l.load * 1e-8 * (double)t * 32 * (l.tm + l.tn) * a[0].K + l.store * out;
-    if (l.tm == 4 && t * 10 >= w * 256 * 9) us *= 0.95;   // whole rounds of the largest tiles run a little ahead of the line
+    if (l.tm == 4 && t * 10 >= w * 256 * 9) us *= 0.93;   // whole rounds of the largest tiles run a little ahead of the line
     if (us < best_us) { best_us = us; best = F32Tile{l.tm, l.tn}; }
   }
   return best;
