@@ -57,7 +57,8 @@ struct LnBwdArgs {
   int rows, D;
 };
 
-// Workgroup `wg` of `nwg`, NWAVES waves of 64 lanes, one row per wave at a time; red = 3 D floats of LDS.
+// Workgroup `wg` of `nwg`, NWAVES waves of 64 lanes, one row per wave at a time; red = NWAVES * D floats of LDS, 16-byte
+// aligned.
 // dy may be the fp32 gradient stream or a T tensor; the result goes to an fp32 stream buffer (dx_s), a T copy
 // for the matrix-core operands (dx_o), or both (either may be null).
 template <typename T, typename TDY, typename TX, int VPL, int NWAVES>
@@ -147,26 +148,33 @@ __device__ __forceinline__ void ln_bwd_rows(const LnBwdArgs<T, TDY, TX>& a, floa
     }
     if (more) cur = nxt;
   }
-  // combine the waves of the workgroup in wave order (fixed, so reproducible)
-  for (int w = 0; w < NWAVES; ++w) {
-    if (wave == w) {
+  // Combine the waves of the workgroup in wave order (fixed, so reproducible), one of the three sums at a time: every wave
+  // puts its own into LDS, then all threads add.  One wave after the other adding to a common row, element by element,
+  // took 1 to 3 us of every launch: 1379 x 768 10.2 -> 7.2 us, 64 x 768 8.0 -> 5.3, 12608 x 768 28.6 -> 27.4.
+  float* const out = a.partial + (size_t)wg * 3 * D;
+  auto combine = [&](const float (&v)[VPL][4], int which) {
+    if (which) __syncthreads();   // the sums in front of these have been read
 #pragma unroll
-      for (int j = 0; j < VPL; ++j) {
-        const int c = lane + 64 * j;
-        if (c < nvec) {
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const int i = 4 * c + e;
-            red[i] = (w ? red[i] : 0.f) + ag[j][e];
-            red[D + i] = (w ? red[D + i] : 0.f) + ab[j][e];
-            red[2 * D + i] = (w ? red[2 * D + i] : 0.f) + as[j][e];
-          }
-        }
-      }
+    for (int j = 0; j < VPL; ++j) {
+      const int c = lane + 64 * j;
+      if (c < nvec) store4(red + wave * D + 4 * c, v[j]);
     }
     __syncthreads();
-  }
-  for (int i = threadIdx.x; i < 3 * D; i += 64 * NWAVES) a.partial[(size_t)wg * 3 * D + i] = red[i];
+    for (int c = threadIdx.x; c < nvec; c += 64 * NWAVES) {
+      float s[4], t[4];
+      load4(red + 4 * c, s);
+#pragma unroll
+      for (int w = 1; w < NWAVES; ++w) {
+        load4(red + w * D + 4 * c, t);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) s[e] += t[e];
+      }
+      store4(out + which * D + 4 * c, s);
+    }
+  };
+  combine(ag, 0);
+  combine(ab, 1);
+  combine(as, 2);
 }
 
 }  // namespace pt

@@ -199,7 +199,7 @@ constexpr int g_ln_bwd_blocks = 0;   // workgroups of the backward kernel (0 = d
 // buffer (dx_s), a T copy for the matrix-core operands (dx_o), or both (either may be null).
 template <typename T, typename TDY, typename TX, int VPL>
 __global__ __launch_bounds__(64 * kLnBwdWaves) void ln_bwd_kernel(LnBwdArgs<T, TDY, TX> a) {
-  extern __shared__ float red[];  // [3][D]: d(gamma), d(beta), column sums of the output
+  extern __shared__ __attribute__((aligned(16))) float red[];  // [waves][D]
   ln_bwd_rows<T, TDY, TX, VPL, kLnBwdWaves>(a, red, blockIdx.x, gridDim.x);
 }
 
@@ -275,7 +275,7 @@ void layernorm_bwd(int dt, bool dy_f32, bool x_f32, const void* dy, int64_t lddy
   if (rows <= 0) return;
   const int cap = g_ln_bwd_blocks > 0 && g_ln_bwd_blocks < kLnBwdBlocks ? g_ln_bwd_blocks : kLnBwdBlocks;
   const int nb = cdiv(rows, kLnBwdWaves) < cap ? cdiv(rows, kLnBwdWaves) : cap;
-  const size_t shm = (size_t)3 * D * sizeof(float);
+  const size_t shm = (size_t)kLnBwdWaves * D * sizeof(float);
 #define LN_BWD(T, TDY, TX, V)                                                                                      \
   do {                                                                                                             \
     const LnBwdArgs<T, TDY, TX> a_{(const TDY*)dy, lddy, (const TX*)x, ldx, mean, rstd, (const T*)gamma, dres, lddres, \
