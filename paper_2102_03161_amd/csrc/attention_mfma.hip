@@ -726,10 +726,14 @@ __device__ __forceinline__ uint4 keep(uint4 v, bool on) {
   const unsigned m = on ? 0xffffffffu : 0u;
   return make_uint4(v.x & m, v.y & m, v.z & m, v.w & m);
 }
+// SPLIT: the two passes of a head on workgroups of their own (blockIdx.z), for no more heads than half the CUs: both load the
+// head's matrices, but neither waits for the other's pass (197 tokens, 84 heads 19.0 -> 15.4 us, 77 tokens, 12 heads 8.9 -> 7.2).
+template <bool SPLIT>
 __global__ __launch_bounds__(512) void attn_bwd_fused_res_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ ctx,
                                                                  const bf16* __restrict__ dctx,
                                                                  const float* __restrict__ lse, bf16* __restrict__ dqkv,
                                                                  int S, int H, int ntile) {
+  const bool with_dq = !SPLIT || blockIdx.z == 0, with_dkv = !SPLIT || blockIdx.z == 1;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const int tile_elems = ntile * 32 * LDR;
   bf16* Qs = reinterpret_cast<bf16*>(smem);
@@ -795,6 +799,7 @@ __global__ __launch_bounds__(512) void attn_bwd_fused_res_kernel(const bf16* __r
   __builtin_amdgcn_sched_barrier(0);   // the second pass's images are requested once K and V have left their registers
 #pragma unroll
   for (int u = 0; u < 4; ++u) {
+    if (!with_dkv) break;
     const int ch = tid + u * (int)blockDim.x, row = ch >> 3, col = (ch & 7) * 8, rc = row < S ? row : S - 1;
     vq[u] = *reinterpret_cast<const uint4*>(base + (int64_t)rc * 3 * D + col);
     vd[u] = *reinterpret_cast<const uint4*>(dobase + (int64_t)rc * D + col);
@@ -811,7 +816,7 @@ __global__ __launch_bounds__(512) void attn_bwd_fused_res_kernel(const bf16* __r
   asm volatile("" ::: "memory");
 
   // ---- pass 1: the wave's rows as queries ----
-  if (active) {
+  if (active && with_dq) {
     f32x16 dq[2];
 #pragma unroll
     for (int dt = 0; dt < 2; ++dt)
@@ -861,6 +866,7 @@ __global__ __launch_bounds__(512) void attn_bwd_fused_res_kernel(const bf16* __r
     if (ok) store_owned_row(obase + (int64_t)own * 3 * D, dq, scale, half);
   }
 
+  if (!with_dkv) return;
   // ---- pass 2: the wave's rows as keys ----
 #pragma unroll
   for (int u = 0; u < 4; ++u) {
@@ -1396,8 +1402,14 @@ void attention_bwd_mfma(const void* qkv, const void* ctx, const void* dctx, cons
   if (S <= g_attn_fused_max_s_bwd) {
     const int ntile = cdiv(S, 32);
     const size_t lds = (size_t)4 * ntile * 32 * LDR * sizeof(bf16) + (size_t)2 * ntile * 32 * sizeof(float);
-    if (allow_lds(attn_bwd_fused_res_kernel, lds) == hipSuccess) {
-      hipLaunchKernelGGL(attn_bwd_fused_res_kernel, dim3(H, nb), dim3(64 * ntile), lds, st, (const bf16*)qkv,
+    // no more heads than half the CUs: a workgroup for each of a head's passes
+    if (2 * nb * H <= device_cu_count() && allow_lds(attn_bwd_fused_res_kernel<true>, lds) == hipSuccess) {
+      hipLaunchKernelGGL(attn_bwd_fused_res_kernel<true>, dim3(H, nb, 2), dim3(64 * ntile), lds, st, (const bf16*)qkv,
+                         (const bf16*)ctx, (const bf16*)dctx, lse, (bf16*)dqkv, S, H, ntile);
+      return;
+    }
+    if (allow_lds(attn_bwd_fused_res_kernel<false>, lds) == hipSuccess) {
+      hipLaunchKernelGGL(attn_bwd_fused_res_kernel<false>, dim3(H, nb), dim3(64 * ntile), lds, st, (const bf16*)qkv,
                          (const bf16*)ctx, (const bf16*)dctx, lse, (bf16*)dqkv, S, H, ntile);
       return;
     }
