@@ -999,18 +999,43 @@ int window_alloc(pt_ctx* c, bool evict, bool block) {
   return -1;
 }
 
-// Stages the host row of `id` into a window slot (asynchronously, on the copy stream); returns the slot or -1.
-int window_stage(pt_ctx* c, int64_t id, bool evict, bool block, hipError_t* err) {
+// Host rows on their way into window slots, on the copy stream.  Rows of neighbouring ids that got neighbouring slots go in one
+// copy: issuing one copy per row took the host 2 us each, with nothing queued on the GPU behind them (200 to 300 us of a
+// step over 128 samples).  Whoever adds rows flushes before it returns or orders anything behind the copies.
+struct StageRun {
+  pt_ctx* c;
+  int64_t id0 = 0;
+  int slot0 = 0, n = 0;
+  hipError_t err = hipSuccess;
+  void flush() {
+    if (n == 0) return;
+    const hipError_t e = hipMemcpyAsync(window_row(c, slot0), host_row(c, id0), (size_t)n * cache_row_bytes(c), hipMemcpyHostToDevice, c->copy_st);
+    if (e == hipSuccess) {
+      c->n_h2d += n;
+    } else {
+      err = e;
+      for (int i = 0; i < n; ++i) { c->win_of.erase(id0 + i); c->win[slot0 + i].state = 0; c->win[slot0 + i].id = -1; }
+    }
+    n = 0;
+  }
+  void add(int64_t id, int slot) {
+    if (n > 0 && id == id0 + n && slot == slot0 + n) { ++n; return; }
+    flush();
+    id0 = id; slot0 = slot; n = 1;
+  }
+  ~StageRun() { flush(); }
+};
+
+// Stages the host row of `id` into a window slot (asynchronously, through `run`); returns the slot or -1.
+int window_stage(pt_ctx* c, int64_t id, bool evict, bool block, StageRun* run) {
   auto it = c->win_of.find(id);
   if (it != c->win_of.end()) return it->second;
   const int slot = window_alloc(c, evict, block);
   if (slot < 0) return -1;
-  const hipError_t e = hipMemcpyAsync(window_row(c, slot), host_row(c, id), cache_row_bytes(c), hipMemcpyHostToDevice, c->copy_st);
-  if (e != hipSuccess) { if (err) *err = e; return -1; }
   c->win[slot].id = id; c->win[slot].state = 1; c->win[slot].stamp = c->call_stamp;
   c->win_of[id] = slot;
-  c->n_h2d++;
-  return slot;
+  run->add(id, slot);
+  return run->err == hipSuccess ? slot : -1;
 }
 
 }  // namespace
@@ -1035,16 +1060,17 @@ pt_status pt_cache_prefetch(pt_ctx* c, const int64_t* sample_ids, int32_t n, int
   if (!c->host_rows) return PT_OK;   // nothing lives on the host: every row is already in HBM
   const int64_t lo = c->cfg.cache_slots, hi = lo + c->cfg.host_slots;
   c->call_stamp++;
-  hipError_t err = hipSuccess;
+  StageRun run{c};
   int staged = 0;
   for (int i = 0; i < n; ++i) {
     const int64_t id = sample_ids[i];
     if (id < 0 || id >= hi) return fail(c, PT_EINVAL, "sample id outside the cache");
     if (id < lo || c->slot_k[(size_t)id] < 0 || c->win_of.count(id)) continue;
-    if (window_stage(c, id, false, false, &err) < 0) break;   // best effort: the window is full
+    if (window_stage(c, id, false, false, &run) < 0) break;   // best effort: the window is full
     ++staged;
   }
-  if (err != hipSuccess) return fail(c, PT_EDEVICE, hipGetErrorString(err));
+  run.flush();
+  if (run.err != hipSuccess) return fail(c, PT_EDEVICE, hipGetErrorString(run.err));
   c->n_prefetched += staged;
   if (staged_out) *staged_out = staged;
   return PT_OK;
@@ -1102,7 +1128,7 @@ pt_status pt_frozen_forward(pt_ctx* c, const void* d_input, int32_t nb, const in
         if (needed + own > (int64_t)c->win.size()) return fail(c, PT_ENOMEM, "the window cannot hold this batch's host-tier rows");
       }
       c->call_stamp++;
-      hipError_t herr = hipSuccess;
+      StageRun run{c};
       for (int i = 0; i < nb; ++i) {
         if (sample_ids[i] < g.cache_slots || kw[i] < 0) continue;
         auto it = c->win_of.find(sample_ids[i]);
@@ -1113,8 +1139,8 @@ pt_status pt_frozen_forward(pt_ctx* c, const void* d_input, int32_t nb, const in
         host_used = true;
         int slot = -1;
         if (kw[i] >= 0) {
-          slot = window_stage(c, sample_ids[i], true, true, &herr);
-          if (slot < 0) return fail(c, herr != hipSuccess ? PT_EDEVICE : PT_ENOMEM, "no window slot for a host-tier row");
+          slot = window_stage(c, sample_ids[i], true, true, &run);
+          if (slot < 0) return fail(c, run.err != hipSuccess ? PT_EDEVICE : PT_ENOMEM, "no window slot for a host-tier row");
           c->win[slot].stamp = c->call_stamp;
           row_r[i] = g.cache_slots + slot;
         }
@@ -1127,6 +1153,8 @@ pt_status pt_frozen_forward(pt_ctx* c, const void* d_input, int32_t nb, const in
           row_w[i] = g.cache_slots + slot;
         }
       }
+      run.flush();
+      if (run.err != hipSuccess) return fail(c, PT_EDEVICE, hipGetErrorString(run.err));
       if (host_used) {
         HIP_TRY(c, hipEventRecord(c->ev_copy, c->copy_st));
         HIP_TRY(c, hipStreamWaitEvent(c->st, c->ev_copy, 0));
