@@ -123,13 +123,15 @@ struct PlainColSum {
     for (int j = 0; j < TN; ++j) { s2[j] += s1[j]; s1[j] = 0.f; }
   }
   // `out`: the sums of this wave's first column; n: columns that exist from there on
-  __device__ __forceinline__ void store(float* out, int n, int lane) const {
+  // turns: column TN l + j is column l of unit j
+  __device__ __forceinline__ void store(float* out, int n, int lane, bool turns = false) const {
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
       float v = (s0[j] + s1[j]) + s2[j];
       v += __shfl_xor(v, 16, 64);
       v += __shfl_xor(v, 32, 64);
-      if (lane < 16 && j * 16 + lane < n) out[j * 16 + lane] = v;
+      const int col = turns ? TN * lane + j : j * 16 + lane;
+      if (lane < 16 && col < n) out[col] = v;
     }
   }
 };
@@ -238,7 +240,7 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(PlainArgs ga) {
 // two register sets, and the one barrier of a tile stands in front of its second half's MFMAs, where no wave has to wait for
 // LDS.  Staged through registers, every tile had its LDS writes, barrier and fragment reads in a row in front of its MFMAs:
 // 1576 x 768 x 3072 112 -> 87 us (86 TFLOP/s; 32x32 tiles), 231 x 768 x 3072 51 -> 27, 1576 x 2304 x 768 74 -> 64, 4081 x 1024 x
-// 4096 354 -> 279 (123 TFLOP/s); a block's weight gradients at width 1024 over 1576 tokens 453 -> 384, at width 256 50 -> 35.
+// 4096 354 -> 283 (121 TFLOP/s); a block's weight gradients at width 1024 over 1576 tokens 457 -> 362, at width 256 51 -> 34.
 // With the reads in front of a half's MFMAs instead of between them the larger tiles are 5 to 7 % slower (4081 x 1024 x 4096
 // 295); two or four tiles deep are the same within 3 %.
 #define PT_LDS(p) ((__attribute__((address_space(3))) void*)(p))
@@ -256,8 +258,12 @@ template <bool STRIDED, int ROWS>
 struct DmaTile {
   static constexpr int LOADS = ROWS / 32, BYTES = ROWS * 128, UNITS = ROWS / 32;   // wave-wide loads per wave; 16-row units per wave
   static constexpr int CPR = STRIDED ? ROWS / 4 : 8;
+  // A strided operand's two or four units take turns with the rows (row UNITS l + i is row l of unit i), so that one LDS read
+  // brings all units' rows of one k: with a read per k and unit a block's weight gradients take 235 us instead of 224 (width 768,
+  // 1576 tokens), 384 instead of 362 (width 1024).
+  static constexpr bool TURNS = STRIDED && (UNITS == 2 || UNITS == 4);
   unsigned voff[LOADS];            // this lane's sources within a tile, bytes
-  unsigned foff[STRIDED ? UNITS : 2];
+  unsigned foff[TURNS ? 1 : STRIDED ? UNITS : 2];
   const char* src;                 // first byte of the tile that is loaded next
   int64_t step;
   static __device__ __forceinline__ int line(int wave, int i, int lane) { return (64 * (wave * LOADS + i) + lane) / CPR; }
@@ -282,8 +288,8 @@ struct DmaTile {
     const int g = lane >> 4, l = lane & 15;
     if constexpr (STRIDED) {
 #pragma unroll
-      for (int i = 0; i < UNITS; ++i) {
-        const int r = rbase + 16 * i + l;
+      for (int i = 0; i < (TURNS ? 1 : UNITS); ++i) {
+        const int r = TURNS ? rbase + UNITS * l : rbase + 16 * i + l;
         foff[i] = lds0 + 4 * g * ROWS * 4 + (((r >> 2) + 4 * g) % CPR) * 16 + (r & 3) * 4;
       }
     } else {
@@ -305,22 +311,33 @@ struct DmaTile {
   // The k values 16 q + 4 g + j of every unit's rows, j = 0..3.  Inline assembly, because the compiler would wait for every
   // load into LDS in front of a read; the values are there behind arrived(), and nothing moves them before.
   struct Frag {
-    typename std::conditional<STRIDED, float[4], f32x4>::type f[UNITS];
-    __device__ __forceinline__ float at(int i, int j) const { return f[i][j]; }
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    // [k] with TURNS, else [unit][k] or a vector of four k per unit
+    typename std::conditional<TURNS, typename std::conditional<UNITS == 2, f32x2, f32x4>::type[4],
+                              typename std::conditional<STRIDED, float[UNITS][4], f32x4[UNITS]>::type>::type f;
+    __device__ __forceinline__ float at(int i, int j) const {
+      if constexpr (TURNS) return f[j][i];
+      else return f[i][j];
+    }
     __device__ __forceinline__ void arrived() {
+      if constexpr (STRIDED && !TURNS) {
 #pragma unroll
-      for (int i = 0; i < UNITS; ++i) {
-        if constexpr (STRIDED) {
+        for (int i = 0; i < UNITS; ++i)
 #pragma unroll
           for (int j = 0; j < 4; ++j) asm volatile("" : "+v"(f[i][j]));
-        } else {
-          asm volatile("" : "+v"(f[i]));
-        }
+      } else {
+#pragma unroll
+        for (int i = 0; i < (TURNS ? 4 : UNITS); ++i) asm volatile("" : "+v"(f[i]));
       }
     }
   };
-  __device__ __forceinline__ void read(unsigned stage, int q, int i, Frag& to) const {   // unit i
-    if constexpr (STRIDED) {
+  static constexpr int READS = TURNS ? 4 : UNITS;   // parts that read() brings
+  __device__ __forceinline__ void read(unsigned stage, int q, int i, Frag& to) const {
+    if constexpr (TURNS) {
+      const unsigned a = stage + foff[0];
+      if constexpr (UNITS == 2) asm volatile("ds_read_b64 %0, %1 offset:%2" : "=v"(to.f[i]) : "v"(a), "n"((16 * q + i) * ROWS * 4));
+      else asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(to.f[i]) : "v"(a), "n"((16 * q + i) * ROWS * 4));
+    } else if constexpr (STRIDED) {
       const unsigned a = stage + foff[i];
 #pragma unroll
       for (int j = 0; j < 4; ++j) asm volatile("ds_read_b32 %0, %1 offset:%2" : "=v"(to.f[i][j]) : "v"(a), "n"((16 * q + j) * ROWS * 4));
@@ -335,7 +352,8 @@ struct DmaTile {
 // other way round, so a lane holds four neighbouring columns 4 (lane / 16) + v of row lane % 16 and moves 16 bytes at a
 // time; one element at a time, 4081 x 3072 x 768 with GELU takes 231 us and 1576 x 3072 x 768 94.  vec: sizes and
 // alignment allow it.
-template <int TM, int TN>
+// TURNS_A, TURNS_B: whether the units take turns with the rows, the columns (DmaTile).
+template <int TM, int TN, bool TURNS_A, bool TURNS_B>
 __device__ __forceinline__ void f32_store(const PlainProb& p, int epi_, bool vec, int row0, int col0, int lane, const f32x4 (&acc)[TM][TN]) {
   const GemmDev<float> g{reinterpret_cast<const float*>(p.A), reinterpret_cast<const float*>(p.B), p.C, p.M, p.N, p.K, p.lda, p.ldb, p.ldc,
                          reinterpret_cast<const float*>(p.bias), reinterpret_cast<const float*>(p.aux), reinterpret_cast<float*>(p.aux_out), p.ld_aux};
@@ -347,10 +365,13 @@ __device__ __forceinline__ void f32_store(const PlainProb& p, int epi_, bool vec
     for (int i = 0; i < TM; ++i)
 #pragma unroll
       for (int j = 0; j < TN; ++j) {
-        const int row = row0 + i * 16 + (lane & 15), col = col0 + j * 16 + 4 * (lane >> 4);
+        const int row = row0 + (TURNS_A ? TM * (lane & 15) + i : i * 16 + (lane & 15));
+        const int col = col0 + (TURNS_B ? 4 * TN * (lane >> 4) + 4 * j : j * 16 + 4 * (lane >> 4));
+        f32x4 v;   // four neighbouring columns: with turns, column TN u + j of the lane's 4 TN is element u of unit j
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = TURNS_B ? acc[i][(4 * j + e) % TN][(4 * j + e) / TN] : acc[i][j][e];
         if (row >= p.M || col >= p.N) continue;
         if (vec) {   // N is a multiple of four
-          f32x4 v = acc[i][j];
           if (BIAS) {
             const f32x4 b = load4(g.bias + col);
 #pragma unroll
@@ -371,7 +392,7 @@ __device__ __forceinline__ void f32_store(const PlainProb& p, int epi_, bool vec
         } else {
 #pragma unroll
           for (int e = 0; e < 4; ++e)
-            if (col + e < p.N) epilogue_store<float, float, EPI>(g, row, col + e, acc[i][j][e]);
+            if (col + e < p.N) epilogue_store<float, float, EPI>(g, row, col + e, v[e]);
         }
       }
   };
@@ -441,9 +462,9 @@ __global__ __launch_bounds__(256) void gemm_f32_dma_kernel(PlainArgs ga) {
   };
   typename LA::Frag fa[2];
   typename LB::Frag fb[2];
-  auto read = [&](int stage, int q, int u) {   // one unit of the A fragments, then of the B fragments
-    if (u < TM) ta.read(stage * STAGE, q, u, fa[q]);
-    else tb.read(stage * STAGE, q, u - TM, fb[q]);
+  auto read = [&](int stage, int q, int u) {   // one part of the A fragments, then of the B fragments
+    if (u < LA::READS) ta.read(stage * STAGE, q, u, fa[q]);
+    else tb.read(stage * STAGE, q, u - LA::READS, fb[q]);
   };
   auto arrived = [&](int q) {
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
@@ -453,12 +474,14 @@ __global__ __launch_bounds__(256) void gemm_f32_dma_kernel(PlainArgs ga) {
   // The MFMAs of half q, and between the first of them the reads of the next half (of tile `stage`), so that the matrix cores
   // do not stand still while those are issued; `load` goes out behind the reads.
   auto half = [&](auto colsum, int q, int stage, auto load) {
-    constexpr int COUNT = 4 * TM * TN, READS = TM + TN, EVERY = COUNT / 2 / READS < 1 ? 1 : COUNT / 2 / READS;   // within the first half of them
+    constexpr int COUNT = 4 * TM * TN, READS = LA::READS + LB::READS, EVERY = COUNT / 2 / READS < 1 ? 1 : COUNT / 2 / READS;   // within the first half of them
 #pragma unroll
     for (int x = 0; x < COUNT; ++x) {
       const int e = x / (TM * TN), i = x / TN % TM, j = x % TN;
-      if (x % EVERY == 0 && x / EVERY < READS) {
-        read(stage, q ^ 1, x / EVERY);
+      if (x % EVERY == 0) {
+        // the last MFMA takes what is left: small tiles have fewer MFMAs than reads
+#pragma unroll
+        for (int u = x / EVERY; u < READS && (u == x / EVERY || x + EVERY >= COUNT); ++u) read(stage, q ^ 1, u);
         __builtin_amdgcn_sched_barrier(0);
       }
       acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[q].at(j, e), fa[q].at(i, e), acc[i][j], 0, 0, 0);
@@ -478,7 +501,7 @@ __global__ __launch_bounds__(256) void gemm_f32_dma_kernel(PlainArgs ga) {
       if (s < n) issue(s, s);
     landed(n - 1 < NS - 1 ? n - 1 : NS - 1);
 #pragma unroll
-    for (int u = 0; u < TM + TN; ++u) read(0, 0, u);
+    for (int u = 0; u < LA::READS + LB::READS; ++u) read(0, 0, u);
     arrived(0);
     int cur = 0;
     for (int t = 0; t < n; ++t) {
@@ -498,9 +521,9 @@ __global__ __launch_bounds__(256) void gemm_f32_dma_kernel(PlainArgs ga) {
   if (do_colsum) run(std::bool_constant<TA>());
   else run(std::false_type());
   if constexpr (TA) {
-    if (do_colsum) cs.store(p.colsum + n0 + wn * 16 * TN, p.N - n0 - wn * 16 * TN, lane);
+    if (do_colsum) cs.store(p.colsum + n0 + wn * 16 * TN, p.N - n0 - wn * 16 * TN, lane, LB::TURNS);
   }
-  f32_store<TM, TN>(p, ga.epi, p.vec != 0, m0 + wm * 16 * TM, n0 + wn * 16 * TN, lane, acc);
+  f32_store<TM, TN, LA::TURNS, LB::TURNS>(p, ga.epi, p.vec != 0, m0 + wm * 16 * TM, n0 + wn * 16 * TN, lane, acc);
 }
 
 // pieces of four elements along the contiguous index
