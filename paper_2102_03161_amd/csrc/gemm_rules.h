@@ -100,21 +100,26 @@ inline int gemm_dma_variant(const Gemm& a) {
   // all hit the L2).
   const double k = 1e-3 * a.K;
   const int64_t t128 = cdiv(a.M, 128) * cdiv(a.N, 128), t64 = cdiv(a.M, 64) * cdiv(a.N, 64);
-  if (a.K % 64) {
+  // Forward products below 4096 rows keep to 64x64 and 128x128 tiles where 128x64 ones are fewer than 160 or do not all fit
+  // (two to a CU): their weights come from beyond the L2s, which few workgroups fetch slowly.  In a step, 1379 x 768 x 768 and
+  // 1379 x 768 x 3072 15.8 us on average on 64x64 tiles against 16.1 (alone 13.9 against 12.5), 2639 x 2304 x 768 17.2 on 128x128
+  // ones against 17.8 (alone 17.4 against 16.4); input gradients 15.4 against 14.8.
+  const int64_t t7 = cdiv(a.M, 128) * cdiv(a.N, 64);
+  if (a.K % 64 || (!a.tb && a.M < 4096 && (t7 < 160 || t7 > 512))) {
     // Microseconds fitted to launches of 17 to 8192 rows with N and K of 768 to 3072, within 15 % (k = K / 1000): a 128x128
     // workgroup alone 5.7 + 8.9 k, w of them w (5.3 + 7.0 k); a 64x64 workgroup alone 3.5 + 4.7 k, w of them w (1.9 + 3.05 k).
     const double w128 = (double)((t128 + 255) / 256), w64 = (double)((t64 + 255) / 256);
     const double us128 = w128 > 1 ? w128 * (5.3 + 7.0 * k) : 5.7 + 8.9 * k;
     const double us64 = w64 > 1 ? w64 * (1.9 + 3.05 * k) : 3.5 + 4.7 * k;
     if (us64 <= us128) return 3;
-    // K no multiple of 32: only eight waves on 64-wide k tiles take it (16384 x 1152 x 4304 228 us against 349 on 64x64
+    // K no multiple of 32: of the 128x128 tiles only eight waves on 64-wide k tiles take it (16384 x 1152 x 4304 228 us against 349 on 64x64
     // tiles and 235 on four waves with 32-wide ones; input gradients 254, 346, 273; 8192 x 3072 x 776 65, 98, 74)
     return a.K % 32 ? 4 : 1;
   }
   // Microseconds fitted to launches of 77 to 10400 rows with N and K of 256 to 4096, within 10 to 12 % (w: tiles on the
   // fullest CU).  1379 x 768 x 3072: 264 tiles of 64x64, 20.5 us, against 132 of 128x64, 18.0; 2639 x 768 x 3072 23.5 against
   // 19.5; 2639 x 3072 x 768 24.3 on 128x128 tiles against 25.6; 520 x 1024 x 4096 14.3 on 64x64 tiles against 20.9 on 128x64.
-  // Over these launches the choice is 1.3 % off the fastest tile on average; with the two lines above it was 2.9 %.
+  // Over these launches the choice is 1.5 % off the fastest tile on average; with the two lines above alone it was 2.9 %.
   auto cost = [&](int bm, int bn, double one0, double one, double more0, double more, double load, double store) {
     const int64_t t = cdiv(a.M, bm) * cdiv(a.N, bn);
     return one0 + one * k + (double)(cdiv(t, 256) - 1) * (more0 + more * k) + load * 1e-8 * (double)t * (bm + bn) * a.K +
