@@ -331,10 +331,9 @@ __device__ __forceinline__ void dma_run(const GemmDev<bf16>& g, const SplitArgs&
     compiler_fence();
     __builtin_amdgcn_s_barrier();   // everybody's loads of tile `it` have landed, and tile it-1 is fully consumed
     compiler_fence();
-    // The next loads go out in front of the fragment reads, but behind them in the TAIL kernels (64x64 tiles, small weight
-    // gradients): there the choice between source and zeros makes the issue as long as the reads' latency, which is
-    // a good part of a tile's chain (1379 x 768 x 2304 15.9 -> 14.5 us, 231 x 256 x 1024 8.3 -> 7.9 us, weight gradients of
-    // width 768 over 2639 tokens 60.9 -> 58.3 us; without TAIL, 2639 x 3072 x 768 on eight waves 20.9 -> 21.2 us).
+    // The next loads go out in front of the fragment reads, but behind them in the TAIL kernels: there the choice between
+    // source and zeros makes the issue as long as the reads' latency, which is a good part of a tile's chain (this loop on
+    // 64x64 tiles, 1379 x 768 x 2304: 15.9 -> 14.5 us; without TAIL, 2639 x 3072 x 768 on eight waves 20.9 -> 21.2 us).
     const bool more = it + kNS - 1 < n;
     if (!TAIL && more) issue(it + kNS - 1, fill);
     const unsigned char* sa = lds + cur * STAGE;
@@ -880,9 +879,9 @@ __global__ __launch_bounds__(512) void gemm_wgrad_group_kernel(GroupArgs ga) {
 }
 
 // The same with BT x BT tiles of the single-role pipeline, for few tokens or narrow matrices, where the large tiles
-// leave most CUs without work or write split-K slabs that cost more than the products (wgrad_tiling has the line).  What
-// bounds a workgroup is the chain of a k tile, barrier, fragment reads, MFMAs (more stages are slower: 64x64 tiles with
-// five 42.8 -> 49.2 us, 128x128 35.0 -> 36.6); two workgroups per CU hide part of each other's.
+// leave most CUs without work or write split-K slabs that cost more than the products (wgrad_tiling has the line).  More
+// stages are slower (64x64 tiles with five 42.8 -> 49.2 us, 128x128 35.0 -> 36.6); two workgroups per CU hide part of each
+// other's barriers and reads.
 template <int BT, int NS, int BK>
 __global__ __launch_bounds__(256, 2) void gemm_wgrad_group_small_kernel(GroupArgs ga) {
   const int total_tiles = ga.tile0[ga.nprob], total_work = total_tiles * ga.splits;
