@@ -1200,10 +1200,7 @@ void gemm_dma(const Gemm& a, int variant, hipStream_t st) {
       break;
     case 7: dispatch_fwd<128, 64, 4, 2, 3, 64>(a, st); break;
     default:
-      // One workgroup on a CU has three tiles in flight instead of two: 1344 x 768 x 3072 15.4 -> 13.1 us, 231 x 768 x 3072
-      // 13.4 -> 11.1, 900 x 1024 x 1024 6.6 -> 6.0; with more than one the third workgroup that fits beside 48 KB counts
-      // for more (1379 x 3072 x 768 17.7 -> 19.6), and a short K has nothing to hide (231 x 256 x 256 3.7 -> 3.9).
-      if ((int64_t)cdiv(a.M, 64) * cdiv(a.N, 64) <= 256 && a.K >= 512) dispatch_fwd<64, 64, 2, 2, 4, 64, true>(a, st);
+      if (gemm_64_four_stages(a)) dispatch_fwd<64, 64, 2, 2, 4, 64, true>(a, st);
       else dispatch_fwd<64, 64, 2, 2, 3, 64, true>(a, st);
       break;
   }

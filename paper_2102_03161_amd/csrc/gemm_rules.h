@@ -65,13 +65,37 @@ inline GemmRegTiling gemm_reg_tiling(const Gemm& a) {
   return GemmRegTiling{tile, (int)splits};
 }
 
+// 64x64 tiles: the kernel with four stages.  One workgroup on a CU has three tiles in flight instead of two: 1344 x 768 x 3072
+// 15.4 -> 13.1 us, 231 x 768 x 3072 13.4 -> 11.1, 900 x 1024 x 1024 6.6 -> 6.0 (launches in a loop, weights in the L2s); with more
+// than one the third workgroup that fits beside 48 KB counts for more (1379 x 3072 x 768 17.7 -> 19.6), and a short K has nothing
+// to hide (231 x 256 x 256 3.7 -> 3.9).
+inline bool gemm_64_four_stages(const Gemm& a) {
+  return (int64_t)((a.M + 63) / 64) * ((a.N + 63) / 64) <= 256 && a.K >= 512;
+}
+
 // Variant of the asynchronous kernels, forward and input-gradient products: 1 = 128x128 tiles, 2 = 256x128, 3 = 64x64, 4 =
 // 128x128 with eight waves, 5 / 6 = the two-group kernel with 256 / 192-row tiles, 7 = 128x64.  Every variant runs the same matrix
 // instructions in the same k order, so a row's result does not depend on the choice (nor, through it, on the batch size).
 inline int gemm_dma_variant(const Gemm& a) {
   auto cdiv = [](int64_t x, int64_t y) { return (x + y - 1) / y; };
+  const double k = 1e-3 * a.K;
+  if (a.K % 64) {
+    // 64x64 or 128x128 tiles.  Microseconds fitted to launches of 17 to 8192 rows with N and K of 768 to 3072 (k = K / 1000): a
+    // 128x128 workgroup alone 5.7 + 8.9 k, w of them w (5.3 + 7.0 k); a 64x64 workgroup alone 3.5 + 4.7 k, w of them
+    // w (1.9 + 3.05 k).  The 64x64 lines are those of an older k loop, up to a third above the present one; over 722 products of
+    // widths 200 to 1152 and 17 to 16384 rows the choice is 1.7 % off the fastest tile on average (10 to 28 % for 62 of them,
+    // 10000 x 600 x 2400 the worst).
+    const int64_t t128 = cdiv(a.M, 128) * cdiv(a.N, 128), t64 = cdiv(a.M, 64) * cdiv(a.N, 64);
+    const double w128 = (double)((t128 + 255) / 256), w64 = (double)((t64 + 255) / 256);
+    const double us128 = w128 > 1 ? w128 * (5.3 + 7.0 * k) : 5.7 + 8.9 * k;
+    const double us64 = w64 > 1 ? w64 * (1.9 + 3.05 * k) : 3.5 + 4.7 * k;
+    if (us64 <= us128) return 3;
+    // K no multiple of 32: of the 128x128 tiles only eight waves on 64-wide k tiles take it (16384 x 1152 x 4304 228 us against 349 on 64x64
+    // tiles and 235 on four waves with 32-wide ones; input gradients 254, 346, 273; 8192 x 3072 x 776 65, 98, 74)
+    return a.K % 32 ? 4 : 1;
+  }
   int pp = 0;   // the two-group kernel whose tiles fill the CUs well
-  if (a.M >= 4096 && a.K % 64 == 0) {
+  if (a.M >= 4096) {
     // At least 4096 rows: the two-group kernel with 256x256 or 192x256 tiles, one workgroup per CU, whichever
     // fills whole rounds of 256 CUs better (M = 12608, N = 768: 198 tiles of 192x256 against 150 of 256x256).
     const int64_t tn = cdiv(a.N, 256);
@@ -85,6 +109,7 @@ inline int gemm_dma_variant(const Gemm& a) {
       if (last == 0 || last >= 224) pp = 6;
       else if (t256 * 10 >= cdiv(t256, 256) * 256 * 9) pp = 5;
       else if (a.M >= 9000) return 2;
+      else if (t256 * 10 >= cdiv(t256, 256) * 256 * 8) pp = 5;   // 4400 x 3072 x 768 36.7 us, 44.3 on 128x128 tiles
     } else {
       const int v = cdiv(t192, 256) * 192 < cdiv(t256, 256) * 256 ? 6 : 5;
       // fewer tiles than 60 % of the CUs of their rounds (8192 tokens at N = 768: 129 tiles): smaller tiles fill the
@@ -92,58 +117,35 @@ inline int gemm_dma_variant(const Gemm& a) {
       const int64_t tiles = v == 6 ? t192 : t256;
       if (tiles * 10 >= cdiv(tiles, 256) * 256 * 6) pp = v;
     }
-    if (pp && (a.M > 12288 || a.K < 256)) return pp;   // beyond what the cost lines below were fitted to
+    if (pp && (a.M > 16384 || a.K < 256)) return pp;   // beyond what their lines below were fitted to
   }
-  // Below that, 64x64, 128x64 or 128x128 tiles.  What bounds them is the way of the operands into LDS: the CU that gets the
-  // most tiles brings in (rows + columns) * K of each, at 20 to 30 bytes per clock, and all CUs together share what the L2s
-  // get from the memory side (loads alone take 20 of the 20.5 us of 1379 x 768 x 3072 on 64x64 tiles, and 14 when they
-  // all hit the L2).
-  const double k = 1e-3 * a.K;
-  const int64_t t128 = cdiv(a.M, 128) * cdiv(a.N, 128), t64 = cdiv(a.M, 64) * cdiv(a.N, 64);
-  // Forward products below 4096 rows keep to 64x64 and 128x128 tiles where 128x64 ones are fewer than 160 or do not all fit
-  // (two to a CU): their weights come from beyond the L2s, which few workgroups fetch slowly.  In a step, 1379 x 768 x 768 and
-  // 1379 x 768 x 3072 15.8 us on average on 64x64 tiles against 16.1 (alone 13.9 against 12.5), 2639 x 2304 x 768 17.2 on 128x128
-  // ones against 17.8 (alone 17.4 against 16.4); input gradients 15.4 against 14.8.
-  const int64_t t7 = cdiv(a.M, 128) * cdiv(a.N, 64);
-  if (a.K % 64 || (!a.tb && a.M < 4096 && (t7 < 160 || t7 > 512))) {
-    // Microseconds fitted to launches of 17 to 8192 rows with N and K of 768 to 3072, within 15 % (k = K / 1000): a 128x128
-    // workgroup alone 5.7 + 8.9 k, w of them w (5.3 + 7.0 k); a 64x64 workgroup alone 3.5 + 4.7 k, w of them w (1.9 + 3.05 k).
-    const double w128 = (double)((t128 + 255) / 256), w64 = (double)((t64 + 255) / 256);
-    const double us128 = w128 > 1 ? w128 * (5.3 + 7.0 * k) : 5.7 + 8.9 * k;
-    const double us64 = w64 > 1 ? w64 * (1.9 + 3.05 * k) : 3.5 + 4.7 * k;
-    if (us64 <= us128) return 3;
-    // K no multiple of 32: of the 128x128 tiles only eight waves on 64-wide k tiles take it (16384 x 1152 x 4304 228 us against 349 on 64x64
-    // tiles and 235 on four waves with 32-wide ones; input gradients 254, 346, 273; 8192 x 3072 x 776 65, 98, 74)
-    return a.K % 32 ? 4 : 1;
-  }
-  // Microseconds fitted to launches of 77 to 10400 rows with N and K of 256 to 4096, within 10 to 12 % (w: tiles on the
-  // fullest CU).  1379 x 768 x 3072: 264 tiles of 64x64, 20.5 us, against 132 of 128x64, 18.0; 2639 x 768 x 3072 23.5 against
-  // 19.5; 2639 x 3072 x 768 24.3 on 128x128 tiles against 25.6; 520 x 1024 x 4096 14.3 on 64x64 tiles against 20.9 on 128x64.
-  // Over these launches the choice is 1.5 % off the fastest tile on average; with the two lines above alone it was 2.9 %.
-  auto cost = [&](int bm, int bn, double one0, double one, double more0, double more, double load, double store) {
-    const int64_t t = cdiv(a.M, bm) * cdiv(a.N, bn);
-    return one0 + one * k + (double)(cdiv(t, 256) - 1) * (more0 + more * k) + load * 1e-8 * (double)t * (bm + bn) * a.K +
-           store * 1e-6 * (double)a.M * a.N;
+  // What bounds the smaller tiles is the way of the operands into LDS: the CU that gets the most tiles brings in (rows +
+  // columns) * K of each, at 20 to 30 bytes per clock, and all CUs together share what comes from beyond the L2s.  A line per
+  // tile: a workgroup alone, each further one on the fullest of 256 CUs, all loads, the stores, and each further round of as
+  // many as a CU holds at a time.  The constants were fitted to the choice between the lines, and only roughly to
+  // microseconds, over 1645 products of 17 to 28000 rows, widths of 256 to 1280 and MLPs four times as wide, timed the way a
+  // step runs them: the weights come from HBM (600 MB of them in turn), the other operand is recent.  There the choice is 0.3 %
+  // off the fastest of its tiles on average below 4096 rows and 0.6 % up to 16384 (lines fitted to launches with their weights
+  // in the L2s: 1.4 and 4.2 %); more than 5 % off are 37 of 1642 products, more than 10 % only 4400 to 5300 x 1024 x 4096 (84
+  // on 128x128 tiles, 66 to 70 on 128x64) and 11500 x 1024 x 256.  Forward, us: 4000 x 768 x 3072 36.5 on 64x64 tiles, 31.9 on
+  // 128x64, 40.7 on 128x128; 1379 x 3072 x 768 18.5, 19.8, 20.6; 4600 x 512 x 2048 23.6, 21.8, 29.2; 6500 x 768 x 3072 58.2, 54.2,
+  // 50.5; input gradient 8192 x 3072 x 768 74.8, 65.6, 62.8, with eight waves 53.9.
+  auto cost = [&](int bm, int bn, int held, double one0, double one, double more0, double more, double load, double store, double round) {
+    const int64_t t = cdiv(a.M, bm) * cdiv(a.N, bn), w = cdiv(t, 256);
+    return one0 + one * k + (double)(w - 1) * (more0 + more * k) + load * 1e-8 * (double)t * (bm + bn) * a.K + store * 1e-6 * (double)a.M * a.N +
+           (double)(cdiv(w, held) - 1) * round * k;
   };
-  const double us64 = cost(64, 64, 3.07, 2.35, 0.1, 2.53, 2.69, 0.35), us128x64 = cost(128, 64, 3.33, 3.73, 0.7, 3.84, 3.64, 0.24);
-  const double us128 = cost(128, 128, 4.24, 6.78, 2.09, 5.52, 7.24, 0.0);
-  // eight waves and whole-line loads where both operands are k-major: 5-10 % faster where CUs hold two tiles
-  const double us128x8 = a.tb ? cost(128, 128, 3.17, 8.44, 1.96, 4.15, 5.69, 0.22) : 1e30;
   struct Choice { int variant; double us; };
-  const Choice small[4] = {{3, us64}, {7, us128x64}, {1, us128}, {4, us128x8}};
-  Choice best = small[0];
-  for (const Choice& c : small) if (c.us < best.us) best = c;
-  if (a.M >= 4096) {
-    // 5300 x 1536 x 384 21.7 us on 192x256 tiles, which fill 66 % of two rounds, against 17.1 on 128x128 ones; 5300 x 4096 x
-    // 1024 (input gradient) 75.6 on 128x128 tiles against 63.9.  The lines are a few per cent off, so tiles that fill the CUs
-    // well, and 128x128 ones (8192 x 768 x 3072 58.6 us, on 128x64 ones 61), have the benefit of the doubt.
-    const double us256 = cost(256, 256, 5.74, 19.28, 12.33, 11.44, 3.69, 0.71), us192 = cost(192, 256, 5.98, 14.2, 19.37, 0.0, 7.65, 0.24);
-    if (pp) return 0.93 * (pp == 5 ? us256 : us192) <= best.us ? pp : best.variant;
-    if (us256 < best.us) best = Choice{5, us256};
-    if (us192 < best.us) best = Choice{6, us192};
-    const Choice square = us128x8 < us128 ? small[3] : small[2];
-    if (0.85 * square.us <= best.us) best = square;
-  }
+  Choice best{3, gemm_64_four_stages(a) ? cost(64, 64, 2, 2.97, 3.76, 0.0, 0.0, 1.26, 0.38, 0.0)
+                                        : cost(64, 64, 3, 2.57, 2.52, 0.64, 1.15, 7.16, 0.0, 1.16)};
+  auto consider = [&](int variant, double us) { if (us < best.us) best = Choice{variant, us}; };
+  consider(7, cost(128, 64, 2, 3.21, 5.73, 0.95, 2.08, 1.56, 0.28, 5.38));
+  consider(1, cost(128, 128, 3, 4.48, 9.69, 3.25, 2.11, 5.50, 0.03, 3.94));
+  // Eight waves with whole-line loads where both operands are k-major.  A step with forward products on them (8192 x 3072 x 768
+  // and 8192 x 768 x 3072, alone within 1 % of four waves) was 0.5 % slower.
+  if (a.tb) consider(4, cost(128, 128, 2, 2.41, 13.19, 0.99, 0.02, 3.06, 0.45, 6.08));
+  if (pp == 5) consider(5, cost(256, 256, 1, 17.80, 10.06, 13.11, 11.52, 2.98, 0.05, 0.37));
+  if (pp == 6) consider(6, cost(192, 256, 1, 10.83, 16.12, 20.17, 0.0, 0.01, 0.01, 0.03));
   return best.variant;
 }
 

@@ -61,6 +61,37 @@ def test_variants_take_the_contractions_they_are_given():
                     assert K % need == 0, (M, N, K, tb, v)
 
 
+# us of each variant on a MI355X, weights from HBM: (rows, columns, contraction, input gradient)
+MEASURED = {
+    (520, 1024, 4096, False): {3: 20.2, 7: 26.8, 1: 47.4, 4: 54.6},
+    (1379, 768, 3072, False): {3: 21.6, 7: 22.4, 1: 38.6, 4: 41.9},
+    (1379, 3072, 768, False): {3: 18.5, 7: 19.8, 1: 20.6, 4: 20.2},
+    (2000, 3072, 1024, False): {3: 24.7, 7: 21.5, 1: 21.5, 4: 22.6},
+    (2639, 768, 768, False): {3: 9.4, 7: 8.5, 1: 12.9, 4: 13.7},
+    (2900, 768, 3072, False): {3: 34.0, 7: 31.1, 1: 39.1, 4: 42.5},
+    (3300, 768, 768, False): {3: 12.0, 7: 11.2, 1: 13.5, 4: 13.9},
+    (3152, 1024, 4096, False): {3: 56.6, 7: 43.4, 1: 58.7, 4: 63.0},
+    (3152, 1024, 3072, True): {3: 44.7, 7: 34.3, 1: 44.8, 4: 47.6},
+    (4000, 768, 3072, False): {3: 36.5, 7: 31.9, 1: 40.7, 4: 43.4},
+    (4000, 768, 3072, True): {3: 36.5, 7: 33.2, 1: 43.1, 4: 46.4},
+    (4096, 768, 3072, False): {3: 37.1, 7: 33.2, 1: 43.1, 4: 43.4, 5: 65.6, 6: 56.4},
+    (4400, 768, 2304, True): {3: 34.2, 7: 27.6, 1: 35.7, 4: 37.0, 5: 55.8, 6: 47.2},
+    (4600, 512, 2048, False): {3: 23.6, 7: 21.8, 1: 29.2, 4: 30.9, 5: 47.7, 6: 40.9},
+    (6500, 384, 1536, False): {3: 18.5, 7: 17.4, 1: 22.1, 4: 23.4, 5: 36.8, 6: 32.1},
+    (8192, 1536, 384, False): {3: 27.6, 7: 25.8, 1: 25.2, 4: 24.4, 5: 28.2, 6: 38.9},
+    (8192, 768, 3072, True): {3: 70.9, 7: 61.9, 1: 64.0, 4: 59.0, 5: 78.1, 6: 65.2},
+    (8192, 3072, 768, True): {3: 74.8, 7: 65.6, 1: 62.8, 4: 53.9, 2: 57.0, 5: 60.4, 6: 67.3},
+    (12608, 768, 3072, False): {3: 109.6, 7: 91.0, 1: 89.4, 4: 91.0, 5: 78.4, 6: 68.1},
+    (12608, 2304, 768, False): {3: 83.4, 7: 72.4, 1: 63.2, 4: 61.7, 5: 53.2, 6: 62.2},
+}
+
+
+@pytest.mark.parametrize("shape", MEASURED)
+def test_tiles_are_near_the_fastest_measured(shape):
+    us = MEASURED[shape]
+    assert us[R.dma_variant(*shape)] <= 1.05 * min(us.values())
+
+
 @pytest.mark.parametrize("name", G.CASES)
 def test_gpu_cases_take_the_kernels_they_are_there_for(name):
     G.takes_its_kernels(name)
