@@ -407,7 +407,7 @@ struct LeanTile {
     src = reinterpret_cast<const char*>(p + (L::K_MAJOR ? r0 * ld + k0 : k0 * ld + r0));
     step = L::K_MAJOR ? L::KW * 2 : L::KW * ld * 2;
 #pragma unroll
-    for (int i = 0; i < L::LOADS; ++i) voff[i] = (unsigned)(reinterpret_cast<const char*>(tile.gp[i]) - src);   // below 2^31: gemm_dma_ok
+    for (int i = 0; i < L::LOADS; ++i) voff[i] = (unsigned)(reinterpret_cast<const char*>(tile.gp[i]) - src);   // below 2^32: gemm_lean_ok
     for (auto& f : tile.foff) f += lds0;
   }
   // klim (TAIL only): k values of the tile that exist; lanes whose k lies past them fetch zeros
@@ -1151,7 +1151,7 @@ static void dispatch_fwd(const Gemm& a, hipStream_t st) {
 // (18 us).  K is split over more workgroups into fp32 slabs in the caller's workspace, and a small kernel
 // sums the slabs in order and applies the epilogue.
 bool gemm_dma_skinny(const Gemm& a, hipStream_t st) {
-  if (a.ta || a.M > 128 || a.K < 1536 || !a.ws || !gemm_dma_ok(a)) return false;
+  if (a.ta || a.M > 128 || a.K < 1536 || !a.ws || !gemm_dma_ok(a) || !gemm_lean_ok(a)) return false;
   int splits = cdiv(a.K, 64) / 6;   // at least six k tiles per split
   if (splits > 16) splits = 16;
   const int64_t mn = (int64_t)a.M * a.N;

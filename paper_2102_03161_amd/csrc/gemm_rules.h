@@ -26,10 +26,17 @@ inline bool gemm_combo_used(const Gemm& a) {
 // what the asynchronous kernels need: 16-byte pieces of every operand
 inline bool gemm_dma_ok(const Gemm& a) {
   if (!aligned_to(a.A, 16) || !aligned_to(a.B, 16) || a.lda % 8 || a.ldb % 8 || a.K < 1) return false;
-  if (a.lda >= (1 << 23) || a.ldb >= (1 << 23)) return false;   // 128 rows lie within 2^31 bytes: 32-bit offsets
   if (a.ta && (a.M % 8 || a.M < 8)) return false;      // strided operands: 16-byte pieces along the rows
   if (!a.tb && (a.N % 8 || a.N < 8)) return false;
   return (a.ta && !a.tb) || a.K % 8 == 0;              // a k-major operand: 16-byte pieces along k
+}
+
+// What the lean k loop needs besides (64-column tiles, small weight gradients): a tile's rows, at most 128 of a k-major operand
+// and 64 of a strided one, within the 2^32 bytes that a lane's unsigned offset spans.  Only the head's products over the first
+// tokens of long sequences have rows far enough apart.
+inline bool gemm_lean_ok(const Gemm& a) {
+  auto within = [](bool k_major, int64_t rows, int64_t ld) { return ((k_major ? std::min<int64_t>(rows, 128) : 64) - 1) * ld * 2 + 256 < ((int64_t)1 << 32); };
+  return within(!a.ta, a.M, a.lda) && within(a.tb, a.N, a.ldb);
 }
 
 // What the register-staged kernel needs: 16-byte pieces along k of a k-major operand, pairs along the rows of a
@@ -79,6 +86,7 @@ inline bool gemm_64_four_stages(const Gemm& a) {
 inline int gemm_dma_variant(const Gemm& a) {
   auto cdiv = [](int64_t x, int64_t y) { return (x + y - 1) / y; };
   const double k = 1e-3 * a.K;
+  const bool lean = gemm_lean_ok(a);
   if (a.K % 64) {
     // 64x64 or 128x128 tiles.  Microseconds fitted to launches of 17 to 8192 rows with N and K of 768 to 3072 (k = K / 1000): a
     // 128x128 workgroup alone 5.7 + 8.9 k, w of them w (5.3 + 7.0 k); a 64x64 workgroup alone 3.5 + 4.7 k, w of them
@@ -89,7 +97,7 @@ inline int gemm_dma_variant(const Gemm& a) {
     const double w128 = (double)((t128 + 255) / 256), w64 = (double)((t64 + 255) / 256);
     const double us128 = w128 > 1 ? w128 * (5.3 + 7.0 * k) : 5.7 + 8.9 * k;
     const double us64 = w64 > 1 ? w64 * (1.9 + 3.05 * k) : 3.5 + 4.7 * k;
-    if (us64 <= us128) return 3;
+    if (lean && us64 <= us128) return 3;
     // K no multiple of 32: of the 128x128 tiles only eight waves on 64-wide k tiles take it (16384 x 1152 x 4304 228 us against 349 on 64x64
     // tiles and 235 on four waves with 32-wide ones; input gradients 254, 346, 273; 8192 x 3072 x 776 65, 98, 74)
     return a.K % 32 ? 4 : 1;
@@ -136,11 +144,13 @@ inline int gemm_dma_variant(const Gemm& a) {
            (double)(cdiv(w, held) - 1) * round * k;
   };
   struct Choice { int variant; double us; };
-  Choice best{3, gemm_64_four_stages(a) ? cost(64, 64, 2, 2.97, 3.76, 0.0, 0.0, 1.26, 0.38, 0.0)
-                                        : cost(64, 64, 3, 2.57, 2.52, 0.64, 1.15, 7.16, 0.0, 1.16)};
+  Choice best{1, cost(128, 128, 3, 4.48, 9.69, 3.25, 2.11, 5.50, 0.03, 3.94)};
   auto consider = [&](int variant, double us) { if (us < best.us) best = Choice{variant, us}; };
-  consider(7, cost(128, 64, 2, 3.21, 5.73, 0.95, 2.08, 1.56, 0.28, 5.38));
-  consider(1, cost(128, 128, 3, 4.48, 9.69, 3.25, 2.11, 5.50, 0.03, 3.94));
+  if (lean) {
+    consider(3, gemm_64_four_stages(a) ? cost(64, 64, 2, 2.97, 3.76, 0.0, 0.0, 1.26, 0.38, 0.0)
+                                       : cost(64, 64, 3, 2.57, 2.52, 0.64, 1.15, 7.16, 0.0, 1.16));
+    consider(7, cost(128, 64, 2, 3.21, 5.73, 0.95, 2.08, 1.56, 0.28, 5.38));
+  }
   // Eight waves with whole-line loads where both operands are k-major.  A step with forward products on them (8192 x 3072 x 768
   // and 8192 x 768 x 3072, alone within 1 % of four waves) was 0.5 % slower.
   if (a.tb) consider(4, cost(128, 128, 2, 2.41, 13.19, 0.99, 0.02, 3.06, 0.45, 6.08));
@@ -183,7 +193,9 @@ inline WgradTiling wgrad_tiling(const Gemm* a, int n) {
     if (s > 1) us += 4.0 + (s + 1) * floats * 1e-6;
     if (us < best_us) { best_us = us; best = WgradTiling{b, s}; }
   };
-  for (int s = 1; s <= 4 && (s == 1 || a[0].K >= 512 * s); s *= 2) {
+  bool lean = true;
+  for (int i = 0; i < n; ++i) lean = lean && gemm_lean_ok(a[i]);
+  for (int s = 1; lean && s <= 4 && (s == 1 || a[0].K >= 512 * s); s *= 2) {
     consider(64, s, 3.6, 7.1, 1.2, 3.75);
     consider(128, s, 4.7, 12.5, 4.0, 9.8);
   }

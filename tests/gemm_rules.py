@@ -25,6 +25,18 @@ extern "C" int path(int dt, int M, int N, int K, int ta, int tb, int epi, int c_
   return gemm_path(dt, make(M, N, K, ta, tb, epi, c_f32, 0));
 }
 extern "C" int dma_variant(int M, int N, int K, int tb) { return gemm_dma_variant(make(M, N, K, 0, tb, EPI_STORE, 0, 0)); }
+// a forward product whose first operand's rows are lda elements apart: path, variant, whether the lean k loop takes it
+extern "C" int far_rows(int M, int N, int K, long long lda) {
+  Gemm g = make(M, N, K, 0, 0, EPI_BIAS, 1, 0);
+  g.lda = lda;
+  return gemm_path(1, g) * 100 + gemm_dma_variant(g) * 10 + gemm_lean_ok(g);
+}
+// the tile of a weight gradient over the same rows
+extern "C" int far_wgrad(int M, int N, int K, long long lda) {
+  Gemm g = make(M, N, K, 1, 0, EPI_STORE, 1, 1 << 24);
+  g.lda = lda;
+  return wgrad_tiling(&g, 1).tile * 10 + gemm_lean_ok(g);
+}
 // a block's four weight gradients with the workspace that the plan gives them at least
 extern "C" int block_wgrads(int D, int F, int tokens) {
   const size_t ws = gemm_wgrad_batch_ws_floats(D, F);
@@ -61,6 +73,7 @@ def lib():
             subprocess.run(["g++", "-std=c++17", "-O1", "-fPIC", "-shared", "-I", CSRC, "-x", "c++", "-", "-o", so],
                            input=SOURCE.encode(), check=True)
             _lib = ctypes.CDLL(so)
+        _lib.far_rows.argtypes = _lib.far_wgrad.argtypes = [ctypes.c_int] * 3 + [ctypes.c_longlong]
         _lib.reg_tiling.argtypes = [ctypes.c_int] * 6 + [ctypes.c_longlong]
     return _lib
 
@@ -84,6 +97,18 @@ T128, T256x128, T64, T128_EIGHT_WAVES, TWO_GROUPS_256, TWO_GROUPS_192, T128x64 =
 def dma_variant(M, N, K, tb=False):
     """tiles of a forward (tb: input-gradient) product"""
     return lib().dma_variant(M, N, K, int(tb))
+
+
+def far_rows(M, N, K, lda):
+    """(path, variant, lean) of a forward product over rows lda elements apart"""
+    r = lib().far_rows(M, N, K, lda)
+    return r // 100, r // 10 % 10, bool(r % 10)
+
+
+def far_wgrad(M, N, K, lda):
+    """(tile, lean) of a weight gradient over rows lda elements apart"""
+    r = lib().far_wgrad(M, N, K, lda)
+    return r // 10, bool(r % 10)
 
 
 def reg_tiling(M, N, K, ta, epi=STORE, c_f32=False, ws_floats=0):

@@ -92,6 +92,21 @@ def test_tiles_are_near_the_fastest_measured(shape):
     assert us[R.dma_variant(*shape)] <= 1.05 * min(us.values())
 
 
+@pytest.mark.parametrize("S,D", [(512, 1024), (4096, 2048), (8192, 1024), (8192, 2048), (16384, 2048), (32768, 2048)])
+@pytest.mark.parametrize("rows", [1, 4, 64, 100, 128, 512])
+def test_rows_far_apart_stay_on_the_asynchronous_kernels(rows, S, D):
+    """The head's products over first tokens: rows S * D elements apart.  A lane's offsets within a tile are 32 bits wide
+    in the kernels of 64-column tiles and small weight gradients, which take what fits and no more."""
+    lda = S * D
+    path, variant, lean = R.far_rows(rows, 8, D, lda)
+    assert path == R.DMA
+    assert lean == ((min(rows, 128) - 1) * lda * 2 + 256 < 2 ** 32)
+    assert lean or variant not in (R.T64, R.T128x64)
+    tile, lean = R.far_wgrad(D, 8, rows, lda)
+    assert lean == (63 * lda * 2 + 256 < 2 ** 32)
+    assert lean or tile == 256
+
+
 @pytest.mark.parametrize("name", G.CASES)
 def test_gpu_cases_take_the_kernels_they_are_there_for(name):
     G.takes_its_kernels(name)
