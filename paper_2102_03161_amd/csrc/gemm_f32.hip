@@ -573,7 +573,7 @@ void launch_dma(const Gemm* a, int n, hipStream_t st) {
 }
 
 void choose_f32(const Gemm* a, int n, bool vec, hipStream_t st) {
-  const F32Tile t = gemm_f32_tile(a, n);
+  const F32Tile t = gemm_f32_tile(a, n, vec);
   if (vec) {
     if (t.tm == 4) launch_dma<4, 4, 3>(a, n, st);
     else if (t.tn == 3) launch_dma<2, 3, 3>(a, n, st);

@@ -222,16 +222,23 @@ inline size_t gemm_wgrad_batch_ws_floats(int D, int F) {
 // all tiles, the stores.  The choice is 0.7 % off the fastest tile on average.  1576 x 768 x 768: 1200 tiles of 32x32 25 us,
 // 300 of 64x64 33; 4081 x 768 x 3072: 512 of 64x96 176 us, 768 of 64x64 181, 3072 of 32x32 224; 4081 x 1024 x 4096: 256 of
 // 128x128 279 us, 1024 of 64x64 324.
+// pipeline false: the kernel that stages its tiles through registers, element by element (rows that are no 16-byte pieces: odd
+// patches and class counts), with lines of its own, fitted to 492 forward products, input and weight gradients of such sizes;
+// the choice is 0.3 % off the fastest tile on average, by the pipeline's lines 1.6 % (6400 x 256 x 363 37 us on 32x32 tiles, 29 on
+// 64x64).
 struct F32Tile { int tm, tn; };
-inline F32Tile gemm_f32_tile(const Gemm* a, int n) {
+inline F32Tile gemm_f32_tile(const Gemm* a, int n, bool pipeline = true) {
   const double k = 1e-3 * a[0].K;
   struct Line { int tm, tn; double one0, one, more0, more, load, store; };
-  static const Line lines[5] = {{1, 1, 2.85, 7.44, 0.11, 5.4, 0.0, 0.67}, {1, 2, 3.27, 11.37, 0.4, 9.87, 1.52, 0.43},
+  static const Line piped[5] = {{1, 1, 2.85, 7.44, 0.11, 5.4, 0.0, 0.67}, {1, 2, 3.27, 11.37, 0.4, 9.87, 1.52, 0.43},
                                 {2, 2, 3.72, 18.18, 0.18, 16.85, 5.75, 0.97}, {2, 3, 4.45, 26.08, 1.08, 24.85, 6.45, 0.79},
                                 {4, 4, 6.49, 62.45, 0.0, 70.09, 7.21, 1.36}};
+  static const Line staged[4] = {{1, 1, 2.73, 16.07, 0.07, 9.0, 6.59, 1.29}, {1, 2, 3.51, 24.75, 0.67, 10.98, 16.55, 0.13},
+                                 {2, 2, 4.21, 39.4, 0.75, 20.55, 11.82, 0.59}, {4, 4, 6.82, 98.64, 0.04, 79.47, 1.35, 1.39}};
   F32Tile best{1, 1};
   double best_us = 1e300;
-  for (const Line& l : lines) {
+  for (int j = 0; j < (pipeline ? 5 : 4); ++j) {
+    const Line& l = pipeline ? piped[j] : staged[j];
     int64_t t = 0;
     double out = 0.0;
     for (int i = 0; i < n; ++i) {
@@ -240,7 +247,7 @@ inline F32Tile gemm_f32_tile(const Gemm* a, int n) {
     }
     const int64_t w = (t + 255) / 256;
     double us = l.one0 + l.one * k + (double)(w - 1) * (l.more0 + l.more * k) + l.load * 1e-8 * (double)t * 32 * (l.tm + l.tn) * a[0].K + l.store * out;
-    if (l.tm == 4 && t * 10 >= w * 256 * 9) us *= 0.93;   // whole rounds of the largest tiles run a little ahead of the line
+    if (pipeline && l.tm == 4 && t * 10 >= w * 256 * 9) us *= 0.93;   // whole rounds of the largest tiles run a little ahead of the line
     if (us < best_us) { best_us = us; best = F32Tile{l.tm, l.tn}; }
   }
   return best;

@@ -50,6 +50,12 @@ extern "C" int f32_tile(int M, int N, int K, int ta, int tb) {
   const F32Tile t = gemm_f32_tile(&g, 1);
   return t.tm * 10 + t.tn;
 }
+// the same in the kernel that stages its tiles through registers
+extern "C" int f32_staged_tile(int M, int N, int K, int ta, int tb) {
+  const Gemm g = make(M, N, K, ta, tb, EPI_STORE, 1, 0);
+  const F32Tile t = gemm_f32_tile(&g, 1, false);
+  return t.tm * 10 + t.tn;
+}
 extern "C" int f32_block_wgrads(int D, int F, int tokens) {
   const Gemm g[4] = {make(F, D, tokens, 1, 0, EPI_STORE, 1, 0), make(D, F, tokens, 1, 0, EPI_STORE, 1, 0),
                      make(D, D, tokens, 1, 0, EPI_STORE, 1, 0), make(D, 3 * D, tokens, 1, 0, EPI_STORE, 1, 0)};
@@ -126,6 +132,11 @@ def block_wgrads(D, F, tokens):
 def f32_tile(M, N, K, tb=False):
     """tile of an fp32 forward (tb: input-gradient) product, in units of 32"""
     return divmod(lib().f32_tile(M, N, K, 0, int(tb)), 10)
+
+
+def f32_staged_tile(M, N, K, ta=False, tb=False):
+    """the same for rows that are no 16-byte pieces"""
+    return divmod(lib().f32_staged_tile(M, N, K, int(ta), int(tb)), 10)
 
 
 def f32_block_wgrads(D, F, tokens):

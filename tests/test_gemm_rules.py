@@ -120,6 +120,24 @@ def test_other_gpu_tests_take_the_weight_gradients_they_are_there_for():
     assert R.block_wgrads(768, 3072, 64 * 197) == (256, 2)
 
 
+# us of 32x32, 32x64, 64x64 and 128x128 tiles on a MI355X, staged through registers: (rows, columns, contraction)
+MEASURED_STAGED = {
+    (197, 768, 147): (5.6, 7.6, 10.7, 26.3),
+    (800, 768, 147): (8.8, 9.7, 11.0, 26.6),
+    (1568, 1024, 363): (36.4, 32.0, 29.1, 49.0),
+    (2500, 256, 49): (5.4, 6.3, 7.2, 17.2),
+    (6400, 256, 363): (36.7, 32.2, 29.1, 48.6),
+    (8192, 1024, 147): (62.0, 52.7, 47.2, 44.1),
+    (12544, 256, 363): (59.4, 52.1, 51.4, 50.1),
+}
+
+
+@pytest.mark.parametrize("shape", MEASURED_STAGED)
+def test_fp32_staged_tiles_are_near_the_fastest_measured(shape):
+    us = dict(zip([(1, 1), (1, 2), (2, 2), (4, 4)], MEASURED_STAGED[shape]))
+    assert us[R.f32_staged_tile(*shape)] <= 1.05 * min(us.values())
+
+
 def test_fp32_tiles():
     rows = {50: (1, 1), 450: (1, 2), 2000: (2, 2), 4081: (4, 4)}
     assert {m: R.f32_tile(m, 1024, 768) for m in rows} == rows

@@ -174,6 +174,18 @@ def test_fp32_products_on_the_largest_tiles(torch_mod):
     check_fp32_step(torch_mod, dict(BERT, L=1, D=256, H=4, F=1024, S=77, max_pos=80, B=53, dtype="f32"), 8)
 
 
+# samples of 64 patches of 147 values, width 512: tiles of the patch embedding, staged through registers
+STAGED = {3: (1, 1), 31: (1, 2), 51: (2, 2), 255: (4, 4)}
+
+
+@pytest.mark.parametrize("nb", STAGED)
+def test_fp32_tiles_staged_through_registers(torch_mod, nb):
+    """fp32 mode: an odd contraction, forward and (rows of 147) in the weight gradient, on each tile size."""
+    assert R.f32_staged_tile(64 * nb, 512, 147) == STAGED[nb]
+    print(f"fp32 staged tiles: nb={nb}", flush=True)
+    check_fp32_step(torch_mod, dict(VIT, patch=7, S=65, L=1, D=512, H=8, F=64, n_out=10, B=nb, dtype="f32"), 10)
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_prefix_rows_do_not_depend_on_the_tiles(torch_mod, dtype):
     """3250 rows take 128x128 tiles in the wide products, 50 and 350 rows smaller ones."""
