@@ -57,7 +57,7 @@ def test_variants_take_the_contractions_they_are_given():
             for K in range(8, 4400, 8):
                 for tb in (False, True):
                     v = R.dma_variant(M, N, K, tb)
-                    need = {R.T128: 32, R.T256x128: 32, R.TWO_GROUPS_256: 64, R.TWO_GROUPS_192: 64}.get(v, 8)
+                    need = {R.T128: 32, R.T256x128: 32, R.TWO_GROUPS_256: 64, R.TWO_GROUPS_192: 64, R.T128x64: 64}.get(v, 8)
                     assert K % need == 0, (M, N, K, tb, v)
 
 
@@ -141,6 +141,7 @@ def test_fp32_staged_tiles_are_near_the_fastest_measured(shape):
 def test_fp32_tiles():
     rows = {50: (1, 1), 450: (1, 2), 2000: (2, 2), 4081: (4, 4)}
     assert {m: R.f32_tile(m, 1024, 768) for m in rows} == rows
+    assert R.f32_tile(1576, 768, 3072) == R.f32_tile(1576, 768, 2304, tb=True) == (2, 3)
 
 
 def test_weight_gradients_are_not_cut_finer_than_their_k_tiles():

@@ -160,12 +160,30 @@ def check_fp32_step(torch, w, seed):
     H.compare_step(w, g, o, 0, 1e-4, rss=H.summand_rss(w, vals, x, y, 0))
 
 
-@pytest.mark.parametrize("nb,F", [(1, 3072), (9, 3072), (40, 3072), (3, 1028)])
+# tiles of a block's forward products and input gradients of 50 rows per sample, and of its weight gradients
+FP32_EDGES = {(1, 3072): ({(1, 1)}, (1, 1)), (9, 3072): ({(1, 1), (1, 2), (2, 3)}, (2, 2)), (40, 3072): ({(2, 2), (2, 3)}, (2, 2)),
+              (3, 1028): ({(1, 1), (1, 2)}, (2, 2))}
+
+
+@pytest.mark.parametrize("nb,F", FP32_EDGES)
 def test_fp32_products_at_tile_edges(torch_mod, nb, F):
-    """fp32 mode: 50, 450 and 2000 rows take 32x32, 32x64 and 64x64 tiles; ten classes and the widths that are no
-    multiple of the tiles take the element-wise loads and the ragged edges."""
+    """fp32 mode: 50, 450 and 2000 rows of width 768 and MLP width 3072 take 32x32 tiles, these with 32x64 and 64x96 ones, and
+    64x64 and 64x96 ones, their weight gradients 32x32 and 64x64; ten classes take the register-staged loads, a width of 1028
+    the ragged edges."""
     print(f"fp32 tile edges: nb={nb} F={F}", flush=True)
+    D, rows = 768, 50 * nb
+    forward = {R.f32_tile(rows, N, K) for N, K in [(3 * D, D), (D, D), (F, D), (D, F)]}
+    backward = {R.f32_tile(rows, N, K, tb=True) for N, K in [(D, 3 * D), (D, D), (D, F), (F, D)]}
+    assert (forward | backward, R.f32_block_wgrads(D, F, rows)) == FP32_EDGES[nb, F]
     check_fp32_step(torch_mod, dict(VIT, L=2, D=768, H=12, F=F, n_out=10, B=nb, dtype="f32"), 6)
+
+
+@pytest.mark.parametrize("S,nb", [(203, 1), (77, 7)])
+def test_fp32_weight_gradients_on_the_largest_tiles(torch_mod, S, nb):
+    """fp32 mode, width 1024: a block's weight gradients on 128x128 tiles over six k tiles and 11 tokens, sixteen and 27."""
+    assert R.f32_block_wgrads(1024, 4096, S * nb) == (4, 4)
+    print(f"fp32 weight gradients of width 1024 over {S * nb} tokens", flush=True)
+    check_fp32_step(torch_mod, dict(BERT, L=1, D=1024, H=16, F=4096, S=S, max_pos=203, B=nb, dtype="f32"), 11)
 
 
 def test_fp32_products_on_the_largest_tiles(torch_mod):
