@@ -244,6 +244,70 @@ def test_host_tier_is_invisible_to_the_result(torch_mod, w):
     plain.close()
 
 
+def test_host_rows_staged_in_any_order(torch_mod):
+    """Rows of neighbouring ids in neighbouring window slots are staged in one copy: ascending, descending and broken runs of
+    ids, runs whose slots do not follow each other, batches with staged and new rows, and a window that fills up in the
+    middle of a run give what an all-HBM context gives, bit for bit, and every row is counted."""
+    torch = torch_mod
+    w = MID_VIT
+    nb, hbm, n_ids = 4, 2, 26
+    tiered = binding.Context(binding.make_config(w, B=nb, cache_slots=hbm, host_slots=n_ids - hbm, window_slots=2 * nb))
+    plain = binding.Context(binding.make_config(w, B=nb, cache_slots=n_ids))
+    vals = H.init_values(w, plain, 31)
+    xs, _ = H.batch_for(w, 31, n_ids, "pool")
+    want = {}
+    for c in (tiered, plain):
+        H.load_params(c, vals)
+        c.set_freeze_boundary(1)
+    for i in range(0, n_ids, nb):                           # misses: every row is written, ascending
+        ids = list(range(i, min(i + nb, n_ids)))
+        for c in (tiered, plain):
+            c.frozen_forward(H.to_dev(torch, xs[ids]), ids)
+        rows = raw_hk(plain, w, len(ids))
+        want.update({sid: rows[j].copy() for j, sid in enumerate(ids)})
+    garbage = H.to_dev(torch, np.zeros_like(xs[:nb]))       # hits do not look at the input
+
+    def forward(ids):
+        print(f"host rows in order {ids}", flush=True)
+        before = tiered.host_tier_stats()
+        tiered.frozen_forward(garbage[:len(ids)].contiguous(), ids)
+        got = raw_hk(tiered, w, len(ids))
+        for j, sid in enumerate(ids):
+            assert np.array_equal(got[j], want[sid]), (ids, sid)
+        after = tiered.host_tier_stats()
+        copied, staged = (after[n] - before[n] for n in ("rows_to_device", "prefetched_used"))
+        assert copied + staged == sum(sid >= hbm for sid in ids)
+        return staged
+
+    def prefetch(ids):
+        before = tiered.host_tier_stats()
+        n = tiered.cache_prefetch(ids)
+        after = tiered.host_tier_stats()
+        assert after["prefetched"] - before["prefetched"] == after["rows_to_device"] - before["rows_to_device"] == n
+        return n
+
+    for ids in ([2, 3, 4, 5], [9, 8, 7, 6], [10, 12, 14, 16], [20, 3, 21, 22], [25, 0, 24, 1], [4, 5, 11, 12]):
+        assert forward(ids) == 0
+    # staged and new rows in one batch: the new ones' slots lie around the staged ones'
+    for ahead, ids in (([13, 14], [12, 13, 14, 15]), ([19, 17], [16, 17, 18, 19]), ([23, 0, 24], [25, 24, 23, 22])):
+        assert prefetch(ahead) == sum(sid >= hbm for sid in ahead) == forward(ids)
+    assert prefetch([6, 7, 8]) == 3 and forward([7, 9, 10, 11]) == 1       # the slot between two staged rows is free again
+    assert prefetch(list(range(10, n_ids))) == 2 * nb - 2                  # the run goes on behind them and ends with the window
+    assert prefetch(list(range(hbm, n_ids))) == 0                          # the window is full
+    assert forward([20, 21, 22, 23]) == 0                                  # takes the slots of the oldest staged rows
+    assert forward([6, 8, 10, 11]) == 0                                    # which were these
+    for i in range(hbm, n_ids, nb):
+        forward(list(range(i, i + nb)))
+    for i in range(n_ids - nb, hbm - 1, -nb):
+        assert forward(list(range(i + nb - 1, i - 1, -1))) == 0
+    for sid in range(n_ids):
+        ra, ka = tiered.cache_row(sid)
+        rb, kb = plain.cache_row(sid)
+        assert ka == kb == 1 and np.array_equal(ra, rb), sid
+    tiered.close()
+    plain.close()
+
+
 def test_cache_timing_profiler(torch_mod):
     """pt_time_frozen_forward: counts what it ran, leaves the batch's h_k in place, and refuses contexts with
     nothing to time."""
