@@ -390,10 +390,13 @@ __device__ __forceinline__ void dma_run(const GemmDev<bf16>& g, const SplitArgs&
 // A wave of a 64x64 tile has four MFMAs in a k tile and spent 88 instructions on it, at five to eight cycles each where it
 // is alone on its SIMD.  Here a tile's source is one pointer per wave, with 32-bit lane offsets that never change, the loop
 // has a copy of its body per stage, so that LDS addresses are immediates, and whole k tiles and a last partial one go
-// separate ways: 54 instructions.  231 x 256 x 1024 7.7 -> 5.5 us, 77 x 768 x 3072 16.5 -> 13.3, 1379 x 2304 x 768 16.8 ->
-// 14.4; weight gradients of width 768 over 2639 tokens 62.3 -> 58.4.  Tiles of 128 columns and more gain up to 6 % alone and
-// lose up to 1 % of a whole step, launches around them included (BERT-base classification 6710 -> 6785 us): they keep
-// dma_run and pp_run.
+// separate ways: 54 instructions.  In a loop over one set of operands 231 x 256 x 1024 7.7 -> 5.5 us, 77 x 768 x 3072 16.5 ->
+// 13.3, 1379 x 2304 x 768 16.8 -> 14.4; weight gradients of width 768 over 2639 tokens 62.3 -> 58.4.  In a step, where weights
+// come from beyond the L2s and are waited for, it saves less: 1379 x 768 with K of 768 to 3072 15.9 -> 15.5 us on average, input
+// gradients 15.6 -> 15.1; 1379 x 3072 x 768 20.3 -> 19.0; 231 x 768 x 256 4.7 -> 4.4; with a fourth stage as well (below) 231 x 256
+// with K of 768 and 1024 7.3 -> 5.8; weight gradients over 1379 tokens 32.2 -> 30.5, 2639 tokens 53.7 -> 51.9.  Tiles of 128 columns and more gain up
+// to 6 % alone and lose up to 1 % of a whole step, launches around them included (BERT-base classification 6710 -> 6785 us):
+// they keep dma_run and pp_run.
 // Fragments read one whole k tile ahead into a second register set (which takes the LDS latency out of a tile's chain)
 // were slower: 1344 x 768 x 3072 13.1 -> 14.4 us.
 template <typename L>

@@ -162,16 +162,21 @@ inline int gemm_dma_variant(const Gemm& a) {
 // A block's weight gradients in one launch of the asynchronous kernels: square tiles (256: the two-group kernel, 64 and 128:
 // the single-role pipeline) and the number of parts that the contraction is cut into, as far as the workspace of the
 // first product has room for their slabs.
-// Microseconds of a launch, fitted to launches over a block's four matrices of widths 256 and 768 with 231 to 12608
-// tokens (within 15 %; k = tokens / 1000, s splits, w workgroups on the fullest CU):
+// Microseconds of a launch (k = tokens / 1000, s splits, w workgroups on the fullest CU):
 //   64x64 tiles    the larger of 3.6 + 7.1 k / s (one workgroup's own chain) and w (1.2 + 3.75 k / s)
 //   128x128 tiles  the larger of 4.7 + 12.5 k / s and w (4 + 9.8 k / s)
 //   256x256 tiles  w (10 + 26 k / s)
 // and for s > 1 the slabs' summation at 4 TB/s, also where it rides on another launch (WgradCarry).
-// Width 768: 1379 tokens 34 us on 128x128 tiles against 43 on 64x64 ones, 2639 tokens 58 against 67 on 256x256 ones
-// with two splits (a step of 2 x 2639 tokens, four blocks frozen, 5920 us against 6300), 8192 tokens 131 us on 256x256
-// ones against 164 by the line above on 128x128; width 256: 231 tokens 5.2 us on 64x64 tiles, 2310 tokens 20 against
-// 34 on 128x128 ones.
+// The lines were fitted at widths 256 and 768 (231 to 12608 tokens, within 15 %) to an older k loop of the two smaller tiles.
+// Of the present kernels, at widths 128 to 1280 and 17 to 16384 tokens, with the first operand from HBM, they are off by 12 %
+// on average for 128 and 256, 21 % for 64x64 tiles (up to 63 %), and say too much by 7 to 18 % for split launches.  The
+// choice suffers less: 1.5 % off the fastest on average over 262 such launches, more than 5 % for 29 of them.  The worst are
+// width 384 from 4096 tokens on (6500 tokens 57 us on 64x64 tiles, 44 on 128x128 ones with four splits), width 512 from 4096 to
+// 4400 (61, on 256x256 tiles 51) and width 768 from 4400 to 5500 (98 to 85 on 256x256 tiles, which also carry the passes that ride
+// there, 93 to 77 on 128x128 ones).
+// Width 768, alone: 1379 tokens 31 us on 128x128 tiles, 47 on 64x64 ones; 2639 tokens 50, on 256x256 ones with two splits 61;
+// 8192 tokens 126 on 256x256 ones, 134 on 128x128.  Width 256: 231 tokens 5.4 us on 64x64 tiles, 7.3 on 128x128; 2310 tokens
+// 16 to 17, on 128x128 18 to 27.
 struct WgradTiling { int tile, splits; };
 inline WgradTiling wgrad_tiling(const Gemm* a, int n) {
   const double k = 1e-3 * a[0].K;
